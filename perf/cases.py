@@ -366,8 +366,9 @@ def _dot(a, b):
 
 
 def _bicgstab(op, b, tol=2e-13, most=400):
+    # a random shadow vector: with the residual itself a point source breaks down at once
     x, r = torch.zeros_like(b), b.clone()
-    rh, p = r.clone(), r.clone()
+    rh, p = _gauss(_gen(1), b.shape), r.clone()
     rho, bb = _dot(rh, r), float(_dot(b, b).real)
     for _ in range(most):
         v = op(p)
