@@ -113,7 +113,7 @@ struct JobTable : JobTableBase {
 
 // Upload several non-empty tables with one host-to-device copy into mem (grown when too small;
 // tables still holding the previous buffer keep it alive).
-void upload_tables(hipStream_t s, std::shared_ptr<DevMem>& mem, std::initializer_list<JobTableBase*> tables);
+void upload_tables(hipStream_t s, std::shared_ptr<DevMem>& mem, const std::vector<JobTableBase*>& tables);
 
 // ---------------------------------------------------------------- gauge handle
 } // namespace wd
@@ -178,6 +178,9 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
              hipStream_t s, double bytes_per_site_total, int stage = -1, int ntl = -1);
 void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s,
                double bytes_total);
+// the block update of the shifted systems (launch_shift_update), timed as a sweep
+void run_shift_update(int nb, const ShiftVectors& v, long n, const ShiftBlock* blk, const ShiftCoef* coef,
+                      hipStream_t s, double bytes_total);
 
 int spinor_fmt_of(wd_prec p);
 int link_fmt_of(wd_prec p, int recon);

@@ -6,8 +6,8 @@
 //                finisher that updates the solver scalars; the adjoint (DAG) variant serves the
 //                normal equations of CG / CG-M (Sec. 8).
 //  * k_sweep   : the fused BiCGstab vector updates of one iteration (Sec. 5: the x <- x - beta s +
-//                chi w update and its companions), the BiCGstab-M shift sweep (Sec. 6.1), and the
-//                CG / CG-M updates.
+//                chi w update and its companions) and the CG updates (the shifted systems
+//                of BiCGstab-M / CG-M: wd_shift.hip).
 //  * k_finish  : fixed-order sums of the block partials and the scalar recurrences.
 //  * k_guess   : the sequential start vector (Sec. 6.2.1) and its residual without the operator.
 //  * packing   : canonical complex128 layout <-> internal checkerboarded structure of arrays;
@@ -52,17 +52,6 @@ __device__ void finish(SysState* S, const double* tot)
         if (c_abs2(rhAs) == 0.0) { S->status = ST_BREAKDOWN; return; }
         const double2 beta = c_neg(c_div(S->delta, rhAs));
         S->beta = beta;
-        // shifted systems: zeta_{n+1} and beta^sigma_n from the collinearity of the residuals
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            // den = beta alpha (zeta_prev - zeta) + zeta_prev beta_prev (1 - sigma beta)
-            double2 den = c_add(c_mul(c_mul(beta, S->alpha), c_sub(q.zeta_prev, q.zeta)),
-                                c_mul(c_mul(q.zeta_prev, S->beta_prev),
-                                      c_sub(c_real(1.0), c_mul(c_real(q.sigma), beta))));
-            q.zeta_next = c_div(c_mul(c_mul(q.zeta, q.zeta_prev), S->beta_prev), den);
-            q.beta_s = c_div(c_mul(beta, q.zeta_next), q.zeta);
-        }
     } else if constexpr (FIN == FIN_CHI) {
         const double2 aww = make_double2(tot[0], tot[1]);
         const double awaw = tot[2];
@@ -70,13 +59,6 @@ __device__ void finish(SysState* S, const double* tot)
         if (awaw == 0.0) { S->status = ST_BREAKDOWN; return; }
         const double2 chi = make_double2(aww.x / awaw, aww.y / awaw);
         S->chi = chi;
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            double2 d = c_add(c_real(1.0), c_mul(chi, c_real(q.sigma)));
-            q.chi_s = c_div(chi, d);
-            q.rho_next = c_div(q.rho, d);
-        }
     } else if constexpr (FIN == FIN_ALPHA) {
         const double2 d1 = make_double2(tot[0], tot[1]);
         const double rr = tot[2];
@@ -89,57 +71,31 @@ __device__ void finish(SysState* S, const double* tot)
         else if (S->mixed && rr < S->delta_rel2 * S->maxrr) pend = ST_RELIABLE;
         else if (S->iter >= S->maxit) pend = ST_MAXIT;
         else if (c_abs2(d1) == 0.0) pend = ST_BREAKDOWN;
-        S->pending = pend;
-        // no shifted scalars to rotate: commit now instead of in a separate end-of-iteration
-        // finisher. The s update of this iteration is then gated off for a system that stops;
-        // a solver that continues from s (reliable update) applies it before the update.
-        if (S->nshift == 0) S->status = pend;
+        // The s update of this iteration is gated off for a system that stops; a solver that
+        // continues from s (reliable update) applies it before the update.
+        S->status = pend;
         if (!S->dc && rr > S->maxrr) S->maxrr = rr;
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            // alpha^sigma_{n+1} = alpha_{n+1} zeta_{n+1} beta^sigma_n / (zeta_n beta_n)
-            q.alpha_s = c_div(c_mul(c_mul(alpha, q.zeta_next), q.beta_s), c_mul(q.zeta, S->beta));
-            double2 zr = c_mul(q.zeta_next, q.rho_next);
-            if (c_abs2(zr) * rr < S->shift_target2) q.freeze = 1;
+        if (ShiftBlock* B = S->blk) {
+            IterScal& q = B->it[B->count];
+            q.beta = S->beta;
+            q.chi = S->chi;
+            q.alpha = alpha;
+            q.rr = rr;
+            B->count += 1;
         }
         S->alpha = alpha;
         S->delta = d1;
-    } else if constexpr (FIN == FIN_END) {
-        S->status = S->pending;
-        S->beta_prev = S->beta;
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            q.zeta_prev = q.zeta;
-            q.zeta = q.zeta_next;
-            q.rho = q.rho_next;
-            if (q.freeze) { q.active = 0; q.conv_iter = S->iter; }
-        }
-        if (S->nshift > 0) S->rsel ^= 1;
     } else if constexpr (FIN == FIN_RESTART) {
         S->delta = make_double2(tot[0], tot[1]);
         S->rr = tot[2];
         S->maxrr = tot[2];
         S->status = (isfinite(tot[2]) && c_finite(S->delta)) ? ST_RUNNING : ST_NAN;
-        S->pending = S->status;
     } else if constexpr (FIN == FIN_CGA) {
         // CG: alpha_n = |r_n|^2 / <p_n, A p_n> (tot[0] = Re <p, A p>; A Hermitian positive definite)
         const double pAp = tot[0];
         if (!isfinite(pAp)) { S->status = ST_NAN; return; }
         if (!(pAp > 0.0)) { S->status = ST_BREAKDOWN; return; }
-        const double alpha = S->rr / pAp;
-        // CG-M: zeta_{n+1} from the collinearity of the shifted residuals, alpha^s_n = alpha_n zeta_{n+1} / zeta_n
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            const double zp = q.zeta_prev.x, z = q.zeta.x;
-            const double den = zp * S->cga_prev * (1.0 + alpha * q.sigma) + alpha * S->cgb * (zp - z);
-            const double zn = z * zp * S->cga_prev / den;
-            q.zeta_next = c_real(zn);
-            q.alpha_s = c_real(alpha * zn / z);
-        }
-        S->cga = alpha;
+        S->cga = S->rr / pAp;
     } else if constexpr (FIN == FIN_CGB) {
         // CG: beta_{n+1} = |r_{n+1}|^2 / |r_n|^2 (tot[2] = |r_{n+1}|^2) and the exit test
         const double rr = tot[2];
@@ -150,30 +106,18 @@ __device__ void finish(SysState* S, const double* tot)
         else if (rr <= S->target2) pend = ST_CONVERGED;
         else if (S->mixed && rr < S->delta_rel2 * S->maxrr) pend = ST_RELIABLE;
         else if (S->iter >= S->maxit) pend = ST_MAXIT;
-        S->pending = pend;
-        // single system: commit now (the p update of a system that stops is gated off, and a
-        // continuing reliable update applies it first); CG-M commits after its shift sweep
-        if (S->nshift == 0) S->status = pend;
+        // the p update of a system that stops is gated off (a continuing reliable update applies it)
+        S->status = pend;
         if (!S->dc && rr > S->maxrr) S->maxrr = rr;
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            const double g = q.zeta_next.x / q.zeta.x;
-            q.beta_s = c_real(beta * g * g);
-            if (q.zeta_next.x * q.zeta_next.x * rr <= S->shift_target2) q.freeze = 1;
+        if (ShiftBlock* B = S->blk) {
+            IterScal& q = B->it[B->count];
+            q.alpha = c_real(S->cga);
+            q.beta = c_real(beta);
+            q.rr = rr;
+            B->count += 1;
         }
         S->rr = rr;
         S->cgb = beta;
-        S->cga_prev = S->cga;
-    } else if constexpr (FIN == FIN_CGEND) {
-        S->status = S->pending;
-        for (int i = 0; i < S->nshift; i++) {
-            ShiftScal& q = S->sh[i];
-            if (!q.active) continue;
-            q.zeta_prev = q.zeta;
-            q.zeta = q.zeta_next;
-            if (q.freeze) { q.active = 0; q.conv_iter = S->iter; }
-        }
     }
 }
 
@@ -223,16 +167,13 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
     const long i = (long)lb * BLOCK + threadIdx.x;
     const bool ok = i < J.n;
     double v[NRED] = {0.0, 0.0, 0.0, 0.0};
-    const int rsel = S->rsel;
-    const SpinorRef& Rcur = rsel ? J.f[R_F3] : J.f[R_F1];  // OP_W / OP_S / OP_SHIFT role layout
-    const SpinorRef& Rnxt = rsel ? J.f[R_F1] : J.f[R_F3];
 
     if constexpr (OP == OP_W) {
         // w = r + beta A s
         if (ok) {
             const cx<T> beta = cvt<T>(S->beta);
             cx<T> r[12], as[12];
-            load_spinor<SFL, T, true>(Rcur, i, r);
+            load_spinor<SFL, T, true>(J.f[R_F1], i, r);
             load_spinor<SFL, T, true>(J.f[R_F2], i, as);
 #pragma unroll
             for (int k = 0; k < 12; k++) r[k] = r[k] + beta * as[k];
@@ -253,8 +194,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             load_spinor<SFL, T, true>(J.f[R_F4], i, aw);
 #pragma unroll
             for (int k = 0; k < 12; k++) w[k] = w[k] - chi * aw[k];
-            // the new residual goes to the buffer not holding r_n
-            store_spinor<SFL, T, NTS>(rsel ? J.f[R_F1] : J.f[R_F6], i, w);
+            store_spinor<SFL, T, NTS>(J.f[R_F6], i, w);
             cx<T> rh[12];
             load_spinor<SFL, T, true>(J.f[R_F5], i, rh);
 #pragma unroll
@@ -270,53 +210,13 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         if (ok) {
             const cx<T> alpha = cvt<T>(S->alpha), chi = cvt<T>(S->chi);
             cx<T> r[12], s[12], as[12];
-            load_spinor<SFL, T, true>(Rnxt, i, r);
+            load_spinor<SFL, T, true>(J.f[R_F3], i, r);
             load_spinor<SFL, T, true>(J.f[R_F0], i, s);
             load_spinor<SFL, T, true>(J.f[R_F2], i, as);
 #pragma unroll
             for (int k = 0; k < 12; k++) s[k] = r[k] + alpha * (s[k] - chi * as[k]);
             store_spinor<SFL, T, NTS>(J.f[R_F0], i, s);
         }
-
-    } else if constexpr (OP == OP_SHIFT) {
-        // BiCGstab-M: base s update, then every active shifted system
-        //   x^s <- x^s - beta^s s^s + chi^s rho_n zeta_{n+1} w
-        //   s^s <- zeta_{n+1} rho_{n+1} r_{n+1} + alpha^s (s^s - (chi^s/beta^s) rho_n (zeta_{n+1} w - zeta_n r_n))
-        if (ok) {
-            const cx<T> alpha = cvt<T>(S->alpha), chi = cvt<T>(S->chi);
-            cx<T> rn[12], r1[12], w[12], s[12], as[12];
-            load_spinor<SFL, T, true>(Rcur, i, rn);
-            load_spinor<SFL, T, true>(Rnxt, i, r1);
-            load_spinor<SFL, T, true>(J.f[R_F4], i, w);
-            load_spinor<SFL, T, true>(J.f[R_F0], i, s);
-            load_spinor<SFL, T, true>(J.f[R_F2], i, as);
-#pragma unroll
-            for (int k = 0; k < 12; k++) s[k] = r1[k] + alpha * (s[k] - chi * as[k]);
-            store_spinor<SFL, T, NTS>(J.f[R_F0], i, s);
-            const int ns = S->nshift;
-            for (int q = 0; q < ns; q++) {
-                const ShiftScal& Q = S->sh[q];
-                if (!Q.active) continue;
-                const SpinorRef xr = S->shv[2 * q], sr = S->shv[2 * q + 1];
-                const cx<T> bs = cvt<T>(Q.beta_s);
-                const cx<T> cxw = cvt<T>(c_mul(c_mul(Q.chi_s, Q.rho), Q.zeta_next));
-                const cx<T> zr1 = cvt<T>(c_mul(Q.zeta_next, Q.rho_next));
-                const cx<T> as_ = cvt<T>(Q.alpha_s);
-                const cx<T> cb_ = cvt<T>(c_mul(c_div(Q.chi_s, Q.beta_s), Q.rho));
-                const cx<T> zn1 = cvt<T>(Q.zeta_next), zn = cvt<T>(Q.zeta);
-                cx<T> xs[12], ss[12];
-                load_spinor<SFL, T, true>(xr, i, xs);
-                load_spinor<SFL, T, true>(sr, i, ss);
-#pragma unroll
-                for (int k = 0; k < 12; k++) {
-                    xs[k] = xs[k] - bs * ss[k] + cxw * w[k];
-                    ss[k] = zr1 * r1[k] + as_ * (ss[k] - cb_ * (zn1 * w[k] - zn * rn[k]));
-                }
-                store_spinor<SFL, T, NTS>(xr, i, xs);
-                store_spinor<SFL, T, NTS>(sr, i, ss);
-            }
-        }
-
     } else if constexpr (OP == OP_INIT) {
         // r_lo = r_hi; optionally rhat = r_lo, s = r_lo (flags 1, 2), x_lo = 0 (flags 4); CG (flags 8):
         // p = r_lo + beta p with the beta the host set in the record; then <rhat, r_lo>, |r_lo|^2
@@ -418,7 +318,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             store_spinor<SF64, double, NTS>(J.f[R_F0], i, acc);
         }
     } else if constexpr (OP == OP_CGX) {
-        // CG: x += alpha p ; r -= alpha A p ; |r|^2
+        // CG: x += alpha p ; r_{n+1} = r_n - alpha A p ; |r_{n+1}|^2 (R_F2 and R_F4 may be one field)
         if (ok) {
             const T alpha = (T)S->cga;
             cx<T> x[12], p[12], r[12], ap[12];
@@ -431,16 +331,15 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             load_spinor<SFL, T, true>(J.f[R_F3], i, ap);
 #pragma unroll
             for (int k = 0; k < 12; k++) r[k] = r[k] - alpha * ap[k];
-            store_spinor<SFL, T, NTS>(J.f[R_F2], i, r);
+            store_spinor<SFL, T, NTS>(J.f[R_F4], i, r);
             // the norm of the residual as stored
-            load_spinor<SFL, T, true>(J.f[R_F2], i, r);
+            load_spinor<SFL, T, true>(J.f[R_F4], i, r);
 #pragma unroll
             for (int k = 0; k < 12; k++) v[2] += (double)r[k].re * r[k].re + (double)r[k].im * r[k].im;
         }
         write_partials<3>(v, S, J.rblk0 + lb);
-    } else if constexpr (OP == OP_CGP || OP == OP_CGPM) {
-        // CG: p = r + beta p ; CG-M, every active shifted system:
-        //   x^s += alpha^s_n p^s ;  p^s = zeta_{n+1} r + beta^s_{n+1} p^s
+    } else if constexpr (OP == OP_CGP) {
+        // CG: p = r + beta p
         if (ok) {
             const T beta = (T)S->cgb;
             cx<T> r[12], p[12];
@@ -449,28 +348,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
 #pragma unroll
             for (int k = 0; k < 12; k++) p[k] = r[k] + beta * p[k];
             store_spinor<SFL, T, NTS>(J.f[R_F0], i, p);
-            if constexpr (OP == OP_CGPM) {
-                const int ns = S->nshift;
-                for (int q = 0; q < ns; q++) {
-                    const ShiftScal& Q = S->sh[q];
-                    if (!Q.active) continue;
-                    const SpinorRef xr = S->shv[2 * q], pr = S->shv[2 * q + 1];
-                    const T as = (T)Q.alpha_s.x, bs = (T)Q.beta_s.x, zn = (T)Q.zeta_next.x;
-                    cx<T> xs[12], ps[12];
-                    load_spinor<SFL, T, true>(xr, i, xs);
-                    load_spinor<SFL, T, true>(pr, i, ps);
-#pragma unroll
-                    for (int k = 0; k < 12; k++) {
-                        xs[k] = xs[k] + as * ps[k];
-                        ps[k] = zn * r[k] + bs * ps[k];
-                    }
-                    store_spinor<SFL, T, NTS>(xr, i, xs);
-                    store_spinor<SFL, T, NTS>(pr, i, ps);
-                }
-            }
         }
     } else if constexpr (OP == OP_MSINIT) {
-        // BiCGstab-M start: r = s = rhat = b, x = 0, x^sigma = 0, s^sigma = b; |b|^2
+        // BiCGstab-M / CG-M start: r = s = b, x = 0; |b|^2 (the shifted systems start in their first update)
         if (ok) {
             cx<T> bb[12], zero[12];
             load_spinor<SFL, T, true>(J.f[R_F1], i, bb);
@@ -480,10 +360,6 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             store_spinor<SFL, T, NTS>(J.f[R_F2], i, bb);
             store_spinor<SFL, T, NTS>(J.f[R_F3], i, bb);
             store_spinor<SFL, T, NTS>(J.f[R_F4], i, zero);
-            for (int q = 0; q < S->nshift; q++) {
-                store_spinor<SFL, T, NTS>(S->shv[2 * q], i, zero);
-                store_spinor<SFL, T, NTS>(S->shv[2 * q + 1], i, bb);
-            }
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 double n2 = (double)bb[k].re * bb[k].re + (double)bb[k].im * bb[k].im;
@@ -1071,10 +947,8 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     FIN_CASE(3, FIN_CHI)
     FIN_CASE(3, FIN_ALPHA)
     FIN_CASE(3, FIN_RESTART)
-    FIN_CASE(0, FIN_END)
     FIN_CASE(3, FIN_CGA)
     FIN_CASE(3, FIN_CGB)
-    FIN_CASE(0, FIN_CGEND)
     return hipErrorInvalidValue;
 }
 
@@ -1096,12 +970,10 @@ hipError_t launch_sweep(int op, int sfl, const SweepJob* jobs, int njobs, long n
     SWEEP_ALL(SF64)
     SWEEP_ALL(SF32)
     SWEEP_ALL(SF16)
-    SWEEP_CASE(OP_SHIFT, SF64)
     SWEEP_CASE(OP_NORM, SF64)
     SWEEP_CASE(OP_MSINIT, SF64)
     SWEEP_CASE(OP_AXPY, SF64)
     SWEEP_CASE(OP_LINCOMB, SF64)
-    SWEEP_CASE(OP_CGPM, SF64)
     return hipErrorInvalidValue;
 }
 

@@ -7,8 +7,8 @@
 namespace wd {
 
 enum HopRed { RED_NONE = 0, RED_ZDOT = 1, RED_OUTX = 2, RED_NORM = 3 };
-enum SweepOp { OP_W = 0, OP_XR = 1, OP_S = 2, OP_SHIFT = 3, OP_INIT = 4, OP_ACC = 5, OP_NORM = 6, OP_MSINIT = 7, OP_AXPY = 8,
-               OP_LINCOMB = 9, OP_CGX = 10, OP_CGP = 11, OP_CGPM = 12 };
+enum SweepOp { OP_W = 0, OP_XR = 1, OP_S = 2, OP_INIT = 4, OP_ACC = 5, OP_NORM = 6, OP_MSINIT = 7, OP_AXPY = 8,
+               OP_LINCOMB = 9, OP_CGX = 10, OP_CGP = 11 };
 
 // exec (may be NULL): incremented once per job that was not gated off. stage: LDS staging of the
 // x/y neighbours (1 on, 0 off, -1 the defaults hop_stage_default() / hop_stage64_default()).
@@ -51,6 +51,17 @@ hipError_t launch_convert_links(int lf, int src_lf, const void* src, void* dst, 
 // temporal gauge of canonical links U: gm = g(n) [V][3][3], Uf = transformed links [4][V][3][3]
 hipError_t launch_temporal_gauge(const double* U, const Geo& g, double* gm, double* Uf, hipStream_t s);
 hipError_t launch_recon_check(const void* lk, int Vh, long lcs, double* blockmax, hipStream_t s, int mode = 0);
+// Shifted systems (BiCGstab-M, CG-M): the coefficients of a block update from the scalars the
+// iteration left in *blk (ns shifts, sv: their x and s (p) fields), then the update itself over n
+// complex numbers; v: the block vectors r_0, w_0, r_1, ... (CG-M: r_0, r_1, ...). base: the base
+// system's record.
+struct ShiftVectors {
+    const void* v[SHIFT_NB];
+};
+hipError_t launch_shift_coef(bool cg, ShiftBlock* blk, ShiftScal* sh, const SpinorRef* sv, ShiftCoef* coef, int ns,
+                             const SysState* base, hipStream_t s);
+hipError_t launch_shift_update(int nb, const ShiftVectors& v, long n, const ShiftBlock* blk, const ShiftCoef* coef,
+                               hipStream_t s, int* exec = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // out[2 j], out[2 j + 1] = <a, bs[j]> (j < m <= DOTS_MAX) over the real sites of full FP64 fields;
 // bs: device array of m views; partials: device, >= (2 stride / BLOCK + 1) * 2 * DOTS_MAX doubles
 constexpr int DOTS_MAX = 8;

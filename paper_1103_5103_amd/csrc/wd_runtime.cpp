@@ -206,7 +206,7 @@ void JobTable<J>::upload(hipStream_t s)
     WD_CHECK_HIP(hipMemcpyAsync((char*)dev->p + off, stage, n, hipMemcpyHostToDevice, s));
 }
 
-void upload_tables(hipStream_t s, std::shared_ptr<DevMem>& mem, std::initializer_list<JobTableBase*> tables)
+void upload_tables(hipStream_t s, std::shared_ptr<DevMem>& mem, const std::vector<JobTableBase*>& tables)
 {
     size_t total = 0;
     std::vector<size_t> offs;
@@ -284,8 +284,29 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     if (red != RED_NONE) run_finish(3, fin, t, sys, gated, s);
 }
 
+// the fields that an operation's kernel reads or writes whatever its flags (bit r: role r)
+static unsigned sweep_roles(int op)
+{
+    switch (op) {
+    case OP_W: return 0b111;
+    case OP_XR: return 0b1111101;
+    case OP_S: return 0b1101;
+    case OP_INIT: return 0b111;
+    case OP_ACC: return 0b11;
+    case OP_MSINIT: return 0b11111;
+    case OP_AXPY: return 0b111;
+    case OP_CGX: return 0b11111;
+    case OP_CGP: return 0b11;
+    default: return 0b1;
+    }
+}
+
 void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s, double bytes)
 {
+    const unsigned need = sweep_roles(op);
+    for (const SweepJob& j : t.host)
+        for (int r = 0; r < NROLE; r++)
+            if (((need >> r) & 1) && !j.f[r].p) throw Error{WD_ERR_ARG, "sweep job without a field that its operation uses"};
     Timer& T = timer();
     hipEvent_t a = nullptr, b = nullptr;
     int* flag = nullptr;
@@ -299,14 +320,27 @@ void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int 
     if (timed) T.pending.push_back({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
     switch (op) {
     case OP_XR: run_finish(3, FIN_ALPHA, t, sys, gated, s); break;
-    case OP_SHIFT: run_finish(0, FIN_END, t, sys, gated, s); break;  // OP_S: committed in FIN_ALPHA
     case OP_INIT:
     case OP_MSINIT: run_finish(3, FIN_RESTART, t, sys, gated, s); break;
     case OP_NORM: run_finish(3, FIN_STORE, t, sys, gated, s); break;
     case OP_CGX: run_finish(3, FIN_CGB, t, sys, gated, s); break;
-    case OP_CGPM: run_finish(0, FIN_CGEND, t, sys, gated, s); break;  // OP_CGP: committed in FIN_CGB
     default: break;
     }
+}
+
+void run_shift_update(int nb, const ShiftVectors& v, long n, const ShiftBlock* blk, const ShiftCoef* coef,
+                      hipStream_t s, double bytes)
+{
+    Timer& T = timer();
+    hipEvent_t a = nullptr, b = nullptr;
+    int* flag = nullptr;
+    if (T.on) {
+        flag = T.slot();
+        a = T.get();
+        b = T.get();
+    }
+    WD_CHECK_HIP(launch_shift_update(nb, v, n, blk, coef, s, flag, a, b));
+    if (T.on) T.pending.push_back({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), 1, -1});
 }
 
 } // namespace wd

@@ -899,6 +899,119 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     }
 }
 
+// ================================================================ shifted systems in blocks
+
+// Host side of the blocked update of the shifted systems (wd_shift.hip): m iterations leave their
+// residuals (BiCGstab-M: and w) in buffers of their own, one update follows. The last residual of a
+// block is the first of the next one, so the buffers are taken in one of two orders in turn, `par`:
+// r_0 .. r_m in buffers 0, 1, .., m or in m, 1, .., m - 1, 0.
+struct ShiftedSystems {
+    int ns = 0, m = 1;
+    bool cg = false;
+    long n = 0;  // complex numbers per field
+    double sites = 0;
+    std::vector<ShiftScal> sh;
+    std::vector<Field> R, W;
+    ShiftScal* d_sh = nullptr;
+    SpinorRef* d_sv = nullptr;
+    ShiftCoef* d_coef = nullptr;
+    ShiftBlock* d_blk = nullptr;
+    int slot(int par, int j) const { return par == 0 ? j : j == 0 ? m : j == m ? 0 : j; }
+    const Field& r(int par, int j) const { return R[slot(par, j)]; }
+    const Field& w(int j) const { return W[j]; }
+
+    // The buffers of m = SHIFT_BLOCK iterations per update, or of fewer where the memory does not
+    // allow that (m = 1: as many fields as an update in every iteration needs).
+    void alloc(wd_gauge* g, const std::string& key, int ns_, bool cg_, int halves, const std::vector<SpinorRef>& sv,
+               hipStream_t st)
+    {
+        ns = ns_;
+        cg = cg_;
+        m = ns > 0 ? SHIFT_BLOCK : 1;
+        for (;;) {
+            R.clear();
+            W.clear();
+            try {
+                // without shifts the one residual is updated in place
+                for (int j = 0; j <= (ns > 0 ? m : 0); j++) R.push_back(g->field(key + "R" + std::to_string(j), SF64, halves));
+                for (int j = 0; j < (cg ? 0 : m); j++) W.push_back(g->field(key + "W" + std::to_string(j), SF64, halves));
+                break;
+            } catch (const Error& e) {
+                if (e.code != WD_ERR_OOM || m == 1) throw;
+                R.clear();
+                W.clear();
+                m /= 2;
+                for (int j = m + 1; j <= SHIFT_BLOCK; j++) g->ws.erase(key + "R" + std::to_string(j));
+                for (int j = m; j < SHIFT_BLOCK; j++) g->ws.erase(key + "W" + std::to_string(j));
+            }
+        }
+        n = R[0].nsites() * 12;
+        sites = (double)R[0].nsites();
+        if (ns == 0) return;
+        d_sh = (ShiftScal*)g->rawbuf(key + "sh", sizeof(ShiftScal) * ns);
+        d_sv = (SpinorRef*)g->rawbuf(key + "shv", sizeof(SpinorRef) * 2 * ns);
+        d_coef = (ShiftCoef*)g->rawbuf(key + "coef", sizeof(ShiftCoef) * ns);
+        d_blk = (ShiftBlock*)g->rawbuf(key + "blk", sizeof(ShiftBlock));
+        copy_in(d_sh, sh.data(), sizeof(ShiftScal) * ns, st);
+        copy_in(d_sv, sv.data(), sizeof(SpinorRef) * 2 * ns, st);
+    }
+    static void copy_in(void* d, const void* h, size_t bytes, hipStream_t st)
+    {
+        char* stg = stage_alloc(bytes);
+        std::memcpy(stg, h, bytes);
+        WD_CHECK_HIP(hipMemcpyAsync(d, stg, bytes, hipMemcpyHostToDevice, st));
+    }
+    // before the first iteration; alpha, beta: the base scalars of the iteration before it
+    void start(double target2, double alpha, double beta, hipStream_t st)
+    {
+        if (ns == 0) return;
+        ShiftBlock b;
+        std::memset(&b, 0, sizeof(b));
+        b.alpha_prev = make_double2(alpha, 0.0);
+        b.beta_prev = make_double2(beta, 0.0);
+        b.target2 = target2;
+        copy_in(d_blk, &b, sizeof(b), st);
+    }
+    void update(int par, const SysState* base, int active, hipStream_t st) const
+    {
+        if (ns == 0) return;
+        ShiftVectors v;
+        std::memset(&v, 0, sizeof(v));
+        const int nb = cg ? m + 1 : 2 * m + 1;
+        for (int j = 0; j <= m; j++) {
+            v.v[cg ? j : 2 * j] = r(par, j).base();
+            if (!cg && j < m) v.v[2 * j + 1] = w(j).base();
+        }
+        WD_CHECK_HIP(launch_shift_coef(cg, d_blk, d_sh, d_sv, d_coef, ns, base, st));
+        run_shift_update(nb, v, n, d_blk, d_coef, st, sites * 192.0 * (4.0 * active + nb));
+    }
+    // what the update's kernel arguments hold, for the key of a captured chunk
+    std::string id() const
+    {
+        std::string k = "|m" + std::to_string(m);
+        for (const void* p : {(const void*)d_sh, (const void*)d_sv, (const void*)d_coef, (const void*)d_blk})
+            k += ":" + std::to_string((uintptr_t)p);
+        for (auto* f : {&R, &W})
+            for (const Field& e : *f) k += ":" + std::to_string((uintptr_t)e.base());
+        return k;
+    }
+    void fetch(hipStream_t st)
+    {
+        if (ns == 0) return;
+        const size_t n1 = sizeof(ShiftScal) * ns;
+        void* stg = pinned(n1);
+        WD_CHECK_HIP(hipMemcpyAsync(stg, d_sh, n1, hipMemcpyDeviceToHost, st));
+        WD_CHECK_HIP(hipStreamSynchronize(st));
+        std::memcpy(sh.data(), stg, n1);
+    }
+    int active() const
+    {
+        int a = 0;
+        for (const ShiftScal& z : sh) a += z.active;
+        return a;
+    }
+};
+
 // ================================================================ BiCGstab-M (FP64, full lattice)
 
 static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* const* x, const double* b,
@@ -918,15 +1031,28 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
             mass_of_shift.push_back(i);
         }
 
-    Field B = g->field("ms.B", SF64, 2), X = g->field("ms.X", SF64, 2), R0 = g->field("ms.R0", SF64, 2);
-    Field R1 = ns > 0 ? g->field("ms.R1", SF64, 2) : R0;
-    Field Sv = g->field("ms.S", SF64, 2), AS = g->field("ms.AS", SF64, 2), W = g->field("ms.W", SF64, 2);
+    Field B = g->field("ms.B", SF64, 2), X = g->field("ms.X", SF64, 2);
+    Field Sv = g->field("ms.S", SF64, 2), AS = g->field("ms.AS", SF64, 2);
     Field AW = g->field("ms.AW", SF64, 2), RES = g->field("ms.RES", SF64, 2);
     std::vector<Field> XS(ns), SS(ns);
     for (int k = 0; k < ns; k++) {
         XS[k] = g->field("ms.XS" + std::to_string(k), SF64, 2);
         SS[k] = g->field("ms.SS" + std::to_string(k), SF64, 2);
     }
+    ShiftedSystems shf;
+    std::vector<SpinorRef> shv;
+    for (int k = 0; k < ns; k++) {
+        ShiftScal z;
+        std::memset(&z, 0, sizeof(z));
+        z.sigma = 1.0 / (2.0 * kappas[mass_of_shift[k]]) - a;
+        z.zeta_prev = z.zeta = z.rho = make_double2(1.0, 0.0);
+        z.active = 1;
+        shf.sh.push_back(z);
+        shv.push_back(XS[k].all());
+        shv.push_back(SS[k].all());
+    }
+    shf.alloc(g, "ms.", ns, false, 2, shv, st);
+    const int m = shf.m;
     const Geo& geo = g->geo;
     const int L64 = g->f64_links();
 
@@ -937,134 +1063,125 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     q.partials = (double*)g->rawbuf("ms.partials", sizeof(double) * NRED * (2 * geo.stride / BLOCK + 1));
     q.maxit = P.max_iter;
     q.mixed = 0;
-    q.nshift = ns;
     q.target2 = -1;
-    q.beta_prev = make_double2(1.0, 0.0);
+    q.blk = shf.d_blk;
     q.alpha = make_double2(0.0, 0.0);
-    std::vector<ShiftScal> sh(std::max(ns, 1));
-    std::vector<SpinorRef> shv(2 * std::max(ns, 1));
-    for (int k = 0; k < ns; k++) {
-        ShiftScal& z = sh[k];
-        std::memset(&z, 0, sizeof(z));
-        z.sigma = 1.0 / (2.0 * kappas[mass_of_shift[k]]) - a;
-        z.zeta_prev = z.zeta = z.rho = make_double2(1.0, 0.0);
-        z.active = 1;
-        shv[2 * k] = XS[k].all();
-        shv[2 * k + 1] = SS[k].all();
-    }
-    ShiftScal* d_sh = (ShiftScal*)g->rawbuf("ms.sh", sizeof(ShiftScal) * sh.size());
-    SpinorRef* d_shv = (SpinorRef*)g->rawbuf("ms.shv", sizeof(SpinorRef) * shv.size());
-    {
-        size_t n1 = sizeof(ShiftScal) * sh.size(), n2 = sizeof(SpinorRef) * shv.size();
-        char* stg = (char*)pinned(n1 + n2);
-        std::memcpy(stg, sh.data(), n1);
-        std::memcpy(stg + n1, shv.data(), n2);
-        WD_CHECK_HIP(hipMemcpyAsync(d_sh, stg, n1, hipMemcpyHostToDevice, st));
-        WD_CHECK_HIP(hipMemcpyAsync(d_shv, stg + n1, n2, hipMemcpyHostToDevice, st));
-        WD_CHECK_HIP(hipStreamSynchronize(st));
-    }
-    q.sh = d_sh;
-    q.shv = d_shv;
     sys.upload(st);
 
     WD_CHECK_HIP(launch_pack_spinor(SF64, b, geo, B.half(0), B.half(1), P.dagger, 1.0, st, g->gm(), g->nc));
     const long nsites = B.nsites();
-    JobTable<SweepJob> Init, SW, SXR, SEND;
+    JobTable<SweepJob> Init;
     SweepJob j = sweep_job(0, nsites);
-    j.f[R_F0] = R0.all();
+    j.f[R_F0] = shf.r(0, 0).all();
     j.f[R_F1] = B.all();
     j.f[R_F2] = Sv.all();
     j.f[R_F3] = Sv.all();
     j.f[R_F4] = X.all();
     Init.host.push_back(j);
-    j = sweep_job(0, nsites);
-    j.f[R_F0] = W.all();
-    j.f[R_F1] = R0.all();
-    j.f[R_F2] = AS.all();
-    j.f[R_F3] = R1.all();
-    SW.host.push_back(j);
-    j = sweep_job(0, nsites);
-    j.f[R_F0] = X.all();
-    j.f[R_F1] = R0.all();
-    j.f[R_F2] = Sv.all();
-    j.f[R_F3] = W.all();
-    j.f[R_F4] = AW.all();
-    j.f[R_F5] = B.all();
-    j.f[R_F6] = R1.all();
-    SXR.host.push_back(j);
-    j = sweep_job(0, nsites);
-    j.f[R_F0] = Sv.all();
-    j.f[R_F1] = R0.all();
-    j.f[R_F2] = AS.all();
-    j.f[R_F3] = R1.all();
-    j.f[R_F4] = W.all();
-    SEND.host.push_back(j);
-    JobTable<HopJob> HAs, HAw;
-    for (int p = 0; p < 2; p++) {
-        HopJob h = hop_job(geo, p, 0, Sv.half(1 - p), AS.half(p), g->slk(L64, p), g->lcs(), -0.5);
-        h.tg = g->tg;
-        h.nc = g->nc;
-        h.x0 = Sv.half(p);
-        h.c0 = a;
-        h.z = B.half(p);
-        HAs.host.push_back(h);
-        h = hop_job(geo, p, 0, W.half(1 - p), AW.half(p), g->slk(L64, p), g->lcs(), -0.5);
-        h.tg = g->tg;
-        h.nc = g->nc;
-        h.x0 = W.half(p);
-        h.c0 = a;
-        HAw.host.push_back(h);
-    }
+    JobTable<HopJob> HAs;
     const int tz64 = tune_tile(g, SF64, L64, st);
-    for (auto* t : {&HAs, &HAw})
-        for (auto& h : t->host) set_tile(h, tz64);
-    for (auto* t : {&Init, &SW, &SXR, &SEND}) layout(*t);
-    for (auto* t : {&HAs, &HAw}) layout(*t);
-    upload_tables(st, g->raw["ms.tables"], {&Init, &SW, &SXR, &SEND, &HAs, &HAw});
-    run_sweep(OP_MSINIT, SF64, Init, sys.d(), 0, st, sweep_bytes(Init, (4 + 2 * ns) * 192.0));
+    auto hop = [&](const Field& in, const Field& out, int p, const SpinorRef* z) {
+        HopJob h = hop_job(geo, p, 0, in.half(1 - p), out.half(p), g->slk(L64, p), g->lcs(), -0.5);
+        h.tg = g->tg;
+        h.nc = g->nc;
+        h.x0 = in.half(p);
+        h.c0 = a;
+        if (z) h.z = *z;
+        set_tile(h, tz64);
+        return h;
+    };
+    for (int p = 0; p < 2; p++) {
+        const SpinorRef z = B.half(p);
+        HAs.host.push_back(hop(Sv, AS, p, &z));
+    }
+    // the sweeps and the second hop of iteration i of a block, for the two orders of the buffers
+    // (without shifts: one buffer, updated in place)
+    struct Step {
+        JobTable<SweepJob> SW, SXR, SEND;
+        JobTable<HopJob> HAw;
+    };
+    std::vector<Step> steps[2];
+    std::vector<JobTableBase*> tabs{&Init, &HAs};
+    const int nord = ns > 0 ? 2 : 1;
+    for (int par = 0; par < nord; par++) {
+        steps[par].resize(m);
+        for (int i = 0; i < m; i++) {
+            Step& S = steps[par][i];
+            const Field &R0 = shf.r(ns > 0 ? par : 0, ns > 0 ? i : 0), &R1 = shf.r(ns > 0 ? par : 0, ns > 0 ? i + 1 : 0);
+            const Field& W = shf.w(i);
+            j = sweep_job(0, nsites);
+            j.f[R_F0] = W.all();
+            j.f[R_F1] = R0.all();
+            j.f[R_F2] = AS.all();
+            S.SW.host.push_back(j);
+            j = sweep_job(0, nsites);
+            j.f[R_F0] = X.all();
+            j.f[R_F2] = Sv.all();
+            j.f[R_F3] = W.all();
+            j.f[R_F4] = AW.all();
+            j.f[R_F5] = B.all();
+            j.f[R_F6] = R1.all();
+            S.SXR.host.push_back(j);
+            j = sweep_job(0, nsites);
+            j.f[R_F0] = Sv.all();
+            j.f[R_F2] = AS.all();
+            j.f[R_F3] = R1.all();
+            S.SEND.host.push_back(j);
+            for (int p = 0; p < 2; p++) S.HAw.host.push_back(hop(W, AW, p, nullptr));
+            for (auto* t : {&S.SW, &S.SXR, &S.SEND}) layout(*t);
+            layout(S.HAw);
+            for (JobTableBase* t : {(JobTableBase*)&S.SW, (JobTableBase*)&S.SXR, (JobTableBase*)&S.SEND, (JobTableBase*)&S.HAw})
+                tabs.push_back(t);
+        }
+    }
+    layout(Init);
+    layout(HAs);
+    upload_tables(st, g->raw["ms.tables"], tabs);
+    run_sweep(OP_MSINIT, SF64, Init, sys.d(), 0, st, sweep_bytes(Init, 4 * 192.0));
     sys.download(st);
     const double bb = sys.h[0].red[2];
     sys.h[0].target2 = P.tol * P.tol * bb;
-    sys.h[0].shift_target2 = P.tol * P.tol * bb;
-    sys.h[0].beta_prev = make_double2(1.0, 0.0);
     sys.h[0].alpha = make_double2(0.0, 0.0);
     if (bb == 0.0) sys.h[0].status = ST_CONVERGED;
     sys.upload(st);
+    shf.start(P.tol * P.tol * bb, 0.0, 1.0, st);
 
-    const int endop = ns > 0 ? OP_SHIFT : OP_S;
-    const double bH = hop_bytes(HAs, SF64, L64, 2), bHw = hop_bytes(HAw, SF64, L64, 1);
-    auto iterate = [&](int active_shifts, hipStream_t q) {
+    const double bH = hop_bytes(HAs, SF64, L64, 2), bHw = hop_bytes(steps[0][0].HAw, SF64, L64, 1);
+    auto iterate = [&](const Step& S, hipStream_t q) {
         run_hop(SF64, L64, false, RED_ZDOT, FIN_BETA, HAs, sys.d(), GATE_RUN, q, bH);
-        run_sweep(OP_W, SF64, SW, sys.d(), GATE_RUN, q, sweep_bytes(SW, 3 * 192));
-        run_hop(SF64, L64, false, RED_OUTX, FIN_CHI, HAw, sys.d(), GATE_RUN, q, bHw);
-        run_sweep(OP_XR, SF64, SXR, sys.d(), GATE_RUN, q, sweep_bytes(SXR, 7 * 192));
-        run_sweep(endop, SF64, SEND, sys.d(), GATE_RUN, q, sweep_bytes(SEND, (ns > 0 ? 6 : 4) * 192 + 4 * 192 * active_shifts));
+        run_sweep(OP_W, SF64, S.SW, sys.d(), GATE_RUN, q, sweep_bytes(S.SW, 3 * 192));
+        run_hop(SF64, L64, false, RED_OUTX, FIN_CHI, S.HAw, sys.d(), GATE_RUN, q, bHw);
+        run_sweep(OP_XR, SF64, S.SXR, sys.d(), GATE_RUN, q, sweep_bytes(S.SXR, 7 * 192));
+        run_sweep(OP_S, SF64, S.SEND, sys.d(), GATE_RUN, q, sweep_bytes(S.SEND, 4 * 192));
     };
-    std::shared_ptr<ChunkGraph> graph;
-    if (graphs_on())
-        graph = cached_graph(g, launch_key("ms", poll, ns, endop, sys.d(), HAs, SW, HAw, SXR, SEND), [&](hipStream_t q) {
-            for (int k = 0; k < poll; k++) iterate(ns, q);
-        });
+    // between two looks at the status: whole blocks, about `poll` iterations
+    const int blocks = std::max(1, poll / m);
+    auto chunk = [&](int par, int active, hipStream_t q) {
+        for (int k = 0; k < blocks; k++, par ^= nord - 1) {
+            for (const Step& S : steps[par]) iterate(S, q);
+            shf.update(par, sys.d(), active, q);
+        }
+    };
     int status = WD_OK;
-    int active_shifts = ns;
+    int active_shifts = ns, par = 0;
     long host_iters = 0;
-    const long host_cap = (long)P.max_iter + 16L * poll + 64;
+    const long host_cap = (long)P.max_iter + 16L * std::max(poll, m) + 64;
+    if (ns > 0 && sys.h[0].status != ST_RUNNING) shf.update(0, sys.d(), ns, st);  // no iteration: x = 0
     while (true) {
         if (sys.h[0].status != ST_RUNNING) break;
         if (host_iters > host_cap) break;  // no exit state reported by the device
-        if (graph) graph->launch(st);
+        if (graphs_on())
+            cached_graph(g, launch_key("ms", blocks * m, ns, par, sys.d(), HAs, steps[par][0].SW, steps[par][0].HAw) + shf.id(),
+                         [&](hipStream_t q) { chunk(par, ns, q); })
+                ->launch(st);
         else
-            for (int k = 0; k < poll; k++) iterate(active_shifts, st);
-        host_iters += poll;
+            chunk(par, active_shifts, st);
+        if (blocks & 1) par ^= nord - 1;
+        host_iters += blocks * m;
         sys.download(st);
-        if (ns > 0) {
-            size_t n1 = sizeof(ShiftScal) * ns;
-            void* stg = pinned(n1);
-            WD_CHECK_HIP(hipMemcpyAsync(stg, d_sh, n1, hipMemcpyDeviceToHost, st));
-            WD_CHECK_HIP(hipStreamSynchronize(st));
-            std::memcpy(sh.data(), stg, n1);
-            active_shifts = 0;
-            for (int k = 0; k < ns; k++) active_shifts += sh[k].active;
+        if (timer().on) {  // the bytes credited to the updates
+            shf.fetch(st);
+            active_shifts = shf.active();
         }
     }
     switch (sys.h[0].status) {
@@ -1074,13 +1191,8 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     case ST_NAN: status = WD_ERR_NAN; break;
     default: status = WD_ERR_NOCONV;
     }
-    if (ns > 0) {
-        size_t n1 = sizeof(ShiftScal) * ns;
-        void* stg = pinned(n1);
-        WD_CHECK_HIP(hipMemcpyAsync(stg, d_sh, n1, hipMemcpyDeviceToHost, st));
-        WD_CHECK_HIP(hipStreamSynchronize(st));
-        std::memcpy(sh.data(), stg, n1);
-    }
+    shf.fetch(st);
+    const std::vector<ShiftScal>& sh = shf.sh;
     const int iters = sys.h[0].iter;
     const double t1 = now_s();
 
@@ -1668,7 +1780,6 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         q.delta_rel2 = P.delta_reliable * P.delta_reliable;
         q.dc = P.mixed && P.mixed_mode == WD_MIXED_DEFECT;
         q.target2 = -1.0;
-        q.cga_prev = 1.0;
         q.status = ST_RUNNING;
     }
     sys.upload(st);
@@ -1753,6 +1864,7 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         sj.f[R_F1] = e.p.all();
         sj.f[R_F2] = e.r.all();
         sj.f[R_F3] = e.w.all();
+        sj.f[R_F4] = e.r.all();
         SX.host.push_back(sj);
         sj = sweep_job(i, e.r.nsites());
         sj.f[R_F0] = e.p.all();
@@ -1971,8 +2083,22 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
     std::vector<Field> X(n), PS(ns);
     for (int i = 0; i < n; i++) X[i] = g->field("cgm.X" + std::to_string(i), SF64, 2);
     for (int k = 0; k < ns; k++) PS[k] = g->field("cgm.P" + std::to_string(k), SF64, 1);
-    Field R = g->field("cgm.r", SF64, 1), Pb = g->field("cgm.p", SF64, 1), Tm = g->field("cgm.t", SF64, 1);
+    Field Pb = g->field("cgm.p", SF64, 1), Tm = g->field("cgm.t", SF64, 1);
     Field Vm = g->field("cgm.v", SF64, 1), Wm = g->field("cgm.w", SF64, 1);
+    ShiftedSystems shf;
+    std::vector<SpinorRef> shv;
+    for (int k = 0; k < ns; k++) {
+        ShiftScal z;
+        std::memset(&z, 0, sizeof(z));
+        z.sigma = sigmas[sys_of_shift[k]] - s0;
+        z.zeta_prev = z.zeta = make_double2(1.0, 0.0);
+        z.active = 1;
+        shf.sh.push_back(z);
+        shv.push_back(X[sys_of_shift[k]].half(0));
+        shv.push_back(PS[k].all());
+    }
+    shf.alloc(g, "cgm.", ns, true, 1, shv, st);
+    const int m = shf.m;
     for (int i = 0; i < n; i++) WD_CHECK_HIP(hipMemsetAsync(X[i].base(), 0, X[i].mem->bytes, st));
     WD_CHECK_HIP(launch_pack_spinor(SF64, b, geo, B.half(0), B.half(1), 0, 1.0, st, g->gm(), g->nc));
 
@@ -1982,54 +2108,44 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
     std::memset(&q, 0, sizeof(q));
     q.partials = (double*)g->rawbuf("cgm.partials", sizeof(double) * NRED * (2 * geo.stride / BLOCK + 1));
     q.maxit = P.max_iter;
-    q.nshift = ns;
     q.target2 = -1;
-    q.cga_prev = 1.0;
-    std::vector<ShiftScal> sh(std::max(ns, 1));
-    std::vector<SpinorRef> shv(2 * std::max(ns, 1));
-    for (int k = 0; k < ns; k++) {
-        ShiftScal& z = sh[k];
-        std::memset(&z, 0, sizeof(z));
-        z.sigma = sigmas[sys_of_shift[k]] - s0;
-        z.zeta_prev = z.zeta = make_double2(1.0, 0.0);
-        z.active = 1;
-        shv[2 * k] = X[sys_of_shift[k]].half(0);
-        shv[2 * k + 1] = PS[k].all();
-    }
-    ShiftScal* d_sh = (ShiftScal*)g->rawbuf("cgm.sh", sizeof(ShiftScal) * sh.size());
-    SpinorRef* d_shv = (SpinorRef*)g->rawbuf("cgm.shv", sizeof(SpinorRef) * shv.size());
-    {
-        const size_t n1 = sizeof(ShiftScal) * sh.size(), n2 = sizeof(SpinorRef) * shv.size();
-        char* stg = stage_alloc(n1 + n2);
-        std::memcpy(stg, sh.data(), n1);
-        std::memcpy(stg + n1, shv.data(), n2);
-        WD_CHECK_HIP(hipMemcpyAsync(d_sh, stg, n1, hipMemcpyHostToDevice, st));
-        WD_CHECK_HIP(hipMemcpyAsync(d_shv, stg + n1, n2, hipMemcpyHostToDevice, st));
-    }
-    q.sh = d_sh;
-    q.shv = d_shv;
+    q.blk = shf.d_blk;
     sys.upload(st);
 
-    const long nh = R.nsites();
-    JobTable<SweepJob> Init, SX, SP;
+    const long nh = Pb.nsites();
+    JobTable<SweepJob> Init;
     SweepJob j = sweep_job(0, nh);
-    // r = p = b_e, x = 0, x^s = 0, p^s = b_e, |b_e|^2
-    j.f[R_F0] = R.all();
+    // r = p = b_e, x = 0, |b_e|^2
+    j.f[R_F0] = shf.r(0, 0).all();
     j.f[R_F1] = B.half(0);
     j.f[R_F2] = Pb.all();
     j.f[R_F3] = Pb.all();
     j.f[R_F4] = X[base].half(0);
     Init.host.push_back(j);
-    j = sweep_job(0, nh);
-    j.f[R_F0] = X[base].half(0);
-    j.f[R_F1] = Pb.all();
-    j.f[R_F2] = R.all();
-    j.f[R_F3] = Wm.all();
-    SX.host.push_back(j);
-    j = sweep_job(0, nh);
-    j.f[R_F0] = Pb.all();
-    j.f[R_F1] = R.all();
-    SP.host.push_back(j);
+    // the sweeps of iteration i of a block, for the two orders of the residual buffers (without
+    // shifts: one buffer, updated in place)
+    struct Step {
+        JobTable<SweepJob> SX, SP;
+    };
+    std::vector<Step> steps[2];
+    const int nord = ns > 0 ? 2 : 1;
+    for (int par = 0; par < nord; par++) {
+        steps[par].resize(m);
+        for (int i = 0; i < m; i++) {
+            const Field &R0 = shf.r(ns > 0 ? par : 0, ns > 0 ? i : 0), &R1 = shf.r(ns > 0 ? par : 0, ns > 0 ? i + 1 : 0);
+            j = sweep_job(0, nh);
+            j.f[R_F0] = X[base].half(0);
+            j.f[R_F1] = Pb.all();
+            j.f[R_F2] = R0.all();
+            j.f[R_F3] = Wm.all();
+            j.f[R_F4] = R1.all();
+            steps[par][i].SX.host.push_back(j);
+            j = sweep_job(0, nh);
+            j.f[R_F0] = Pb.all();
+            j.f[R_F1] = R1.all();
+            steps[par][i].SP.host.push_back(j);
+        }
+    }
     JobTable<HopJob> H1, H2, H3, H4;
     {
         const void* d0 = g->slk(L64, 0);
@@ -2062,53 +2178,59 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
         }
         layout(*t);
     }
-    for (auto* t : {&Init, &SX, &SP}) layout(*t);
-    upload_tables(st, g->raw["cgm.tables"], {&Init, &SX, &SP, &H1, &H2, &H3, &H4});
-    run_sweep(OP_MSINIT, SF64, Init, sys.d(), 0, st, sweep_bytes(Init, (4 + 2 * ns) * 192.0));
+    std::vector<JobTableBase*> tabs{&Init, &H1, &H2, &H3, &H4};
+    layout(Init);
+    for (int par = 0; par < nord; par++)
+        for (Step& S : steps[par])
+            for (auto* t : {&S.SX, &S.SP}) {
+                layout(*t);
+                tabs.push_back(t);
+            }
+    upload_tables(st, g->raw["cgm.tables"], tabs);
+    run_sweep(OP_MSINIT, SF64, Init, sys.d(), 0, st, sweep_bytes(Init, 4 * 192.0));
     sys.download(st);
     const double bb = sys.h[0].red[2];
     sys.h[0].target2 = P.tol * P.tol * bb;
-    sys.h[0].shift_target2 = P.tol * P.tol * bb;
-    sys.h[0].cga_prev = 1.0;
     sys.h[0].cgb = 0.0;
     if (bb == 0.0) sys.h[0].status = ST_CONVERGED;
     sys.upload(st);
+    shf.start(P.tol * P.tol * bb, 1.0, 0.0, st);
 
     const double bH = hop_bytes(H1, SF64, L64, 0);
-    auto iterate = [&](int active_shifts, hipStream_t qs) {
+    auto iterate = [&](const Step& S, hipStream_t qs) {
         run_hop(SF64, L64, false, RED_NONE, FIN_STORE, H1, sys.d(), GATE_RUN, qs, bH);
         run_hop(SF64, L64, false, RED_NONE, FIN_STORE, H2, sys.d(), GATE_RUN, qs, bH + nh * 192.0);
         run_hop(SF64, L64, true, RED_NONE, FIN_STORE, H3, sys.d(), GATE_RUN, qs, bH);
         run_hop(SF64, L64, true, RED_ZDOT, FIN_CGA, H4, sys.d(), GATE_RUN, qs, bH + nh * 2 * 192.0);
-        run_sweep(OP_CGX, SF64, SX, sys.d(), GATE_RUN, qs, sweep_bytes(SX, 6 * 192));
-        run_sweep(ns > 0 ? OP_CGPM : OP_CGP, SF64, SP, sys.d(), GATE_RUN, qs,
-                  sweep_bytes(SP, 3 * 192 + 4 * 192 * active_shifts));
+        run_sweep(OP_CGX, SF64, S.SX, sys.d(), GATE_RUN, qs, sweep_bytes(S.SX, 6 * 192));
+        run_sweep(OP_CGP, SF64, S.SP, sys.d(), GATE_RUN, qs, sweep_bytes(S.SP, 3 * 192));
     };
-    std::shared_ptr<ChunkGraph> graph;
-    if (graphs_on())
-        graph = cached_graph(g, launch_key("cgm", poll, ns, 0, sys.d(), H1, H2, H3, H4, SX, SP), [&](hipStream_t qs) {
-            for (int k = 0; k < poll; k++) iterate(ns, qs);
-        });
-    auto fetch_shifts = [&]() {
-        if (ns == 0) return;
-        const size_t n1 = sizeof(ShiftScal) * ns;
-        void* stg = pinned(n1);
-        WD_CHECK_HIP(hipMemcpyAsync(stg, d_sh, n1, hipMemcpyDeviceToHost, st));
-        WD_CHECK_HIP(hipStreamSynchronize(st));
-        std::memcpy(sh.data(), stg, n1);
+    // between two looks at the status: whole blocks, about `poll` iterations
+    const int blocks = std::max(1, poll / m);
+    auto chunk = [&](int par, int active, hipStream_t qs) {
+        for (int k = 0; k < blocks; k++, par ^= nord - 1) {
+            for (const Step& S : steps[par]) iterate(S, qs);
+            shf.update(par, sys.d(), active, qs);
+        }
     };
-    int active_shifts = ns;
+    int active_shifts = ns, par = 0;
     long host_iters = 0;
-    const long host_cap = (long)P.max_iter + 16L * poll + 64;
+    const long host_cap = (long)P.max_iter + 16L * std::max(poll, m) + 64;
+    if (ns > 0 && sys.h[0].status != ST_RUNNING) shf.update(0, sys.d(), ns, st);  // no iteration: x = 0
     while (sys.h[0].status == ST_RUNNING && host_iters <= host_cap) {
-        if (graph) graph->launch(st);
+        if (graphs_on())
+            cached_graph(g, launch_key("cgm", blocks * m, ns, par, sys.d(), H1, H2, H3, H4, steps[par][0].SX) + shf.id(),
+                         [&](hipStream_t qs) { chunk(par, ns, qs); })
+                ->launch(st);
         else
-            for (int k = 0; k < poll; k++) iterate(active_shifts, st);
-        host_iters += poll;
+            chunk(par, active_shifts, st);
+        if (blocks & 1) par ^= nord - 1;
+        host_iters += blocks * m;
         sys.download(st);
-        fetch_shifts();
-        active_shifts = 0;
-        for (int k = 0; k < ns; k++) active_shifts += sh[k].active;
+        if (timer().on) {  // the bytes credited to the updates
+            shf.fetch(st);
+            active_shifts = shf.active();
+        }
     }
     int status;
     switch (sys.h[0].status) {
@@ -2118,7 +2240,8 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
     case ST_NAN: status = WD_ERR_NAN; break;
     default: status = WD_ERR_NOCONV;
     }
-    fetch_shifts();
+    shf.fetch(st);
+    const std::vector<ShiftScal>& sh = shf.sh;
     const int iters = sys.h[0].iter;
     const double t1 = now_s();
 

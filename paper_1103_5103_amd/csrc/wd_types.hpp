@@ -36,48 +36,76 @@ constexpr int GATE_STOPPED = (1 << ST_CONVERGED) | (1 << ST_RELIABLE) | (1 << ST
 // Finisher kinds (what the last block does with the reduced sums)
 enum Fin {
     FIN_STORE = 0,   // keep the sums in red[] for the host
-    FIN_BETA = 1,    // beta = -delta / <rhat, A s>            (+ shifted zeta, beta)
-    FIN_CHI = 2,     // chi = <A w, w> / <A w, A w>          (+ shifted chi, rho)
-    FIN_ALPHA = 3,   // delta' = <rhat, r>, |r|^2, alpha    (+ shifted alpha, freezing)
-    FIN_END = 4,     // end of iteration: commit status     (+ rotate shifted scalars)
+    FIN_BETA = 1,    // beta = -delta / <rhat, A s>
+    FIN_CHI = 2,     // chi = <A w, w> / <A w, A w>
+    FIN_ALPHA = 3,   // delta' = <rhat, r>, |r|^2, alpha, status (+ the iteration's scalars for the shifts)
     FIN_RESTART = 5, // new residual: delta = <rhat, r>, |r|^2, status RUNNING
-    FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>                (+ shifted zeta, alpha)
-    FIN_CGB = 7,     // CG: beta = |r_new|^2 / |r|^2, status     (+ shifted beta, freezing)
-    FIN_CGEND = 8,   // CG-M end of iteration: commit status, rotate the shifted zeta
+    FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>
+    FIN_CGB = 7,     // CG: beta = |r_new|^2 / |r|^2, status     (+ the iteration's scalars for the shifts)
+};
+
+// ---------------------------------------------------------------- shifted systems
+// The shifted systems of BiCGstab-M / CG-M are not touched by the iteration. It leaves its residuals
+// (BiCGstab-M: also w) in separate buffers and its scalars in a list; every SHIFT_BLOCK iterations
+// the shifted x and s (CG-M: p) are brought up to date in one pass (wd_shift.hip). Over a block of
+// m iterations x^s and s^s are linear combinations of themselves and of r_0, w_0, r_1, ..., r_m.
+constexpr int SHIFT_BLOCK = 8;               // iterations per update, at most
+constexpr int SHIFT_NB = 2 * SHIFT_BLOCK + 1;  // vectors of a block: r_0, w_0, r_1, ..., r_m
+
+// the scalars of one iteration (CG-M: alpha_n, beta_{n+1} in the real parts)
+struct IterScal {
+    double2 beta, chi, alpha;
+    double rr;
 };
 
 struct ShiftScal {
     double sigma;
-    double2 zeta_prev, zeta, zeta_next;
-    double2 rho, rho_next;
-    double2 beta_s, chi_s, alpha_s;
-    int active;      // 1: updated this iteration, 0: frozen
-    int freeze;      // freeze after this iteration
+    double2 zeta_prev, zeta;
+    double2 rho;
+    int active;      // 1: updated, 0: frozen
     int conv_iter;   // iteration at which the shift was frozen
+};
+
+// one shifted system's part of a block update:
+//   x <- x + cx[0] s + sum_k cx[1 + k] v_k,  s <- cs[0] s + sum_k cs[1 + k] v_k
+struct ShiftCoef {
+    void* x;
+    void* s;
+    int store_s;  // 0: the shift was frozen in this block, s is not needed any more
     int pad;
+    double2 cx[SHIFT_NB + 1], cs[SHIFT_NB + 1];
+};
+
+// what the iteration hands to the block update, and the update's own state (device memory, one per
+// solve)
+struct ShiftBlock {
+    IterScal it[SHIFT_BLOCK];  // the iterations since the last update
+    int count;                 // how many
+    int updates;               // updates so far (the first one starts from x = 0, s = r_0)
+    int first;                 // this update is the first one
+    int nrun;                  // shifted systems in this update (entries of coef), -1: no update
+    unsigned mask;             // which block vectors the update reads
+    int pad;
+    double2 alpha_prev, beta_prev;  // the base scalars before the block (CG-M: alpha, beta)
+    double target2;  // a shift is frozen once its |r|^2 is below
 };
 
 struct SysState {
     int status;        // SysStatus
-    int pending;       // status committed at the end of the iteration
     int iter;
     int maxit;
     int mixed;
-    int rsel;          // which residual buffer holds r_n (multi-shift keeps r_n and r_{n+1})
-    int nshift;
     int dc;            // defect correction: the reliable-update threshold is relative to the
                        // residual at the start of the inner solve (maxrr is not raised)
-    double2 delta, beta, chi, alpha, beta_prev;
+    double2 delta, beta, chi, alpha;
     double rr;         // |r|^2 of the iterated residual
     double maxrr;      // max |r|^2 since the last reliable update
     double target2;    // stop when rr <= target2
     double delta_rel2; // reliable update when rr < delta_rel2 * maxrr
-    double shift_target2;
-    double cga, cga_prev, cgb;  // CG: alpha_n, alpha_{n-1}, beta_n
+    double cga, cgb;   // CG: alpha_n, beta_n
     double red[NRED];  // last reduced sums
     double* partials;  // [max blocks][NRED]
-    ShiftScal* sh;     // [nshift]
-    SpinorRef* shv;    // [2 * nshift]: x_sigma, s_sigma (BiCGstab-M) or x_sigma, p_sigma (CG-M)
+    ShiftBlock* blk;   // multi-shift solves: where the iteration leaves its scalars (else NULL)
 };
 
 // one entry per system of a launch: which partial sums the finisher adds
