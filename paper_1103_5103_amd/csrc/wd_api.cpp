@@ -215,10 +215,13 @@ static wd_status apply_impl(wd_gauge* g, double kappa, double* out, const double
                 j.c0 = 1.0 / (2.0 * kappa);
                 j.c2 = -0.5;
                 j.links = g->lk(L64_18, p);
+                j.links_nb = g->lk(L64_18, 1 - p);
                 j.lcs = g->lcs();
                 j.nblk = (g->geo.Vh + BLOCK - 1) / BLOCK;
-                j.blk0 = b0;
                 j.rblk0 = b0;
+                j.ilv = 2;
+                j.ilv_pos = p;
+                full_tile(j);
                 b0 += j.nblk;
                 t.host.push_back(j);
             }

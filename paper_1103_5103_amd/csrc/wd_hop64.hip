@@ -18,4 +18,36 @@ hipError_t launch_hop64(bool dag, int lf, int red, const HopJob* jobs, int njobs
     return hipErrorInvalidValue;
 }
 
+// both parities in one launch (k_hop's FULL)
+#define HOP_FULL(LF_, DAG_, RED_)                                                                                  \
+    if (lf == LF_ && dag == DAG_ && red == RED_) {                                                                 \
+        if (tg) hipExtLaunchKernelGGL((k_hop<SF64, LF_, DAG_, RED_, FIN_STORE, true, false, !DAG_, true>),         \
+                                      grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, sys, gated, exec); \
+        else hipExtLaunchKernelGGL((k_hop<SF64, LF_, DAG_, RED_, FIN_STORE, true, false, false, true>),            \
+                                   grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, sys, gated, exec); \
+        return hipGetLastError();                                                                                  \
+    }
+void full_tile(HopJob& j)
+{
+    const int slice = j.g.Xh * j.g.Y * j.g.Z;
+    j.tb = slice % BLOCK == 0 ? 8 : 0;
+    j.bps = slice / BLOCK;
+}
+
+hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
+                           int gated, hipStream_t s, int* exec, int tg, hipEvent_t ev0, hipEvent_t ev1)
+{
+    if (tg && dag) return hipErrorInvalidValue;  // the adjoint hop runs on the caller's links only
+    if (nblocks <= 0) return hipSuccess;
+    HOP_FULL(L64_18, false, RED_NONE)
+    HOP_FULL(L64_18, true, RED_NONE)
+    HOP_FULL(L64_18, false, RED_ZDOT)
+    HOP_FULL(L64_18, false, RED_OUTX)
+    HOP_FULL(L64_18, false, RED_NORM)
+    HOP_FULL(L64_12, false, RED_ZDOT)
+    HOP_FULL(L64_12, false, RED_OUTX)
+    HOP_FULL(L64_12, false, RED_NORM)
+    return hipErrorInvalidValue;
+}
+
 } // namespace wd

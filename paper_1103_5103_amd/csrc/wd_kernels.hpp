@@ -20,6 +20,16 @@ enum SweepOp { OP_W = 0, OP_XR = 1, OP_S = 2, OP_INIT = 4, OP_ACC = 5, OP_NORM =
 hipError_t launch_hop(int sf, int lf, bool dag, int red, int fin, const HopJob* jobs, int njobs, long nblocks,
                       SysState* sys, int gated, hipStream_t s, int* exec = nullptr, int stage = -1, int tg = 0,
                       int ntl = 1, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// FP64 hop of both parities of full-lattice fields (every job with links_nb set, its two parities
+// in one group); RED_NONE with 18-real links only
+// Block order of such a launch: t fastest within groups of 8 blocks (2048 sites of each parity), so
+// that the t neighbours' spinors and links are still in L2 (32^3x64, <rhat, A s> in site order / groups
+// of 4 / 8 / 16 / 32 blocks: 460 / 479 / 428 / 435 / 452 us); site order where t-slices are no whole
+// number of blocks.
+void full_tile(HopJob& j);
+hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
+                           int gated, hipStream_t s, int* exec = nullptr, int tg = 0, hipEvent_t ev0 = nullptr,
+                           hipEvent_t ev1 = nullptr);
 // Multi-RHS hop (tables whose jobs have rhs >= 2): kt = mrhs_kt(largest group), 2 or 4 systems per
 // thread at most (0: unsupported group size). Low-precision spinors only.
 int mrhs_kt(int k);

@@ -80,7 +80,6 @@ void apply_noalloc(wd_gauge* g, double kappa, double* out, const double* in, boo
     JobPair jp;
     std::memset(&jp, 0, sizeof(jp));
     const int nb = (G.Vh + BLOCK - 1) / BLOCK;
-    double link_bytes = 0;
     for (int p = 0; p < 2; p++) {
         HopJob& j = jp.j[p];
         j.g = G;
@@ -92,20 +91,19 @@ void apply_noalloc(wd_gauge* g, double kappa, double* out, const double* in, boo
         j.c0 = 1.0 / (2.0 * kappa);
         j.c2 = -0.5;
         j.links = g->lk(L64_18, p);
+        j.links_nb = g->lk(L64_18, 1 - p);
         j.lcs = g->lcs();
         j.nblk = nb;
-        j.blk0 = p * nb;
         j.rblk0 = p * nb;
         j.rnblk = 2 * nb;
-        j.ilv = 1;
-        link_bytes += (double)G.Vh * 8 * link_chunks(L64_18) * link_chunk_bytes(L64_18);
+        j.ilv = 2;
+        j.ilv_pos = p;
+        full_tile(j);
     }
-    // the load policy wd_apply's launch takes (non-temporal links above 64 MB)
-    const int ntl = link_bytes > 64.0 * (1 << 20) ? 1 : 0;
     WD_CHECK_HIP(launch_pack_spinor(SF64, in, G, f64_half(fa, G.stride, 0), f64_half(fa, G.stride, 1), 0, 1.0, s));
     hipLaunchKernelGGL(k_store_jobs, dim3(1), dim3(64), 0, s, jobs, jp);
     WD_CHECK_HIP(hipGetLastError());
-    WD_CHECK_HIP(launch_hop(SF64, L64_18, dag, RED_NONE, FIN_STORE, jobs, 2, 2L * nb, sys, 0, s, nullptr, -1, 0, ntl));
+    WD_CHECK_HIP(launch_hop_full(dag, L64_18, RED_NONE, jobs, 2, 2L * nb, sys, 0, s));
     WD_CHECK_HIP(launch_unpack_spinor(SF64, out, G, f64_half(fb, G.stride, 0), f64_half(fb, G.stride, 1), 0, 1.0, s));
 }
 

@@ -210,8 +210,8 @@ static bool tile_valid(const Geo& g, int tz)
 static void set_tile(HopJob& j, int tz)
 {
     if (!tile_valid(j.g, tz)) tz = 0;
-    j.tz = tz;
-    j.bpp = tz > 0 ? j.g.Xh * j.g.Y / BLOCK : 0;
+    j.tb = tz > 0 ? tz * (j.g.Xh * j.g.Y / BLOCK) : 0;
+    j.bps = tz > 0 ? j.g.Xh * j.g.Y / BLOCK * j.g.Z : 0;
 }
 
 static HopJob hop_job(const Geo& g, int parity, int sys, const SpinorRef& in, const SpinorRef& out,
@@ -349,8 +349,12 @@ static int interleave_max() { return kIlvMax; }
 
 static bool same_links(const HopJob& a, const HopJob& b)
 {
+    // full-lattice launches: the two parities of one system
+    if (a.links_nb || b.links_nb)
+        return a.sys == b.sys && a.parity != b.parity && a.links == b.links_nb && a.links_nb == b.links && a.nblk == b.nblk &&
+               a.tb == b.tb && a.bps == b.bps;
     return a.links == b.links && a.parity == b.parity && a.g.Vh == b.g.Vh && a.g.X == b.g.X && a.g.Y == b.g.Y &&
-           a.g.Z == b.g.Z && a.g.T == b.g.T && a.nblk == b.nblk && a.tz == b.tz && a.bpp == b.bpp && a.rhs == b.rhs &&
+           a.g.Z == b.g.Z && a.g.T == b.g.T && a.nblk == b.nblk && a.tb == b.tb && a.bps == b.bps && a.rhs == b.rhs &&
            a.tg == b.tg && a.lcs == b.lcs;
 }
 static bool same_links(const SweepJob&, const SweepJob&) { return false; }
@@ -403,7 +407,8 @@ static SweepJob sweep_job(int sys, long n)
     return j;
 }
 
-// Compulsory bytes of a hop launch: every job's spinors; the links once per interleaved group,
+// Compulsory bytes of a hop launch: every job's spinors; the links once per interleaved group (both
+// parities of a full-lattice launch count the 8 links per site that they use),
 // in temporal gauge without the unit time links (loaded on the sites of time slices 0 and T - 1)
 static double hop_bytes(const JobTable<HopJob>& t, int sf, int lf, int extra_fields)
 {
@@ -411,7 +416,7 @@ static double hop_bytes(const JobTable<HopJob>& t, int sf, int lf, int extra_fie
     for (auto& j : t.host) {
         n += (double)j.g.Vh;
         const double frac = j.tg ? 0.75 + 0.25 * (j.g.T > 2 ? 2.0 / j.g.T : 1.0) : 1.0;
-        if (j.ilv <= 1 || j.ilv_pos == 0) nl += (double)j.g.Vh * frac;
+        if (j.ilv <= 1 || j.ilv_pos == 0 || j.links_nb) nl += (double)j.g.Vh * frac;
     }
     return n * (2 + extra_fields) * spinor_site_bytes(sf) + nl * link_site_bytes(lf);
 }
@@ -1033,7 +1038,7 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
 
     Field B = g->field("ms.B", SF64, 2), X = g->field("ms.X", SF64, 2);
     Field Sv = g->field("ms.S", SF64, 2), AS = g->field("ms.AS", SF64, 2);
-    Field AW = g->field("ms.AW", SF64, 2), RES = g->field("ms.RES", SF64, 2);
+    Field AW = g->field("ms.AW", SF64, 2);
     std::vector<Field> XS(ns), SS(ns);
     for (int k = 0; k < ns; k++) {
         XS[k] = g->field("ms.XS" + std::to_string(k), SF64, 2);
@@ -1079,15 +1084,15 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     j.f[R_F4] = X.all();
     Init.host.push_back(j);
     JobTable<HopJob> HAs;
-    const int tz64 = tune_tile(g, SF64, L64, st);
     auto hop = [&](const Field& in, const Field& out, int p, const SpinorRef* z) {
         HopJob h = hop_job(geo, p, 0, in.half(1 - p), out.half(p), g->slk(L64, p), g->lcs(), -0.5);
+        h.links_nb = g->slk(L64, 1 - p);
         h.tg = g->tg;
         h.nc = g->nc;
         h.x0 = in.half(p);
         h.c0 = a;
         if (z) h.z = *z;
-        set_tile(h, tz64);
+        full_tile(h);
         return h;
     };
     for (int p = 0; p < 2; p++) {
@@ -1212,14 +1217,15 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
             const Field& Xi = i == base ? X : XS[shift_of[i]];
             const double ai = 1.0 / (2.0 * kappas[i]);
             for (int p = 0; p < 2; p++) {
-                HopJob h = hop_job(geo, p, i, Xi.half(1 - p), RES.half(p), g->slk(L64, p), g->lcs(), 0.5);
+                HopJob h = hop_job(geo, p, i, Xi.half(1 - p), SpinorRef{}, g->slk(L64, p), g->lcs(), 0.5);
+                h.links_nb = g->slk(L64, 1 - p);
                 h.tg = g->tg;
                 h.nc = g->nc;
                 h.x0 = B.half(p);
                 h.c0 = 1.0;
                 h.x1 = Xi.half(p);
                 h.c1 = -ai;
-                set_tile(h, tz64);
+                full_tile(h);
                 R.host.push_back(h);
             }
         }

@@ -127,10 +127,12 @@ struct HopJob {
     SpinorRef x0, x1;    // epilogue terms (p == nullptr: absent)
     SpinorRef z;         // partner of <z, out>
     const void* links;   // the 8 links per site of this output parity
+    const void* links_nb;  // full-lattice launches: those of the other parity (else NULL)
     long lcs;            // link chunk stride
     double c0, c1, c2;   // out = c0 x0 + c1 x1 + c2 * hop
-    int tz;              // block order: 0 = site order; > 0 = t fastest within groups of tz z-planes
-    int bpp;             // blocks per (z, t) plane when tz > 0
+    int tb;              // block order: 0 = site order; > 0 = t fastest within groups of tb consecutive
+                         // blocks of a t-slice (which is a whole number of blocks then)
+    int bps;             // blocks per t-slice when tb > 0
     // Jobs that read the same links (same gauge field and parity) may form an interleaved group
     // of ilv consecutive jobs with equal blk0: block blk0 + ilv * l + k runs block l of job
     // (first + k), so the systems' blocks for one range of sites run together on one XCD and the

@@ -1,0 +1,54 @@
+"""The FP64 hop of both parities in one launch (wd_apply, wd_apply_dag, BiCGstab-M): forward links
+only, the two parities' blocks in turn, blocks ordered t fastest in groups of a t-slice. Shapes at the
+edges of that order: slices of 9 blocks (a smaller last group), of exactly one group, of one block, of
+no whole number of blocks, T = 2, and the smallest lattice; links that are not SU(3) too.
+
+Tolerance: one application has about 150 rounded FP64 terms per component, of comparable size:
+150 x 1.1e-16 < 2e-14 relative to the largest component.
+"""
+import numpy as np
+import pytest
+import torch
+
+import lattice_inputs as li
+import oracle
+import paper_1103_5103_amd as wd
+
+pytestmark = pytest.mark.gpu
+SHAPES = [(8, 16, 36, 4), (16, 16, 18, 2), (16, 16, 16, 2), (8, 8, 8, 4), (6, 10, 4, 6), (2, 2, 2, 2), (4, 4, 4, 8)]
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("su3", [True, False])
+@pytest.mark.parametrize("dims", SHAPES)
+def test_apply_matches_oracle(dims, su3):
+    print("case", dims, su3, flush=True)
+    anti = dims[0] != 6
+    U = li.random_links(dims, 1.0, 1901)
+    if not su3:
+        U = U + 0.1 * li.random_links(dims, 0.3, 1902)
+    psi = li.gaussian_field(dims, 2901)
+    g = wd.wd_gauge_create(_t(U), antiperiodic=anti)
+    for dag in (False, True):
+        ref = oracle.apply(U, 0.125, psi, dag=dag, antiperiodic=anti)
+        out = (wd.wd_apply_dag if dag else wd.wd_apply)(g, 0.125, _t(psi)).cpu().numpy()
+        assert np.abs(out - ref).max() <= 2e-14 * np.abs(ref).max(), (dims, su3, dag)
+    g.close()
+
+
+@pytest.mark.parametrize("dims", SHAPES[:5])
+@pytest.mark.parametrize("gauge", ["caller", "temporal"])
+def test_bicgstab_m_matches_oracle(dims, gauge):
+    print("case", dims, gauge, flush=True)
+    kappas = [0.12, 0.13]
+    U, b = li.random_links(dims, 1.0, 1903), li.gaussian_field(dims, 2903)
+    p = wd.params(tol=1e-10, mixed=False, eo=False)
+    g = wd.wd_gauge_create(_t(U), hint=wd.params(mixed=False, temporal_gauge=gauge == "temporal", nonchiral=gauge == "caller"))
+    xs, sts = wd.bicgstab_m_solve(g, kappas, _t(b), p=p)
+    for k, x, s in zip(kappas, xs, sts):
+        res = oracle.true_residual(U, k, x.cpu().numpy(), b)
+        assert res < 1e-10 and abs(res - s["true_rel_res"]) < 1e-3 * res + 1e-15, (dims, k, res, s)
+    g.close()
