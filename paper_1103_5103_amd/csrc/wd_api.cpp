@@ -196,44 +196,14 @@ static wd_status apply_impl(wd_gauge* g, double kappa, double* out, const double
         if (out == in) throw Error{WD_ERR_ARG, "in and out must be distinct"};
         if (!(kappa > 0)) throw Error{WD_ERR_ARG, "kappa must be positive"};
         hipStream_t s = (hipStream_t)stream;
-        Field& A = g->field("apply.in", SF64, 2);
-        Field& B = g->field("apply.out", SF64, 2);
-        char key[64];
-        std::snprintf(key, sizeof(key), "apply.%.17g.%d", kappa, (int)dag);
-        auto it = g->hop_tables.find(key);
-        if (it == g->hop_tables.end()) {
-            JobTable<HopJob> t;
-            int b0 = 0;
-            for (int p = 0; p < 2; p++) {
-                HopJob j;
-                std::memset(&j, 0, sizeof(j));
-                j.g = g->geo;
-                j.parity = p;
-                j.in = A.half(1 - p);
-                j.out = B.half(p);
-                j.x0 = A.half(p);
-                j.c0 = 1.0 / (2.0 * kappa);
-                j.c2 = -0.5;
-                j.links = g->lk(L64_18, p);
-                j.links_nb = g->lk(L64_18, 1 - p);
-                j.lcs = g->lcs();
-                j.nblk = (g->geo.Vh + BLOCK - 1) / BLOCK;
-                j.rblk0 = b0;
-                j.ilv = 2;
-                j.ilv_pos = p;
-                full_tile(j);
-                b0 += j.nblk;
-                t.host.push_back(j);
-            }
-            for (auto& j : t.host) j.rnblk = b0;
-            t.upload(s);
-            if (g->hop_tables.size() > 64) g->hop_tables.clear();
-            it = g->hop_tables.emplace(key, t).first;
+        // the kernel reads neighbours while it writes: an input that overlaps the output is copied first
+        const size_t bytes = (size_t)g->V * 24 * sizeof(double);
+        if (ranges_overlap(out, in, bytes)) {
+            void* copy = g->rawbuf("apply.in", bytes);
+            WD_CHECK_HIP(hipMemcpyAsync(copy, in, bytes, hipMemcpyDeviceToDevice, s));
+            in = (const double*)copy;
         }
-        SysState* dummy = (SysState*)g->rawbuf("apply.sys", sizeof(SysState));
-        WD_CHECK_HIP(launch_pack_spinor(SF64, in, g->geo, A.half(0), A.half(1), 0, 1.0, s));
-        run_hop(SF64, L64_18, dag, RED_NONE, FIN_STORE, it->second, dummy, 0, s, (double)g->geo.Vh * 2 * (192 * 3 + 1152));
-        WD_CHECK_HIP(launch_unpack_spinor(SF64, out, g->geo, B.half(0), B.half(1), 0, 1.0, s));
+        run_apply(g, kappa, out, in, dag, s);
         return WD_OK;
     });
 }

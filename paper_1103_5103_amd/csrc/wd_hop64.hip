@@ -39,8 +39,6 @@ hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int nj
 {
     if (tg && dag) return hipErrorInvalidValue;  // the adjoint hop runs on the caller's links only
     if (nblocks <= 0) return hipSuccess;
-    HOP_FULL(L64_18, false, RED_NONE)
-    HOP_FULL(L64_18, true, RED_NONE)
     HOP_FULL(L64_18, false, RED_ZDOT)
     HOP_FULL(L64_18, false, RED_OUTX)
     HOP_FULL(L64_18, false, RED_NORM)

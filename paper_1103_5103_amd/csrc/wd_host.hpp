@@ -139,7 +139,6 @@ struct wd_gauge {
     void ensure_slinks(int lf, hipStream_t s);
     std::map<std::string, wd::Field> ws;              // cached workspace fields
     std::map<std::string, std::shared_ptr<wd::DevMem>> raw;
-    std::map<std::string, wd::JobTable<wd::HopJob>> hop_tables;
     std::map<std::string, std::shared_ptr<void>> graphs;  // captured iteration chunks by launch key
     hipStream_t stream = nullptr;
     double recon_err = 1.0;  // max |row2 - conj(row0 x row1)| over the links
@@ -163,15 +162,23 @@ void* pinned(size_t bytes);
 // handed out again after the device has drained (the ring synchronises when it wraps)
 char* stage_alloc(size_t bytes);
 
-// wd_apply_noalloc: a fixed device array per GPU (kNoallocScratchBytes) holds the job table and a
-// system record in its first kNoallocTableBytes, then the packed FP64 input and output fields
+// wd_apply_noalloc: a fixed device array per GPU (kNoallocScratchBytes) takes a copy of an input that
+// overlaps the output. The size limit counts a table and two packed fields.
 constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;
 constexpr size_t kNoallocTableBytes = (size_t)64 << 10;
 constexpr int kNoallocMaxDevices = 64;
 size_t noalloc_scratch_need(long stride);
 void apply_noalloc(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s);
 
+// do two device ranges of this many bytes share an address
+inline bool ranges_overlap(const void* a, const void* b, size_t bytes)
+{
+    return (const char*)a < (const char*)b + bytes && (const char*)b < (const char*)a + bytes;
+}
+
 // launch helpers with optional timing
+// out = M(kappa) in or M^dag in on canonical FP64 fields that do not overlap
+void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s);
 // stage / ntl: -1 the defaults (LDS staging as built; non-temporal link loads unless the launch's
 // links are shared or small), else forced (0 off, 1 on)
 void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>& t, SysState* sys, int gated,

@@ -21,7 +21,7 @@ hipError_t launch_hop(int sf, int lf, bool dag, int red, int fin, const HopJob* 
                       SysState* sys, int gated, hipStream_t s, int* exec = nullptr, int stage = -1, int tg = 0,
                       int ntl = 1, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // FP64 hop of both parities of full-lattice fields (every job with links_nb set, its two parities
-// in one group); RED_NONE with 18-real links only
+// in one group); red: one of the fused reductions
 // Block order of such a launch: t fastest within groups of 8 blocks (2048 sites of each parity), so
 // that the t neighbours' spinors and links are still in L2 (32^3x64, <rhat, A s> in site order / groups
 // of 4 / 8 / 16 / 32 blocks: 460 / 479 / 428 / 435 / 452 us); site order where t-slices are no whole
@@ -88,6 +88,9 @@ struct GuessArgs {
     long n;
     int k, acc;
 };
+// dst = M src (dag: M^dag src), canonical FP64 fields that do not overlap, 18-real links; c0 = 1/(2 kappa)
+hipError_t launch_apply(bool dag, double* dst, const double* src, const Geo& g, const void* lk_even, const void* lk_odd,
+                        long lcs, double c0, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_guess(const GuessArgs& a, hipStream_t s);
 hipError_t launch_dots(SpinorRef a, const SpinorRef* bs, int m, const Geo& g, double* partials, double* out,
                        hipStream_t s);

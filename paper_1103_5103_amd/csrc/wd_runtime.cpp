@@ -286,6 +286,19 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     if (red != RED_NONE) run_finish(3, fin, t, sys, gated, s);
 }
 
+void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s)
+{
+    Timer& T = timer();
+    hipEvent_t a = nullptr, b = nullptr;
+    if (T.on) {
+        a = T.get();
+        b = T.get();
+    }
+    WD_CHECK_HIP(launch_apply(dag, out, in, g->geo, g->lk(L64_18, 0), g->lk(L64_18, 1), g->lcs(), 1.0 / (2.0 * kappa), s,
+                              a, b));
+    if (T.on) T.pending.push_back({TK_HOP_F64, a, b, (double)g->V * (2 * 192 + 4 * 144), -1, 0, -1});
+}
+
 // the fields that an operation's kernel reads or writes whatever its flags (bit r: role r)
 static unsigned sweep_roles(int op)
 {

@@ -1,4 +1,4 @@
-"""The FP64 hop of both parities in one launch (wd_apply, wd_apply_dag, BiCGstab-M): forward links
+"""FP64 operators on both parities in one launch (wd_apply, wd_apply_dag, BiCGstab-M): forward links
 only, the two parities' blocks in turn, blocks ordered t fastest in groups of a t-slice. Shapes at the
 edges of that order: slices of 9 blocks (a smaller last group), of exactly one group, of one block, of
 no whole number of blocks, T = 2, and the smallest lattice; links that are not SU(3) too.
@@ -15,7 +15,7 @@ import oracle
 import paper_1103_5103_amd as wd
 
 pytestmark = pytest.mark.gpu
-SHAPES = [(8, 16, 36, 4), (16, 16, 18, 2), (16, 16, 16, 2), (8, 8, 8, 4), (6, 10, 4, 6), (2, 2, 2, 2), (4, 4, 4, 8)]
+SHAPES = [(8, 16, 36, 4), (16, 16, 18, 2), (16, 16, 16, 2), (8, 8, 8, 4), (6, 10, 4, 6), (2, 2, 2, 2), (4, 4, 4, 8), (40, 2, 2, 4), (14, 10, 6, 2)]
 
 
 def _t(a):
@@ -51,4 +51,26 @@ def test_bicgstab_m_matches_oracle(dims, gauge):
     for k, x, s in zip(kappas, xs, sts):
         res = oracle.true_residual(U, k, x.cpu().numpy(), b)
         assert res < 1e-10 and abs(res - s["true_rel_res"]) < 1e-3 * res + 1e-15, (dims, k, res, s)
+    g.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 8), (8, 16, 36, 4)])
+def test_apply_with_overlapping_fields(dims):
+    """Distinct in and out that share memory give the result of separate fields."""
+    U = li.random_links(dims, 1.0, 1905)
+    g = wd.wd_gauge_create(_t(U))
+    n = int(np.prod(g.field_shape))
+    for dag in (False, True):
+        for shift in (1, n // 2):
+            buf = torch.zeros(n + shift, dtype=torch.complex128, device="cuda")
+            psi = _t(li.gaussian_field(dims, 2905))
+            ref = (wd.wd_apply_dag if dag else wd.wd_apply)(g, 0.12, psi)
+            for no_alloc in (False, True):
+                a, b = buf[:n].view(g.field_shape), buf[shift:].view(g.field_shape)
+                b.copy_(psi)
+                if no_alloc:
+                    wd.wd_apply_noalloc(g, 0.12, b, a, dagger=dag)
+                else:
+                    (wd.wd_apply_dag if dag else wd.wd_apply)(g, 0.12, b, out=a)
+                assert torch.equal(a, ref), (dims, dag, shift, no_alloc)
     g.close()
