@@ -306,7 +306,8 @@ def bicgstab_solve(g: Gauge, kappa: float, b: torch.Tensor, x: torch.Tensor | No
                    p: SolverParams | None = None, raise_on_fail: bool = True):
     """Solve M(kappa) x = b; returns (x, stats dict). With p.use_x0, x holds the start vector."""
     p = params() if p is None else p
-    x = torch.zeros_like(b) if x is None else x
+    if x is None:  # written whole by the solve; zero only as a start vector
+        x = torch.zeros_like(b) if p.use_x0 else torch.empty_like(b)
     st = SolverStats()
     code = load().bicgstab_solve(g.handle, float(kappa), _ptr(x, "x", g.field_shape), _ptr(b, "b", g.field_shape),
                                  ctypes.byref(p), ctypes.byref(st), _stream())
@@ -316,7 +317,7 @@ def bicgstab_solve(g: Gauge, kappa: float, b: torch.Tensor, x: torch.Tensor | No
 
 def _xs(g, xs, n, like):
     if xs is None:
-        xs = [torch.zeros_like(like) for _ in range(n)]
+        xs = [torch.empty_like(like) for _ in range(n)]  # written whole by the solve
     arr = (ctypes.c_void_p * n)(*[_ptr(t, "x[i]", g.field_shape).value for t in xs])
     return xs, arr
 

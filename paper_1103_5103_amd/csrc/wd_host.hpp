@@ -162,6 +162,38 @@ void* pinned(size_t bytes);
 // handed out again after the device has drained (the ring synchronises when it wraps)
 char* stage_alloc(size_t bytes);
 
+// Host memory for the reports of one solve's systems (at most kMaxReports), taken from a process-wide
+// pool and given back when the solve ends; the stream must have drained by then. The pool keeps at
+// most kReportPool blocks, the rest is freed. Safe with several threads.
+constexpr int kMaxReports = 1024;
+constexpr int kReportPool = 16;
+struct Reports {
+    volatile SysReport* r = nullptr;
+    hipStream_t st;
+    explicit Reports(hipStream_t s);
+    ~Reports();
+    Reports(const Reports&) = delete;
+    Reports& operator=(const Reports&) = delete;
+    struct View {
+        int status, nrel, iter;
+        double rr;
+    };
+    View get(int i) const;
+    // wait until ok(view) holds for system i; throws if the stream ends or fails without it
+    template <class F>
+    View wait(int i, F&& ok) const
+    {
+        View v = get(i);
+        for (long n = 1; !ok(v); n++) {
+            pause(n, i);
+            v = get(i);
+        }
+        return v;
+    }
+    void pause(long n, int i) const;
+    mutable bool idle = false;  // the stream had drained at the last look
+};
+
 // wd_apply_noalloc: a fixed device array per GPU (kNoallocScratchBytes) takes a copy of an input that
 // overlaps the output. The size limit counts a table and two packed fields.
 constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;

@@ -42,21 +42,38 @@ __device__ __forceinline__ double2 c_real(double r) { return make_double2(r, 0.0
 __device__ __forceinline__ double c_abs2(double2 a) { return a.x * a.x + a.y * a.y; }
 __device__ __forceinline__ bool c_finite(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 
+// Tell the host (relaxed system-scope stores; the first has left before the second is issued).
+__device__ __forceinline__ void report(SysState* S)
+{
+    SysReport* R = S->report;
+    if (!R) return;
+    __hip_atomic_store(&R->rr, S->rr_true, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __builtin_amdgcn_s_waitcnt(0);
+    const unsigned long long v = ((unsigned long long)S->status << 56) |
+                                 ((unsigned long long)(S->nrel & 0xffffff) << 32) | (unsigned)S->iter;
+    __hip_atomic_store(&R->state, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void stop(SysState* S, int status)
+{
+    S->status = status;
+    report(S);
+}
+
 template <int FIN>
 __device__ void finish(SysState* S, const double* tot)
 {
     for (int k = 0; k < NRED; k++) S->red[k] = tot[k];
     if constexpr (FIN == FIN_BETA) {
         const double2 rhAs = make_double2(tot[0], tot[1]);
-        if (!c_finite(rhAs)) { S->status = ST_NAN; return; }
-        if (c_abs2(rhAs) == 0.0) { S->status = ST_BREAKDOWN; return; }
+        if (!c_finite(rhAs)) return stop(S, ST_NAN);
+        if (c_abs2(rhAs) == 0.0) return stop(S, ST_BREAKDOWN);
         const double2 beta = c_neg(c_div(S->delta, rhAs));
         S->beta = beta;
     } else if constexpr (FIN == FIN_CHI) {
         const double2 aww = make_double2(tot[0], tot[1]);
         const double awaw = tot[2];
-        if (!c_finite(aww) || !isfinite(awaw)) { S->status = ST_NAN; return; }
-        if (awaw == 0.0) { S->status = ST_BREAKDOWN; return; }
+        if (!c_finite(aww) || !isfinite(awaw)) return stop(S, ST_NAN);
+        if (awaw == 0.0) return stop(S, ST_BREAKDOWN);
         const double2 chi = make_double2(aww.x / awaw, aww.y / awaw);
         S->chi = chi;
     } else if constexpr (FIN == FIN_ALPHA) {
@@ -85,11 +102,26 @@ __device__ void finish(SysState* S, const double* tot)
         }
         S->alpha = alpha;
         S->delta = d1;
+        report(S);
     } else if constexpr (FIN == FIN_RESTART) {
         S->delta = make_double2(tot[0], tot[1]);
         S->rr = tot[2];
         S->maxrr = tot[2];
         S->status = (isfinite(tot[2]) && c_finite(S->delta)) ? ST_RUNNING : ST_NAN;
+        report(S);
+    } else if constexpr (FIN == FIN_UPDATE) {
+        // the true residual: finished, or go on with rhat and s kept (SEL1) or from r alone (SEL2: after a
+        // breakdown, and every outer step of defect correction)
+        const double rr = tot[2];
+        const int was = S->status;
+        S->nrel += 1;
+        S->rr_true = rr;
+        if (!isfinite(rr)) S->status = ST_NAN;
+        else if (rr <= S->target2) S->status = ST_DONE;
+        else if (was == ST_MAXIT || S->iter >= S->maxit) S->status = ST_NOCONV;
+        else if (was == ST_BREAKDOWN) S->status = ++S->restarts > 2 ? ST_BROKEN : ST_SEL2;
+        else S->status = S->dc ? ST_SEL2 : ST_SEL1;
+        report(S);
     } else if constexpr (FIN == FIN_CGA) {
         // CG: alpha_n = |r_n|^2 / <p_n, A p_n> (tot[0] = Re <p, A p>; A Hermitian positive definite)
         const double pAp = tot[0];
@@ -219,7 +251,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         }
     } else if constexpr (OP == OP_INIT) {
         // r_lo = r_hi; optionally rhat = r_lo, s = r_lo (flags 1, 2), x_lo = 0 (flags 4); CG (flags 8):
-        // p = r_lo + beta p with the beta the host set in the record; then <rhat, r_lo>, |r_lo|^2
+        // p = r_lo + beta p with the beta the host set in the record; then <rhat, r_lo>, |r_lo|^2.
+        // A system that restarts (SEL2) takes its flags from the second byte.
+        const int flags = S->status == ST_SEL2 ? J.flags >> 8 : J.flags & 255;
         if (ok) {
             cx<T> r[12];
             {
@@ -231,9 +265,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             store_spinor<SFL, T, NTS>(J.f[R_F0], i, r);
             // the dot products use the values as stored
             load_spinor<SFL, T, true>(J.f[R_F0], i, r);
-            if (J.flags & 1) store_spinor<SFL, T, NTS>(J.f[R_F2], i, r);
-            if (J.flags & 2) store_spinor<SFL, T, NTS>(J.f[R_F3], i, r);
-            if (J.flags & 8) {
+            if (flags & 1) store_spinor<SFL, T, NTS>(J.f[R_F2], i, r);
+            if (flags & 2) store_spinor<SFL, T, NTS>(J.f[R_F3], i, r);
+            if (flags & 8) {
                 const T bt = (T)S->cgb;
                 cx<T> pp[12];
                 load_spinor<SFL, T, true>(J.f[R_F3], i, pp);
@@ -241,14 +275,14 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
                 for (int k = 0; k < 12; k++) pp[k] = r[k] + bt * pp[k];
                 store_spinor<SFL, T, NTS>(J.f[R_F3], i, pp);
             }
-            if (J.flags & 4) {
+            if (flags & 4) {
                 cx<T> zero[12];
 #pragma unroll
                 for (int k = 0; k < 12; k++) zero[k] = mk<T>(T(0), T(0));
                 store_spinor<SFX, T, NTS>(J.f[R_F4], i, zero);
             }
             cx<T> rh[12];
-            if (J.flags & 1) {
+            if (flags & 1) {
 #pragma unroll
                 for (int k = 0; k < 12; k++) rh[k] = r[k];
             } else {
@@ -947,6 +981,7 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     FIN_CASE(3, FIN_CHI)
     FIN_CASE(3, FIN_ALPHA)
     FIN_CASE(3, FIN_RESTART)
+    FIN_CASE(3, FIN_UPDATE)
     FIN_CASE(3, FIN_CGA)
     FIN_CASE(3, FIN_CGB)
     return hipErrorInvalidValue;

@@ -77,6 +77,54 @@ void* pinned(size_t bytes)
     return buf;
 }
 
+// ---------------------------------------------------------------- reports
+static std::mutex g_reports_mu;
+static std::vector<void*> g_reports;
+
+Reports::Reports(hipStream_t s) : st(s)
+{
+    void* p = nullptr;
+    {
+        std::lock_guard<std::mutex> lk(g_reports_mu);
+        if (!g_reports.empty()) {
+            p = g_reports.back();
+            g_reports.pop_back();
+        }
+    }
+    if (!p)
+        WD_CHECK_HIP(hipHostMalloc(&p, sizeof(SysReport) * kMaxReports,
+                                   hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent));
+    std::memset(p, 0, sizeof(SysReport) * kMaxReports);
+    r = (volatile SysReport*)p;
+}
+Reports::~Reports()
+{
+    (void)hipStreamSynchronize(st);  // no kernel may report into a block that another solve has taken
+    std::lock_guard<std::mutex> lk(g_reports_mu);
+    if (g_reports.size() < (size_t)kReportPool) g_reports.push_back((void*)r);
+    else (void)hipHostFree((void*)r);
+}
+Reports::View Reports::get(int i) const
+{
+    View v;
+    const unsigned long long s = __atomic_load_n(&r[i].state, __ATOMIC_ACQUIRE);
+    v.status = (int)(s >> 56);
+    v.nrel = (int)((s >> 32) & 0xffffff);
+    v.iter = (int)(unsigned)s;
+    v.rr = r[i].rr;
+    return v;
+}
+void Reports::pause(long n, int i) const
+{
+    if (idle) throw Error{WD_ERR_HIP, "the stream ended without the report of system " + std::to_string(i)};
+    __builtin_ia32_pause();
+    if (n % 4096) return;
+    // about every 100 us: has the stream failed, or ended (then the report is there at the next look)?
+    const hipError_t e = hipStreamQuery(st);
+    if (e == hipSuccess) idle = true;
+    else if (e != hipErrorNotReady) throw Error{WD_ERR_HIP, std::string("hipStreamQuery: ") + hipGetErrorString(e)};
+}
+
 // ---------------------------------------------------------------- timing
 Timer& timer()
 {

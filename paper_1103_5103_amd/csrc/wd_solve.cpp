@@ -424,16 +424,17 @@ static double hop_bytes(const JobTable<HopJob>& t, int sf, int lf, int extra_fie
 // rhat written (flags 1) or read (when it is a field of its own: CG passes r_lo), s written
 // (flags 2), p read and written (flags 8), x_lo cleared (flags 4; FP32 storage for the 16-bit
 // formats)
-static double init_bytes(const JobTable<SweepJob>& t, int sfl)
+static double init_bytes(const JobTable<SweepJob>& t, int sfl, bool restart = false)
 {
     const double bl = spinor_site_bytes(sfl), bx = spinor_site_bytes(sfl == SF64 ? SF64 : SF32);
     double n = 0;
     for (auto& j : t.host) {
+        const int flags = restart ? j.flags >> 8 : j.flags & 255;
         double b = spinor_site_bytes(SF64) + bl;
-        if ((j.flags & 1) || j.f[R_F2].p != j.f[R_F0].p) b += bl;
-        if (j.flags & 2) b += bl;
-        if (j.flags & 8) b += 2 * bl;
-        if (j.flags & 4) b += bx;
+        if ((flags & 1) || j.f[R_F2].p != j.f[R_F0].p) b += bl;
+        if (flags & 2) b += bl;
+        if (flags & 8) b += 2 * bl;
+        if (flags & 4) b += bx;
         n += (double)j.n * b;
     }
     return n;
@@ -528,7 +529,10 @@ static void prepare_source(wd_gauge* g, const std::string& key, const double* b,
 // launches after a system has stopped).
 constexpr int kPoll = 3;
 
-static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream_t st, int poll)
+// Returns with the last kernels (the unpacking) queued: rep, whose reports slot0 .. are used, ends with
+// the stream drained.
+static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream_t st, int poll, const Reports& rep,
+                     int slot0 = 0)
 {
     const int n = (int)S.size();
     const int SFL = P.mixed ? spinor_fmt_of(P.spinor_store) : SF64;
@@ -569,6 +573,9 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         e.a = 1.0 / (2.0 * e.kappa);
     }
 
+    bool any_x0 = false;
+    for (auto& e : S) any_x0 = any_x0 || e.x_ready || P.use_x0;
+
     SysArray sys;
     sys.alloc(n, S[0].g->raw["eo.sys"]);
     for (int i = 0; i < n; i++) {
@@ -581,14 +588,15 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         q.mixed = P.mixed;
         q.delta_rel2 = P.delta_reliable * P.delta_reliable;
         q.dc = P.mixed && P.mixed_mode == WD_MIXED_DEFECT;
+        q.report = (SysReport*)&rep.r[slot0 + i];
         q.target2 = -1.0;
+        q.rr_true = -1.0;
         q.status = ST_RUNNING;
     }
-    sys.upload(st);
 
     // ---- static job tables
     JobTable<HopJob> Hhb, Hx1, Hx2, Hrec;
-    JobTable<SweepJob> Nb, Bp, InitFirst, InitRel, InitRestart, Acc;
+    JobTable<SweepJob> Nb, Bp, InitFirst, Init, Acc;
     JobTable<HopJob> H1, H2, H3, H4;
     JobTable<SweepJob> SW, SXR, SS;
     std::vector<int> need_src;
@@ -635,12 +643,11 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         sj.f[R_F2] = e.rh.all();
         sj.f[R_F3] = e.s.all();
         sj.f[R_F4] = e.xl.all();
+        sj.flags = (1 | 2) << 8;  // after an update: keep rhat and s (SEL1), or restart from r (SEL2)
+        Init.host.push_back(sj);
         sj.flags = 1 | 2 | 4;
+        if (!any_x0) sj.f[R_F1] = e.BP.all();  // x0 = 0: the start residual is b_prec
         InitFirst.host.push_back(sj);
-        sj.flags = 0;
-        InitRel.host.push_back(sj);
-        sj.flags = 1 | 2;
-        InitRestart.host.push_back(sj);
         sj = sweep_job(i, e.xl.nsites());
         sj.f[R_F0] = e.X64.half(0);
         sj.f[R_F1] = e.xl.all();
@@ -697,14 +704,14 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         group_by_links(*t);
         layout(*t);
     }
-    for (auto* t : {&Nb, &Bp, &InitFirst, &InitRel, &InitRestart, &Acc, &SW, &SXR, &SS}) layout(*t);
+    for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &Acc, &SW, &SXR, &SS}) layout(*t);
     // one copy for all tables, into a buffer kept by the first handle across solves
     upload_tables(st, S[0].g->raw["eo.tables"],
-                  {&Hhb, &Hx1, &Hx2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &InitRel, &InitRestart, &Acc,
-                   &SW, &SXR, &SS});
+                  {&Hhb, &Hx1, &Hx2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &Init, &Acc, &SW, &SXR, &SS});
 
     // ---- setup
     if (!need_src.empty()) {
+        sys.upload(st);
         run_hop(SF64, L64, false, RED_NONE, FIN_STORE, Hhb, sys.d(), 0, st, hop_bytes(Hhb, SF64, L64, 0));
         run_sweep(OP_NORM, SF64, Nb, sys.d(), 0, st, sweep_bytes(Nb, 192));
         sys.download(st);
@@ -713,15 +720,13 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
             for (int k : need_src)
                 if (S[i].src.bb < 0 && S[i].src.B64.base() == S[k].src.B64.base()) S[i].src.bb = S[k].src.bb;
     }
-    bool any_x0 = false;
     for (auto& e : S) {
-        any_x0 = any_x0 || e.x_ready || P.use_x0;
         if (e.x_ready) continue;
         if (P.use_x0)
             WD_CHECK_HIP(launch_pack_spinor(SF64, e.x, e.g->geo, e.X64.half(0), e.X64.half(1), P.dagger, 1.0, st,
                                             e.g->gm(), e.g->nc));
-        else
-            WD_CHECK_HIP(hipMemsetAsync(e.X64.base(), 0, e.X64.mem->bytes, st));
+        else  // the even half is iterated, the odd one written at the end
+            WD_CHECK_HIP(hipMemsetAsync(e.X64.base(), 0, e.X64.mem->bytes / 2, st));
     }
     WD_REQUIRE(n == 1 || !(S[0].r_ready || S[0].bp_ready), "a prepared start is for single-system solves");
     if (!S[0].bp_ready) run_sweep(OP_AXPY, SF64, Bp, sys.d(), 0, st, sweep_bytes(Bp, 3 * 192));
@@ -746,10 +751,6 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         }
     }
     sys.upload(st);
-    if (!any_x0) {
-        for (auto& j : InitFirst.host) j.f[R_F1] = S[j.sys].BP.all();
-        InitFirst.upload(st);
-    }
     run_sweep(OP_INIT, SFL, InitFirst, sys.d(), GATE_RUN, st, init_bytes(InitFirst, SFL));
     for (int i = 0; i < n; i++) S[i].t0 = t_start;
 
@@ -776,27 +777,59 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     // ST_DONE first): x_hi += x_lo, r_hi = b_prec - M_prec x_hi, |r_hi|^2. Every step runs on the
     // full job tables, so no per-subset tables or host synchronisation are needed.
     auto reliable_update = [&]() {
-        // the s update of the iteration in which the system stopped was gated off: apply it
-        // (the scalars of that iteration are still in place), since a continuing reliable update
-        // keeps s; defect correction restarts with s = r instead
-        if (!(P.mixed && P.mixed_mode == WD_MIXED_DEFECT)) run_sweep(OP_S, SFL, SS, sys.d(), GATE_STOPPED, st, bSS);
         run_sweep(OP_ACC, SFL, Acc, sys.d(), GATE_STOPPED, st, sweep_bytes(Acc, 2 * 192 + 2 * bx));
         run_hop(SF64, L64, false, RED_NONE, FIN_STORE, Hx1, sys.d(), GATE_STOPPED, st, hop_bytes(Hx1, SF64, L64, 0));
-        run_hop(SF64, L64, false, RED_NORM, FIN_STORE, Hx2, sys.d(), GATE_STOPPED, st, hop_bytes(Hx2, SF64, L64, 2));
+        run_hop(SF64, L64, false, RED_NORM, FIN_UPDATE, Hx2, sys.d(), GATE_STOPPED, st, hop_bytes(Hx2, SF64, L64, 2));
+    };
+    // the new residual into the iteration, and RUNNING again, for the systems that go on
+    auto resume = [&]() {
+        // the s update of the iteration in which the system stopped was gated off: apply it (the
+        // scalars and the iterated residual of that iteration are still in place), since a continuing
+        // reliable update keeps s; defect correction restarts with s = r instead
+        if (!(P.mixed && P.mixed_mode == WD_MIXED_DEFECT)) run_sweep(OP_S, SFL, SS, sys.d(), 1 << ST_SEL1, st, bSS);
+        run_sweep(OP_INIT, SFL, Init, sys.d(), (1 << ST_SEL1) | (1 << ST_SEL2), st,
+                  init_bytes(Init, SFL, P.mixed && P.mixed_mode == WD_MIXED_DEFECT));
     };
 
     int active = 0;
     for (auto& e : S) active += !e.done;
+    // The host watches the systems' reports and keeps one step of the iteration queued behind the one it
+    // waits for (its launches are gated off where the system has stopped meanwhile). A system that
+    // stopped gets its FP64 update; whether it has finished, goes on or restarts is decided on the
+    // device. After an update that only verifies convergence nothing is queued until its outcome is
+    // known.
+    struct Watch {
+        int expect = 0;      // the iteration that the queued steps reach
+        int nrel = 0;        // updates queued
+        bool verify = false; // waits for the outcome of an update without a resume behind it
+    };
+    std::vector<Watch> watch(n);
+    const int step = graph ? poll : 1;
     long host_iters = 0;
-    const long host_cap = (long)P.max_iter + 16L * poll + 64;
+    const long host_cap = 4L * P.max_iter + 16L * poll + 64;  // with the steps queued past a stop
+    int inflight = 0;  // queued steps not yet waited for
+    auto finished = [&](int i, const Reports::View& v) {
+        EoSys& e = S[i];
+        e.done = true;
+        e.t1 = now_s();
+        e.final_status = v.status == ST_DONE ? WD_OK : v.status == ST_NOCONV ? WD_ERR_NOCONV : v.status == ST_NAN ? WD_ERR_NAN : WD_ERR_BREAKDOWN;
+        active--;
+    };
+    auto terminal = [](int s) { return s == ST_DONE || s == ST_NOCONV || s == ST_BROKEN || s == ST_NAN; };
     while (active > 0) {
-        if (graph) graph->launch(st);
-        else
-            for (int k = 0; k < poll; k++) iterate(st);
-        host_iters += poll;
-        sys.download(st);
+        int running = 0;
+        for (int i = 0; i < n; i++) running += !S[i].done && !watch[i].verify;
+        while (running > 0 && inflight < 2) {
+            if (graph) graph->launch(st);
+            else iterate(st);
+            for (int i = 0; i < n; i++)
+                if (!watch[i].verify) watch[i].expect += step;
+            host_iters += step;
+            inflight++;
+        }
         if (host_iters > host_cap) {
             // the device never reported an exit state: stop instead of iterating forever
+            WD_CHECK_HIP(hipStreamSynchronize(st));
             for (auto& e : S)
                 if (!e.done) {
                     e.done = true;
@@ -805,66 +838,53 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
                 }
             break;
         }
-        bool any = false;
-        for (int i = 0; i < n; i++) {
-            const int stt = sys.h[i].status;
-            if (S[i].done || stt == ST_RUNNING) continue;
-            if (stt == ST_NAN) {  // gated off for good: no status change needed on the device
-                S[i].done = true;
-                S[i].final_status = WD_ERR_NAN;
-                S[i].t1 = now_s();
-                active--;
-                continue;
+        // the oldest step (or the outcome of a verifying update); if some system has stopped there, all
+        bool stopped = false, any_resume = false, any_update = false;
+        for (int pass = 0; pass < 2; pass++) {
+            const int back = pass == 0 && inflight > 0 ? (inflight - 1) * step : 0;
+            for (int i = 0; i < n; i++) {
+                if (S[i].done) continue;
+                const Watch& w = watch[i];
+                const Reports::View v = rep.wait(slot0 + i, [&](const Reports::View& v) {
+                    if (v.nrel != w.nrel) return false;
+                    if (w.verify) return true;
+                    return (v.status != ST_RUNNING && v.status != ST_SEL1 && v.status != ST_SEL2) ||
+                           (v.status == ST_RUNNING && v.iter >= w.expect - back);
+                });
+                stopped = stopped || v.status != ST_RUNNING;
             }
-            any = true;
+            if (!stopped) break;
         }
-        if (!any) continue;
-        reliable_update();
-        sys.download(st);
-        bool any_next = false, any_fresh = false;
+        inflight = stopped || inflight == 0 ? 0 : inflight - 1;
+        if (!stopped) continue;
         for (int i = 0; i < n; i++) {
-            EoSys& e = S[i];
-            SysState& q = sys.h[i];
-            const int stt = q.status;
-            if (e.done || stt == ST_RUNNING || stt == ST_NAN) continue;
-            e.reliable++;
-            const double rr = q.red[2];
-            e.rr_true = rr;
-            int next = ST_SEL1;  // continue: keep rhat and s
-            if (!std::isfinite(rr)) {
-                e.done = true;
-                e.final_status = WD_ERR_NAN;
-            } else if (rr <= q.target2) {
-                e.done = true;
-                e.final_status = WD_OK;
-            } else if (stt == ST_MAXIT || q.iter >= q.maxit) {
-                e.done = true;
-                e.final_status = WD_ERR_NOCONV;
-            } else if (stt == ST_BREAKDOWN) {
-                if (++e.restarts > 2) {
-                    e.done = true;
-                    e.final_status = WD_ERR_BREAKDOWN;
-                } else {
-                    next = ST_SEL2;  // restart fresh
-                }
-            }
-            // new residual: keep rhat and s (reliable update) or restart with rhat = s = r
-            // (breakdown, and every outer step of defect correction: a fresh inner solve)
-            if (!e.done && P.mixed && P.mixed_mode == WD_MIXED_DEFECT) next = ST_SEL2;
-            if (e.done) {
-                e.t1 = now_s();
-                active--;
-                q.status = ST_DONE;
-            } else {
-                q.status = next;
-                any_next = any_next || next == ST_SEL1;
-                any_fresh = any_fresh || next == ST_SEL2;
+            if (S[i].done) continue;
+            Watch& w = watch[i];
+            const Reports::View v = rep.get(slot0 + i);
+            w.expect = v.iter;
+            if (terminal(v.status)) {
+                finished(i, v);
+            } else if (v.status == ST_SEL1 || v.status == ST_SEL2) {  // the check failed: go on
+                w.verify = false;
+                any_resume = true;
+            } else if (v.status != ST_RUNNING) {
+                w.nrel++;
+                w.verify = v.status == ST_CONVERGED || v.status == ST_MAXIT;
+                any_update = true;
+                any_resume = any_resume || !w.verify;
             }
         }
-        sys.upload(st);
-        // the restart finishers set the continuing systems RUNNING again
-        if (any_next) run_sweep(OP_INIT, SFL, InitRel, sys.d(), 1 << ST_SEL1, st, init_bytes(InitRel, SFL));
-        if (any_fresh) run_sweep(OP_INIT, SFL, InitRestart, sys.d(), 1 << ST_SEL2, st, init_bytes(InitRestart, SFL));
+        if (any_update) reliable_update();
+        if (any_resume) {
+            resume();
+            for (auto& w : watch) w.verify = false;
+        }
+    }
+    for (int i = 0; i < n; i++) {
+        const Reports::View v = rep.get(slot0 + i);
+        S[i].iters = v.iter;
+        S[i].reliable = v.nrel;
+        if (v.nrel > 0) S[i].rr_true = v.rr;
     }
 
     // ---- finish: odd half from eq. eo3, unpack. With x_o from eq. eo3 the full residual is
@@ -880,7 +900,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
             nsweep += by_sweep;
         }
         if (nsweep < n) {
-            sys.upload(st);
+            sys.upload(st);  // (gates of this last step; the records are not used after it)
             run_hop(SF64, L64, false, RED_NONE, FIN_STORE, Hrec, sys.d(), 1 << ST_SEL2, st, hop_bytes(Hrec, SF64, L64, 1));
         }
         for (int i = 0; i < n; i++) {
@@ -894,11 +914,9 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
                                                   st, e.g->gm(), e.g->nc));
         }
     }
-    sys.download(st);
     for (int i = 0; i < n; i++) {
         EoSys& e = S[i];
         if (e.t1 == 0) e.t1 = now_s();
-        e.iters = sys.h[i].iter;
         if (!std::isfinite(e.src.bb) || e.final_status == WD_ERR_NAN) e.true_rel = std::nan("");
         else e.true_rel = (e.src.bb > 0 && e.rr_true >= 0) ? std::sqrt(e.rr_true) / (e.a * std::sqrt(e.src.bb)) : 0.0;
     }
@@ -1268,7 +1286,8 @@ wd_status solve_single(wd_gauge* g, double kappa, double* x, const double* b, co
     S[0].b = b;
     S[0].x = x;
     S[0].slot = 0;
-    eo_solve(S, P, st, kPoll);
+    Reports rep(st);
+    eo_solve(S, P, st, kPoll, rep);
     if (stats) {
         stats->iters = S[0].iters;
         stats->reliable_updates = S[0].reliable;
@@ -1302,7 +1321,8 @@ wd_status solve_batch(int nsys, const wd_system* sys, const wd_solver_params& P,
         S[i].x = sys[i].x;
         S[i].slot = slots[sys[i].gauge]++;
     }
-    eo_solve(S, P, st, kPoll);
+    Reports rep(st);
+    eo_solve(S, P, st, kPoll, rep);
     wd_status worst = WD_OK;
     for (int i = 0; i < nsys; i++) {
         if (stats) {
@@ -1513,7 +1533,8 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
         }
         wd_solver_params Q = P;
         Q.use_x0 = 0;
-        eo_solve(S, Q, st, kPoll);
+        Reports rep(st);
+        eo_solve(S, Q, st, kPoll, rep);
         wd_status worst = WD_OK;
         for (int i = 0; i < n; i++) {
             if (stats) {
@@ -1553,6 +1574,7 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
         X[i] = g->field("mm.X" + std::to_string(i), SF64, 2);
         R[i] = g->field("mm.R" + std::to_string(i), SF64, 1);
     }
+    Reports rep(st);
     std::vector<char> res_ok(n, 0);  // R[i] holds the residual of X[i] (a converged FP64 check)
     Field BPm = g->field("mm.BP", SF64, 1);
     SysState* dummy = (SysState*)g->rawbuf("apply.sys", sizeof(SysState));
@@ -1676,7 +1698,7 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
             e.x_ready = true;
         }
         std::vector<EoSys> S{e};
-        eo_solve(S, Q, st, kPoll);
+        eo_solve(S, Q, st, kPoll, rep, idx);
         src = S[0].src;  // |b|^2 is known after the first mass
         if (stats) {
             stats[idx].iters = S[0].iters;
@@ -1848,7 +1870,7 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         InitFirst.host.push_back(sj);
         sj.flags = 8;  // p = r + beta' p (beta' set by the host)
         InitRel.host.push_back(sj);
-        sj.flags = 2;
+        sj.flags = 2 << 8;  // (run for SEL2)
         InitRestart.host.push_back(sj);
         // iteration: t = D_oe p ; v = M_prec p ; t = (D_eo)^dag v ; w = (A + sigma) p, <p, w> ;
         // x += alpha p, r -= alpha w, |r|^2 ; p = r + beta p
@@ -2050,7 +2072,7 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         }
         sys.upload(st);
         if (any_next) run_sweep(OP_INIT, SFL, InitRel, sys.d(), 1 << ST_SEL1, st, init_bytes(InitRel, SFL));
-        if (any_fresh) run_sweep(OP_INIT, SFL, InitRestart, sys.d(), 1 << ST_SEL2, st, init_bytes(InitRestart, SFL));
+        if (any_fresh) run_sweep(OP_INIT, SFL, InitRestart, sys.d(), 1 << ST_SEL2, st, init_bytes(InitRestart, SFL, true));
     }
 
     for (auto& e : S)

@@ -25,9 +25,11 @@ enum SysStatus {
     ST_BREAKDOWN = 3,
     ST_NAN = 4,
     ST_MAXIT = 5,
-    ST_DONE = 6,        // set by the host for a finished system of a batch (no kernel runs it)
-    ST_SEL1 = 7,        // set by the host to select systems for a gated step (e.g. continue
-    ST_SEL2 = 8,        //   after a reliable update / restart fresh; finish by sweep / by hop)
+    ST_DONE = 6,        // finished (no kernel runs it): the FP64 residual met the target, or set by the host
+    ST_SEL1 = 7,        // selected for a gated step: continue after a reliable update / finish by sweep
+    ST_SEL2 = 8,        //   restart fresh / finish by hop
+    ST_NOCONV = 9,      // finished: iteration cap
+    ST_BROKEN = 10,     // finished: broke down again after its restarts
 };
 // Kernel gates are masks of the statuses allowed to run (0: no gating); GATE_RUN = the iteration.
 constexpr int GATE_RUN = 1 << ST_RUNNING;
@@ -41,6 +43,7 @@ enum Fin {
     FIN_ALPHA = 3,   // delta' = <rhat, r>, |r|^2, alpha, status (+ the iteration's scalars for the shifts)
     FIN_RESTART = 5, // new residual: delta = <rhat, r>, |r|^2, status RUNNING
     FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>
+    FIN_UPDATE = 8,  // FP64 residual update: |r|^2, finished or which way to go on
     FIN_CGB = 7,     // CG: beta = |r_new|^2 / |r|^2, status     (+ the iteration's scalars for the shifts)
 };
 
@@ -90,8 +93,20 @@ struct ShiftBlock {
     double target2;  // a shift is frozen once its |r|^2 is below
 };
 
+// What a system reports to the host, in host memory that the device writes (even-odd solves): the host
+// watches it instead of copying the record and waiting for the stream. state holds the status, the
+// number of FP64 updates and the iteration in one word, stored after rr.
+struct SysReport {
+    double rr;                 // |r|^2 of the last FP64 residual update
+    unsigned long long state;  // status << 56 | updates << 32 | iteration
+};
+
 struct SysState {
     int status;        // SysStatus
+    int nrel;          // FP64 residual updates so far
+    int restarts;      // after breakdowns
+    int pad;
+    SysReport* report; // NULL: none
     int iter;
     int maxit;
     int mixed;
@@ -100,6 +115,7 @@ struct SysState {
     double2 delta, beta, chi, alpha;
     double rr;         // |r|^2 of the iterated residual
     double maxrr;      // max |r|^2 since the last reliable update
+    double rr_true;    // |r|^2 of the last FP64 residual update
     double target2;    // stop when rr <= target2
     double delta_rel2; // reliable update when rr < delta_rel2 * maxrr
     double cga, cgb;   // CG: alpha_n, beta_n
