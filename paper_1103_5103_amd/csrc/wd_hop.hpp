@@ -18,13 +18,13 @@ __device__ __forceinline__ int xcd_remap(int b, int nb)
 
 // Block reduction of NR partial sums; thread 0 stores the block's partial at slot rb.
 template <int NR>
-__device__ __forceinline__ void write_partials(double v[NRED], SysState* S, int rb)
+__device__ __forceinline__ void write_partials(double v[NRED], SysState* S, int rb, bool second = false)
 {
     __shared__ double lds[NRED * (BLOCK / 64)];
     block_sum<NR>(v, lds);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int k = 0; k < NR; k++) S->partials[(long)rb * NRED + k] = v[k];
+        for (int k = 0; k < NR; k++) (second ? S->partials2 : S->partials)[(long)rb * NRED + k] = v[k];
     }
 }
 
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
             for (int k = 0; k < 12; k++) v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
         }
     }
-    if constexpr (RED != RED_NONE) write_partials<3>(v, S, J.rblk0 + lb);
+    if constexpr (RED != RED_NONE) write_partials<3>(v, S, J.rblk0 + lb, J.p2 != 0);
 }
 
 // ================================================================ launch dispatch

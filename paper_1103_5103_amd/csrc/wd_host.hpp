@@ -215,8 +215,9 @@ void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool da
 // links are shared or small), else forced (0 off, 1 on)
 void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>& t, SysState* sys, int gated,
              hipStream_t s, double bytes_per_site_total, int stage = -1, int ntl = -1);
+// fold: the sweep does the finisher of the reduction before it and leaves its own to the next sweep
 void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s,
-               double bytes_total);
+               double bytes_total, bool fold = false);
 // the block update of the shifted systems (launch_shift_update), timed as a sweep
 void run_shift_update(int nb, const ShiftVectors& v, long n, const ShiftBlock* blk, const ShiftCoef* coef,
                       hipStream_t s, double bytes_total);

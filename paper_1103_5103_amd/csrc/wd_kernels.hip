@@ -59,50 +59,77 @@ __device__ __forceinline__ void stop(SysState* S, int status)
     report(S);
 }
 
+// The scalars of a BiCGstab iteration from the reduced sums; each returns the status that follows.
+__device__ __forceinline__ int calc_beta(double2 delta, const double* tot, double2& beta)
+{
+    const double2 rhAs = make_double2(tot[0], tot[1]);
+    if (!c_finite(rhAs)) return ST_NAN;
+    if (c_abs2(rhAs) == 0.0) return ST_BREAKDOWN;
+    beta = c_neg(c_div(delta, rhAs));
+    return ST_RUNNING;
+}
+__device__ __forceinline__ int calc_chi(const double* tot, double2& chi)
+{
+    const double2 aww = make_double2(tot[0], tot[1]);
+    const double awaw = tot[2];
+    if (!c_finite(aww) || !isfinite(awaw)) return ST_NAN;
+    if (awaw == 0.0) return ST_BREAKDOWN;
+    chi = make_double2(aww.x / awaw, aww.y / awaw);
+    return ST_RUNNING;
+}
+// iter: the iteration that ends here
+__device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int iter, const double* tot, double2& alpha)
+{
+    const double2 d1 = make_double2(tot[0], tot[1]);
+    const double rr = tot[2];
+    alpha = c_neg(c_div(c_mul(S->beta, d1), c_mul(delta, S->chi)));
+    if (!isfinite(rr) || !c_finite(d1)) return ST_NAN;
+    if (rr <= S->target2) return ST_CONVERGED;
+    if (S->mixed && rr < S->delta_rel2 * S->maxrr) return ST_RELIABLE;
+    if (iter >= S->maxit) return ST_MAXIT;
+    if (c_abs2(d1) == 0.0) return ST_BREAKDOWN;
+    return ST_RUNNING;
+}
+__device__ __forceinline__ void store_alpha(SysState* S, int iter, const double* tot, double2 alpha, int status)
+{
+    const double rr = tot[2];
+    S->iter = iter;
+    S->rr = rr;
+    // The s update of this iteration is gated off for a system that stops; a solver that
+    // continues from s (reliable update) applies it later.
+    S->status = status;
+    if (!S->dc && rr > S->maxrr) S->maxrr = rr;
+    if (ShiftBlock* B = S->blk) {
+        IterScal& q = B->it[B->count];
+        q.beta = S->beta;
+        q.chi = S->chi;
+        q.alpha = alpha;
+        q.rr = rr;
+        B->count += 1;
+    }
+    S->alpha = alpha;
+    S->delta = make_double2(tot[0], tot[1]);
+    report(S);
+}
+
 template <int FIN>
 __device__ void finish(SysState* S, const double* tot)
 {
     for (int k = 0; k < NRED; k++) S->red[k] = tot[k];
     if constexpr (FIN == FIN_BETA) {
-        const double2 rhAs = make_double2(tot[0], tot[1]);
-        if (!c_finite(rhAs)) return stop(S, ST_NAN);
-        if (c_abs2(rhAs) == 0.0) return stop(S, ST_BREAKDOWN);
-        const double2 beta = c_neg(c_div(S->delta, rhAs));
+        double2 beta;
+        const int st = calc_beta(S->delta, tot, beta);
+        if (st != ST_RUNNING) return stop(S, st);
         S->beta = beta;
     } else if constexpr (FIN == FIN_CHI) {
-        const double2 aww = make_double2(tot[0], tot[1]);
-        const double awaw = tot[2];
-        if (!c_finite(aww) || !isfinite(awaw)) return stop(S, ST_NAN);
-        if (awaw == 0.0) return stop(S, ST_BREAKDOWN);
-        const double2 chi = make_double2(aww.x / awaw, aww.y / awaw);
+        double2 chi;
+        const int st = calc_chi(tot, chi);
+        if (st != ST_RUNNING) return stop(S, st);
         S->chi = chi;
     } else if constexpr (FIN == FIN_ALPHA) {
-        const double2 d1 = make_double2(tot[0], tot[1]);
-        const double rr = tot[2];
-        S->iter += 1;
-        S->rr = rr;
-        const double2 alpha = c_neg(c_div(c_mul(S->beta, d1), c_mul(S->delta, S->chi)));
-        int pend = ST_RUNNING;
-        if (!isfinite(rr) || !c_finite(d1)) pend = ST_NAN;
-        else if (rr <= S->target2) pend = ST_CONVERGED;
-        else if (S->mixed && rr < S->delta_rel2 * S->maxrr) pend = ST_RELIABLE;
-        else if (S->iter >= S->maxit) pend = ST_MAXIT;
-        else if (c_abs2(d1) == 0.0) pend = ST_BREAKDOWN;
-        // The s update of this iteration is gated off for a system that stops; a solver that
-        // continues from s (reliable update) applies it before the update.
-        S->status = pend;
-        if (!S->dc && rr > S->maxrr) S->maxrr = rr;
-        if (ShiftBlock* B = S->blk) {
-            IterScal& q = B->it[B->count];
-            q.beta = S->beta;
-            q.chi = S->chi;
-            q.alpha = alpha;
-            q.rr = rr;
-            B->count += 1;
-        }
-        S->alpha = alpha;
-        S->delta = d1;
-        report(S);
+        double2 alpha;
+        const int iter = S->iter + 1, st = calc_alpha(S, S->delta, iter, tot, alpha);
+        store_alpha(S, iter, tot, alpha, st);
     } else if constexpr (FIN == FIN_RESTART) {
         S->delta = make_double2(tot[0], tot[1]);
         S->rr = tot[2];
@@ -175,11 +202,38 @@ __global__ __launch_bounds__(BLOCK) void k_finish(const FinJob* __restrict__ fin
     if (threadIdx.x == 0) finish<FIN>(S, tot);
 }
 
+// Sum of a system's partial sums in every thread of the block, in the order of k_finish.
+template <int NR>
+__device__ __forceinline__ void sum_partials(const double* __restrict__ partials, int n, double tot[NRED])
+{
+    __shared__ double lds[NR * (BLOCK / 64)];
+    double v[NR];
+#pragma unroll
+    for (int k = 0; k < NR; k++) v[k] = 0.0;
+    for (int i = threadIdx.x; i < n; i += BLOCK)
+#pragma unroll
+        for (int k = 0; k < NR; k++) v[k] += partials[(long)i * NRED + k];
+#pragma unroll
+    for (int k = 0; k < NR; k++) {
+        const double s = wave_sum(v[k]);
+        if ((threadIdx.x & 63) == 0) lds[k * (BLOCK / 64) + (threadIdx.x >> 6)] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NR; k++) {
+        double s = 0;
+        for (int w = 0; w < BLOCK / 64; w++) s += lds[k * (BLOCK / 64) + w];
+        tot[k] = s;
+    }
+}
+
 // ================================================================ sweeps
 
 template <class T> __device__ __forceinline__ cx<T> cvt(double2 a) { return mk<T>((T)a.x, (T)a.y); }
 
-template <int OP, int SFL>
+// FOLD (OP_W, OP_XR, OP_S): the finisher of the preceding reduction is done here, by every block for
+// itself; block 0 stores its results.
+template <int OP, int SFL, bool FOLD = false>
 __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jobs, int njobs,
                                                  SysState* __restrict__ sys, int gated, int* exec)
 {
@@ -202,23 +256,57 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
 
     if constexpr (OP == OP_W) {
         // w = r + beta A s
+        cx<T> r[12], as[12];
         if (ok) {
-            const cx<T> beta = cvt<T>(S->beta);
-            cx<T> r[12], as[12];
             load_spinor<SFL, T, true>(J.f[R_F1], i, r);
             load_spinor<SFL, T, true>(J.f[R_F2], i, as);
+        }
+        double2 beta_d;
+        if constexpr (FOLD) {
+            double tot[NRED];
+            sum_partials<2>(S->partials, J.rnblk, tot);
+            const int st = calc_beta(S->delta, tot, beta_d);
+            if (lb == 0 && threadIdx.x == 0) {
+                if (st != ST_RUNNING) stop(S, st);
+                else {
+                    S->beta = beta_d;
+                    S->delta_w = S->delta;
+                    S->iter_w = S->iter;
+                }
+            }
+            if (st != ST_RUNNING) return;
+        } else {
+            beta_d = S->beta;
+        }
+        if (ok) {
+            const cx<T> beta = cvt<T>(beta_d);
 #pragma unroll
             for (int k = 0; k < 12; k++) r[k] = r[k] + beta * as[k];
             store_spinor<SFL, T, NTS>(J.f[R_F0], i, r);
         }
     } else if constexpr (OP == OP_XR) {
         // x <- x - beta s + chi w ; r_{n+1} = w - chi A w ; <rhat, r_{n+1}>, |r_{n+1}|^2
+        cx<T> x[12], s[12], w[12];
         if (ok) {
-            const cx<T> beta = cvt<T>(S->beta), chi = cvt<T>(S->chi);
-            cx<T> x[12], s[12], w[12];
             load_spinor<SFX, T, true>(J.f[R_F0], i, x);
             load_spinor<SFL, T, true>(J.f[R_F2], i, s);
             load_spinor<SFL, T, true>(J.f[R_F3], i, w);
+        }
+        double2 chi_d;
+        if constexpr (FOLD) {
+            double tot[NRED];
+            sum_partials<3>(S->partials2, J.rnblk, tot);
+            const int st = calc_chi(tot, chi_d);
+            if (lb == 0 && threadIdx.x == 0) {
+                if (st != ST_RUNNING) stop(S, st);
+                else S->chi = chi_d;
+            }
+            if (st != ST_RUNNING) return;
+        } else {
+            chi_d = S->chi;
+        }
+        if (ok) {
+            const cx<T> beta = cvt<T>(S->beta), chi = cvt<T>(chi_d);
 #pragma unroll
             for (int k = 0; k < 12; k++) x[k] = x[k] - beta * s[k] + chi * w[k];
             store_spinor<SFX, T, NTS>(J.f[R_F0], i, x);
@@ -239,12 +327,25 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         write_partials<3>(v, S, J.rblk0 + lb);
     } else if constexpr (OP == OP_S) {
         // s <- r_{n+1} + alpha (s - chi A s)
+        cx<T> r[12], s[12], as[12];
         if (ok) {
-            const cx<T> alpha = cvt<T>(S->alpha), chi = cvt<T>(S->chi);
-            cx<T> r[12], s[12], as[12];
             load_spinor<SFL, T, true>(J.f[R_F3], i, r);
             load_spinor<SFL, T, true>(J.f[R_F0], i, s);
             load_spinor<SFL, T, true>(J.f[R_F2], i, as);
+        }
+        double2 alpha_d;
+        if constexpr (FOLD) {
+            // delta, iter: this launch changes them, so the blocks take the copies that OP_W left
+            double tot[NRED];
+            sum_partials<3>(S->partials, J.rnblk, tot);
+            const int iter = S->iter_w + 1, st = calc_alpha(S, S->delta_w, iter, tot, alpha_d);
+            if (lb == 0 && threadIdx.x == 0) store_alpha(S, iter, tot, alpha_d, st);
+            if (st != ST_RUNNING) return;
+        } else {
+            alpha_d = S->alpha;
+        }
+        if (ok) {
+            const cx<T> alpha = cvt<T>(alpha_d), chi = cvt<T>(S->chi);
 #pragma unroll
             for (int k = 0; k < 12; k++) s[k] = r[k] + alpha * (s[k] - chi * as[k]);
             store_spinor<SFL, T, NTS>(J.f[R_F0], i, s);
@@ -987,6 +1088,12 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     return hipErrorInvalidValue;
 }
 
+#define SWEEP_FOLD(OP_, SF_)                                                                                       \
+    if (fold && op == OP_ && sfl == SF_) {                                                                         \
+        hipExtLaunchKernelGGL((k_sweep<OP_, SF_, true>), grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, \
+                              sys, gated, exec);                                                                   \
+        return hipGetLastError();                                                                                  \
+    }
 #define SWEEP_CASE(OP_, SF_)                                                                                       \
     if (op == OP_ && sfl == SF_) {                                                                                 \
         hipExtLaunchKernelGGL((k_sweep<OP_, SF_>), grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, sys, \
@@ -999,9 +1106,13 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     SWEEP_CASE(OP_CGX, SF_) SWEEP_CASE(OP_CGP, SF_)
 
 hipError_t launch_sweep(int op, int sfl, const SweepJob* jobs, int njobs, long nblocks, SysState* sys, int gated,
-                        hipStream_t s, int* exec, hipEvent_t ev0, hipEvent_t ev1)
+                        hipStream_t s, int* exec, hipEvent_t ev0, hipEvent_t ev1, bool fold)
 {
     if (nblocks <= 0) return hipSuccess;
+    SWEEP_FOLD(OP_W, SF64) SWEEP_FOLD(OP_XR, SF64) SWEEP_FOLD(OP_S, SF64)
+    SWEEP_FOLD(OP_W, SF32) SWEEP_FOLD(OP_XR, SF32) SWEEP_FOLD(OP_S, SF32)
+    SWEEP_FOLD(OP_W, SF16) SWEEP_FOLD(OP_XR, SF16) SWEEP_FOLD(OP_S, SF16)
+    if (fold) return hipErrorInvalidValue;
     SWEEP_ALL(SF64)
     SWEEP_ALL(SF32)
     SWEEP_ALL(SF16)

@@ -41,7 +41,8 @@ int hop_stage64_default();
 hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState* sys, int gated, hipStream_t s,
                          hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_sweep(int op, int sfl, const SweepJob* jobs, int njobs, long nblocks, SysState* sys, int gated,
-                        hipStream_t s, int* exec = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                        hipStream_t s, int* exec = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                        bool fold = false);
 // gm (may be NULL): canonical [V][3][3] colour rotation g(n): pack stores g(n) psi(n), unpack
 // returns g(n)^dag psi'(n). nc: the internal field is in the non-chiral spin basis (pack rotates
 // into it after gamma5 and g(n), unpack out of it before them)

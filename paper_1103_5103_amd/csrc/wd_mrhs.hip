@@ -162,7 +162,7 @@ __global__ __launch_bounds__(BLOCK) void k_hop_mrhs(const HopJob* __restrict__ j
         // block-uniform conditions: every thread of the block takes the same branches
 #pragma unroll
         for (int k = 0; k < KT; k++)
-            if (run[k]) write_partials<3>(v[k], sys + jobs[j0 + k].sys, jobs[j0 + k].rblk0 + lb);
+            if (run[k]) write_partials<3>(v[k], sys + jobs[j0 + k].sys, jobs[j0 + k].rblk0 + lb, jobs[j0 + k].p2 != 0);
     }
 }
 

@@ -331,7 +331,7 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     }
     if (timed)
         T.pending.push_back({cls, a, b, bytes, (int)(flag - T.dflags), t.n(), cls == TK_HOP_LO ? TK_HOP_LO_RED + red : -1});
-    if (red != RED_NONE) run_finish(3, fin, t, sys, gated, s);
+    if (red != RED_NONE && fin != FIN_NONE) run_finish(3, fin, t, sys, gated, s);
 }
 
 void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s)
@@ -364,7 +364,8 @@ static unsigned sweep_roles(int op)
     }
 }
 
-void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s, double bytes)
+void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s, double bytes,
+               bool fold)
 {
     const unsigned need = sweep_roles(op);
     for (const SweepJob& j : t.host)
@@ -379,8 +380,9 @@ void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int 
         a = T.get();
         b = T.get();
     }
-    WD_CHECK_HIP(launch_sweep(op, sfl, t.d(), t.n(), t.nblocks, sys, gated, s, flag, a, b));
+    WD_CHECK_HIP(launch_sweep(op, sfl, t.d(), t.n(), t.nblocks, sys, gated, s, flag, a, b, fold));
     if (timed) T.pending.push_back({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
+    if (fold) return;
     switch (op) {
     case OP_XR: run_finish(3, FIN_ALPHA, t, sys, gated, s); break;
     case OP_INIT:

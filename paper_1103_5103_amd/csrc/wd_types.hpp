@@ -31,6 +31,11 @@ enum SysStatus {
     ST_NOCONV = 9,      // finished: iteration cap
     ST_BROKEN = 10,     // finished: broke down again after its restarts
 };
+// Finishers of small launches are folded into the sweep that follows: every block of the sweep adds the
+// partial sums and computes the scalars itself, block 0 stores them (FIN_NONE: no finisher launch).
+// The sweep after a hop writes its own partial sums while it reads the hop's, so the two hops of an
+// iteration use one set each; what a block reads is never written by the same launch.
+constexpr int FIN_NONE = -1;
 // Kernel gates are masks of the statuses allowed to run (0: no gating); GATE_RUN = the iteration.
 constexpr int GATE_RUN = 1 << ST_RUNNING;
 constexpr int GATE_STOPPED = (1 << ST_CONVERGED) | (1 << ST_RELIABLE) | (1 << ST_BREAKDOWN) | (1 << ST_MAXIT);
@@ -113,6 +118,8 @@ struct SysState {
     int dc;            // defect correction: the reliable-update threshold is relative to the
                        // residual at the start of the inner solve (maxrr is not raised)
     double2 delta, beta, chi, alpha;
+    double2 delta_w;   // folded finishers: delta and iter as they were when w was formed
+    int iter_w, pad2;
     double rr;         // |r|^2 of the iterated residual
     double maxrr;      // max |r|^2 since the last reliable update
     double rr_true;    // |r|^2 of the last FP64 residual update
@@ -121,6 +128,7 @@ struct SysState {
     double cga, cgb;   // CG: alpha_n, beta_n
     double red[NRED];  // last reduced sums
     double* partials;  // [max blocks][NRED]
+    double* partials2; // a second set, for the second hop of an iteration with folded finishers
     ShiftBlock* blk;   // multi-shift solves: where the iteration leaves its scalars (else NULL)
 };
 
@@ -161,6 +169,7 @@ struct HopJob {
     // site applies the hop to all ilv (<= rhs) systems of the group, loading each link once; the
     // group then spans nblk blocks rather than ilv * nblk. Every job of a launch has the same mode.
     int rhs;
+    int p2;              // partial sums go to the system's second set
     int nc;              // spinors in the non-chiral basis (gamma_4 diagonal): time hops read and
                          // update two spin components (hop_t_nc)
 };
