@@ -3,6 +3,8 @@
 // dispatch macros of its launchers. Instantiated in wd_hop_lo.hip (FP32 / FP16 spinors) and
 // wd_hop64.hip (FP64).
 #pragma once
+#include <type_traits>
+
 #include "wd_kernels.hpp"
 
 namespace wd {
@@ -239,9 +241,10 @@ __device__ __forceinline__ void group_barrier(cx<T> acc[12], int& dep)
 // Both directions of axis MU; the two links are loaded together (one 16-byte load per chunk for
 // the paired 16-bit formats). G = directions per ordering group. NTL: non-temporal link loads.
 // FULL: the backward link is formed from the neighbour's forward link instead of its stored copy.
+// acc takes the forward, accb (usually the same) the backward direction.
 template <int MU, int G, bool DAG, int SFI, int LF, bool STG, bool NTL, bool FULL, class T>
 __device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int z, int t, const HopIn<SFI, STG>& in,
-                                         const void* links, long lcs, cx<T> acc[12], int& dep)
+                                         const void* links, long lcs, cx<T> acc[12], cx<T> accb[12], int& dep)
 {
     cx<T> Wf[9], Wb[9];
     // temporal gauge: U_t(n) is the unit matrix unless t = T - 1, U_t(n - t)^dag unless t = 0
@@ -263,13 +266,13 @@ __device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int
     if (MU == 3 && in.nc) {
         hop_t_nc<0, DAG, SFI, T>(g, cb, x, y, z, t, in.in, Wf, acc, dep, unit_f);
         group_barrier<2 * MU, G>(acc, dep);
-        hop_t_nc<1, DAG, SFI, T>(g, cb, x, y, z, t, in.in, Wb, acc, dep, unit_b);
+        hop_t_nc<1, DAG, SFI, T>(g, cb, x, y, z, t, in.in, Wb, accb, dep, unit_b);
         group_barrier<2 * MU + 1, G>(acc, dep);
         return;
     }
     hop_dir<MU, 0, DAG, SFI, STG, T>(g, cb, x, y, z, t, in, Wf, acc, dep, unit_f);
     group_barrier<2 * MU, G>(acc, dep);
-    hop_dir<MU, 1, DAG, SFI, STG, T>(g, cb, x, y, z, t, in, Wb, acc, dep, unit_b);
+    hop_dir<MU, 1, DAG, SFI, STG, T>(g, cb, x, y, z, t, in, Wb, accb, dep, unit_b);
     group_barrier<2 * MU + 1, G>(acc, dep);
 }
 
@@ -283,10 +286,10 @@ __device__ __forceinline__ void hop_site(const Geo& g, int p, int cb, const HopI
 #pragma unroll
     for (int k = 0; k < 12; k++) acc[k] = mk<T>(T(0), T(0));
     int dep = 0;
-    hop_axis<0, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, dep);
-    hop_axis<1, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, dep);
-    hop_axis<2, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, dep);
-    hop_axis<3, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, dep);
+    hop_axis<0, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, acc, dep);
+    hop_axis<1, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, acc, dep);
+    hop_axis<2, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, acc, dep);
+    hop_axis<3, G, DAG, SFI, LF, STG, NTL, FULL, T>(g, cb, x, y, z, t, in, links, lcs, acc, acc, dep);
 }
 
 // Job-local block order. With tb > 0 the blocks walk t fastest inside groups of tb blocks of a
@@ -394,6 +397,129 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
     if constexpr (RED != RED_NONE) write_partials<3>(v, S, J.rblk0 + lb, J.p2 != 0);
 }
 
+// The hop for launches that leave the chip mostly idle (up to kSplitSites sites, one system): such a
+// launch takes as long as one wave's chain of memory round trips and arithmetic, so the chain is cut.
+// A block covers SPLIT_SITES sites with five waves: waves 0..3 do one axis each (both directions, all
+// their loads at once, no LDS window), wave 4 loads the epilogue's fields meanwhile, adds the partial
+// results in LDS and finishes. Sites per block SPLIT_SITES instead of BLOCK also spread a small
+// lattice over four times as many CUs.
+constexpr int SPLIT_SITES = 64;
+constexpr int SPLIT_THREADS = 5 * 64;
+template <int SF, int LF, bool DAG, int RED, bool TG>
+__global__ __launch_bounds__(SPLIT_THREADS) void k_hop_split(const HopJob* __restrict__ jobs, int njobs,
+                                                             SysState* __restrict__ sys, int gated, int* exec)
+{
+    using T = typename SReal<SF>::T;
+    using V = typename std::conditional<SF == SF64, d2v, f4v>::type;
+    constexpr int NC = SF == SF64 ? 12 : 6;      // 16-byte pieces of an accumulator
+    constexpr int PC = SF == SF64 ? 1 : 2;       // complex numbers per piece
+    // the x axis' sum, then each direction of y, z and t: added in the order of k_hop, so that the result
+    // is the same to the last bit (FP16 spinors: up to the rounding of their scale)
+    __shared__ V part[7][NC][SPLIT_SITES];
+    const int b = (int)blockIdx.x;
+    const HopJob& J = jobs[find_job(jobs, njobs, b)];
+    SysState* S = sys + J.sys;
+    if (gated && !((gated >> S->status) & 1)) return;  // gated: mask of the statuses that run
+    const int lb = b - J.blk0;
+    if (exec && lb == 0 && threadIdx.x == 0) atomicAdd(exec, 1);  // timing: jobs that did work
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+    const int cb = lb * SPLIT_SITES + lane;
+    const bool ok = cb < J.g.Vh;
+    if (wave < 4) {
+        cx<T> acc[2][12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[0][k] = acc[1][k] = mk<T>(T(0), T(0));
+        if (ok) {
+            const Stg<SF, false> none{};
+            const HopIn<SF, false> hin{J.in, none, 0, 0, TG && J.tg != 0, J.nc != 0};
+            int x, y, z, t, dep = 0;
+            cb_coords(J.g, J.parity, cb, x, y, z, t);
+            if (wave == 0) hop_axis<0, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+            else if (wave == 1) hop_axis<1, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+            else if (wave == 2) hop_axis<2, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+            else hop_axis<3, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+        }
+        if (wave == 0)
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc[0][k] = acc[0][k] + acc[1][k];
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            if (d == 1 && wave == 0) break;
+#pragma unroll
+            for (int j = 0; j < NC; j++) {
+                V q;
+#pragma unroll
+                for (int c = 0; c < PC; c++) {
+                    q[2 * c] = acc[d][j * PC + c].re;
+                    q[2 * c + 1] = acc[d][j * PC + c].im;
+                }
+                part[wave == 0 ? 0 : 2 * wave - 1 + d][j][lane] = q;
+            }
+        }
+        __syncthreads();
+        return;
+    }
+    cx<T> x0[12], x1[12], z[12];
+    const bool has0 = J.x0.p != nullptr, has1 = J.x1.p != nullptr;
+    if (ok) {
+        if (has0) load_spinor<SF, T>(J.x0, cb, x0);
+        if (has1) load_spinor<SF, T>(J.x1, cb, x1);
+        if constexpr (RED == RED_ZDOT) load_spinor<SF, T>(J.z, cb, z);
+    }
+    __syncthreads();
+    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    if (ok) {
+        cx<T> acc[12];
+#pragma unroll
+        for (int j = 0; j < NC; j++) {
+            V q = part[0][j][lane];
+#pragma unroll
+            for (int d = 1; d < 7; d++) q = q + part[d][j][lane];
+#pragma unroll
+            for (int k = 0; k < PC; k++) acc[j * PC + k] = mk<T>(q[2 * k], q[2 * k + 1]);
+        }
+        const T c2 = (T)J.c2;
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[k] = c2 * acc[k];
+        if (has0) {
+            const T c0 = (T)J.c0;
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc[k] = acc[k] + c0 * x0[k];
+        }
+        if (has1) {
+            const T c1 = (T)J.c1;
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc[k] = acc[k] + c1 * x1[k];
+        }
+        store_spinor<SF, T>(J.out, cb, acc);
+        if constexpr (RED == RED_ZDOT) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                v[0] += (double)z[k].re * acc[k].re + (double)z[k].im * acc[k].im;
+                v[1] += (double)z[k].re * acc[k].im - (double)z[k].im * acc[k].re;
+            }
+        } else if constexpr (RED == RED_OUTX) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                v[0] += (double)acc[k].re * x0[k].re + (double)acc[k].im * x0[k].im;
+                v[1] += (double)acc[k].re * x0[k].im - (double)acc[k].im * x0[k].re;
+                v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
+            }
+        } else if constexpr (RED == RED_NORM) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
+        }
+    }
+    if constexpr (RED != RED_NONE) {
+        double* P = (J.p2 ? S->partials2 : S->partials) + (long)(J.rblk0 + lb) * NRED;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const double s = wave_sum(v[k]);
+            if (lane == 0) P[k] = s;
+        }
+    }
+}
+
 // ================================================================ launch dispatch
 
 static inline dim3 grid1(long nblk) { return dim3((unsigned)nblk); }
@@ -426,3 +552,4 @@ static inline dim3 grid1(long nblk) { return dim3((unsigned)nblk); }
 #define HOP_DAG_64(LF_) HOP_DAG_LO(SF64, LF_) HOP_CASE(SF64, LF_, true, RED_NORM, FIN_STORE)
 
 } // namespace wd
+

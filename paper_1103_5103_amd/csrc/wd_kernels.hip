@@ -264,7 +264,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         double2 beta_d;
         if constexpr (FOLD) {
             double tot[NRED];
-            sum_partials<2>(S->partials, J.rnblk, tot);
+            sum_partials<2>(S->partials, J.pnblk, tot);
             const int st = calc_beta(S->delta, tot, beta_d);
             if (lb == 0 && threadIdx.x == 0) {
                 if (st != ST_RUNNING) stop(S, st);
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         double2 chi_d;
         if constexpr (FOLD) {
             double tot[NRED];
-            sum_partials<3>(S->partials2, J.rnblk, tot);
+            sum_partials<3>(S->partials2, J.pnblk, tot);
             const int st = calc_chi(tot, chi_d);
             if (lb == 0 && threadIdx.x == 0) {
                 if (st != ST_RUNNING) stop(S, st);

@@ -30,6 +30,12 @@ void full_tile(HopJob& j);
 hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
                            int gated, hipStream_t s, int* exec = nullptr, int tg = 0, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
+// The hop for small launches (tables whose jobs have split set): all formats, the reductions and
+// adjoint variants of launch_hop. split_blocks: its blocks (and partial sums) per job.
+int split_blocks(int Vh);
+hipError_t launch_hop_split(int sf, int lf, bool dag, int red, const HopJob* jobs, int njobs, long nblocks,
+                            SysState* sys, int gated, hipStream_t s, int* exec = nullptr, int tg = 0,
+                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Multi-RHS hop (tables whose jobs have rhs >= 2): kt = mrhs_kt(largest group), 2 or 4 systems per
 // thread at most (0: unsupported group size). Low-precision spinors only.
 int mrhs_kt(int k);

@@ -318,7 +318,9 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     }
     if (link_bytes <= 64.0 * (1 << 20)) ntl = 0;
     if (ntl_force >= 0) ntl = ntl_force != 0;
-    if (!t.host.empty() && t.host[0].links_nb) {
+    if (!t.host.empty() && t.host[0].split) {
+        WD_CHECK_HIP(launch_hop_split(sf, lf, dag, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));
+    } else if (!t.host.empty() && t.host[0].links_nb) {
         WD_CHECK_HIP(launch_hop_full(dag, lf, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));
     } else if (!t.host.empty() && t.host[0].rhs >= 2) {
         int kmax = 1;

@@ -132,6 +132,24 @@ struct SysArray {
 
 static inline int nblk(long n) { return (int)((n + BLOCK - 1) / BLOCK); }
 
+// Hops of one system on at most this many sites per launch take the variant for small launches
+// (k_hop_split): up to one of its blocks per CU. Measured with it / with k_hop: one mass on 8^4 (2048 sites
+// per launch) 785 / 925 us, FP64 on 10x6x14x18 (7560) 580 / 665 us, 12^4 (10368, FP16 spinors) 865 / 1057
+// us; 16^4 (32768) 1233 / 1195 us, FP64 994 / 867 us; 16^3x32 (65536) six masses 5.08 / 4.09 ms.
+constexpr long kSplitSites = 16384;
+static void set_split(JobTable<HopJob>& t)
+{
+    long sites = 0;
+    for (const HopJob& j : t.host) sites += j.g.Vh;
+    if (sites > kSplitSites) return;
+    for (HopJob& j : t.host) {
+        j.split = 1;
+        j.nblk = split_blocks(j.g.Vh);
+        j.tb = j.rhs = 0;
+        j.links_nb = nullptr;
+    }
+}
+
 // ---------------------------------------------------------------- hop autotuner
 // For the hops of one handle in a launch in which nshared systems read its links, the tuner picks
 // the block order (site order, tz = 0, or t fastest within groups of tz z-planes) and the way the
@@ -359,7 +377,7 @@ static bool same_links(const HopJob& a, const HopJob& b)
 }
 static bool same_links(const SweepJob&, const SweepJob&) { return false; }
 // largest group of jobs sharing links: rhs systems per thread for the multi-RHS hop, else kIlvMax
-static int group_max(const HopJob& j) { return j.rhs >= 2 ? j.rhs : interleave_max(); }
+static int group_max(const HopJob& j) { return j.split ? 1 : j.rhs >= 2 ? j.rhs : interleave_max(); }
 static int group_max(const SweepJob&) { return 1; }
 static int group_blocks(const HopJob& j, int K) { return j.rhs >= 2 ? j.nblk : K * j.nblk; }
 static int group_blocks(const SweepJob& j, int K) { return K * j.nblk; }
@@ -590,7 +608,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         EoSys& e = S[i];
         SysState& q = sys.h[i];
         std::memset(&q, 0, sizeof(q));
-        const size_t np = (size_t)NRED * (2 * e.g->geo.stride / BLOCK + 1);
+        const size_t np = (size_t)NRED * (2 * e.g->geo.stride / 64 + 1);
         q.partials = (double*)e.g->rawbuf("eo" + std::to_string(e.slot) + ".partials", sizeof(double) * 2 * np);
         q.partials2 = q.partials + np;
         q.maxit = P.max_iter;
@@ -710,9 +728,12 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
             j.tg = S[j.sys].g->tg;  // solver links of a temporal-gauge handle
             j.nc = S[j.sys].g->nc;  // and the handle's spin basis
         }
+        if (n == 1) set_split(*t);
         group_by_links(*t);
         layout(*t);
     }
+    for (auto& j : SW.host) j.pnblk = H2.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
+    for (auto& j : SXR.host) j.pnblk = H4.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
     for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &Acc, &SW, &SXR, &SS}) layout(*t);
     const bool fold = fold_finishers(SW);
     for (auto& j : H4.host) j.p2 = fold;
@@ -1094,7 +1115,7 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     sys.alloc(1, g->raw["ms.sys"]);
     SysState& q = sys.h[0];
     std::memset(&q, 0, sizeof(q));
-    const size_t np = (size_t)NRED * (2 * geo.stride / BLOCK + 1);
+    const size_t np = (size_t)NRED * (2 * geo.stride / 64 + 1);
     q.partials = (double*)g->rawbuf("ms.partials", sizeof(double) * 2 * np);
     q.partials2 = q.partials + np;
     q.maxit = P.max_iter;
@@ -1164,6 +1185,9 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
             j.f[R_F3] = R1.all();
             S.SEND.host.push_back(j);
             for (int p = 0; p < 2; p++) S.HAw.host.push_back(hop(W, AW, p, nullptr));
+            set_split(S.HAw);
+            const int pn = 2 * (S.HAw.host[0].split ? split_blocks(geo.Vh) : nblk(geo.Vh));
+            S.SW.host[0].pnblk = S.SXR.host[0].pnblk = pn;
             for (auto* t : {&S.SW, &S.SXR, &S.SEND}) layout(*t);
             layout(S.HAw);
             for (JobTableBase* t : {(JobTableBase*)&S.SW, (JobTableBase*)&S.SXR, (JobTableBase*)&S.SEND, (JobTableBase*)&S.HAw})
@@ -1171,6 +1195,7 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
         }
     }
     layout(Init);
+    set_split(HAs);
     layout(HAs);
     const bool fold = fold_finishers(Init);
     for (auto& v : steps)
@@ -1239,7 +1264,7 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     // true residual of every mass in one launch (one reduction group per mass; the residual
     // fields are not kept, only their norms), then unpack
     {
-        const size_t pstride = (size_t)NRED * (2 * geo.stride / BLOCK + 1);
+        const size_t pstride = (size_t)NRED * (2 * geo.stride / 64 + 1);
         SysArray rs;
         rs.alloc(nk, g->raw["ms.rsys"]);
         double* rpart = (double*)g->rawbuf("ms.rpartials", sizeof(double) * pstride * nk);
@@ -1391,7 +1416,7 @@ wd_status apply_prec(wd_gauge* g, double kappa, double* out, const double* in, c
     }
     SysArray sys;
     sys.alloc(K, g->raw["ap.sys"]);
-    const size_t pstride = (size_t)NRED * (2 * G.stride / BLOCK + 1);
+    const size_t pstride = (size_t)NRED * (2 * G.stride / 64 + 1);
     double* part = (double*)g->rawbuf("ap.partials", sizeof(double) * pstride * K);
     for (int k = 0; k < K; k++) {
         std::memset(&sys.h[k], 0, sizeof(SysState));
@@ -1422,6 +1447,10 @@ wd_status apply_prec(wd_gauge* g, double kappa, double* out, const double* in, c
         j.z = F[k].half(0);
         set_tile(j, tz);
         H2.host.push_back(j);
+    }
+    if (K == 1 && v.stage < 0 && v.nontemporal < 0 && v.tile < 0 && v.rhs_per_thread < 0) {  // as the solvers
+        set_split(H1);
+        set_split(H2);
     }
     layout(H1);
     layout(H2);
@@ -1819,7 +1848,7 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         SysState& q = sys.h[i];
         std::memset(&q, 0, sizeof(q));
         q.partials = (double*)e.g->rawbuf("cg" + std::to_string(e.slot) + ".partials",
-                                          sizeof(double) * NRED * (2 * e.g->geo.stride / BLOCK + 1));
+                                          sizeof(double) * NRED * (2 * e.g->geo.stride / 64 + 1));
         q.maxit = P.max_iter;
         q.mixed = P.mixed;
         q.delta_rel2 = P.delta_reliable * P.delta_reliable;
@@ -1929,6 +1958,7 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         for (auto& j : t->host) j.tg = S[j.sys].g->tg;
     for (auto* t : {&Hx1, &Hx2, &Hx3, &Hx4, &H1, &H2, &H3, &H4}) {
         for (auto& j : t->host) j.nc = S[j.sys].g->nc;  // every hop works in the handle's spin basis
+        if (n == 1) set_split(*t);
         group_by_links(*t);
         layout(*t);
     }
@@ -2151,7 +2181,7 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
     sys.alloc(1, g->raw["cgm.sys"]);
     SysState& q = sys.h[0];
     std::memset(&q, 0, sizeof(q));
-    q.partials = (double*)g->rawbuf("cgm.partials", sizeof(double) * NRED * (2 * geo.stride / BLOCK + 1));
+    q.partials = (double*)g->rawbuf("cgm.partials", sizeof(double) * NRED * (2 * geo.stride / 64 + 1));
     q.maxit = P.max_iter;
     q.target2 = -1;
     q.blk = shf.d_blk;
@@ -2221,6 +2251,7 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
             set_tile(h, tz64);
             h.nc = g->nc;  // the adjoint hops too work in the handle's spin basis
         }
+        set_split(*t);
         layout(*t);
     }
     std::vector<JobTableBase*> tabs{&Init, &H1, &H2, &H3, &H4};

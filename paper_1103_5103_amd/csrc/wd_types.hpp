@@ -169,6 +169,7 @@ struct HopJob {
     // site applies the hop to all ilv (<= rhs) systems of the group, loading each link once; the
     // group then spans nblk blocks rather than ilv * nblk. Every job of a launch has the same mode.
     int rhs;
+    int split;           // run by the hop for small launches (blocks of SPLIT_SITES sites)
     int p2;              // partial sums go to the system's second set
     int nc;              // spinors in the non-chiral basis (gamma_4 diagonal): time hops read and
                          // update two spin components (hop_t_nc)
@@ -185,7 +186,7 @@ struct SweepJob {
     int rblk0;
     int rnblk;
     int flags;   // op-specific
-    int pad;
+    int pnblk;   // folded finishers: partial sums that the hop before this sweep left
     double c[8]; // op-specific coefficients
     SpinorRef f[NROLE];
 };
