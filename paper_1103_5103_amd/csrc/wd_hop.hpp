@@ -3,8 +3,6 @@
 // dispatch macros of its launchers. Instantiated in wd_hop_lo.hip (FP32 / FP16 spinors) and
 // wd_hop64.hip (FP64).
 #pragma once
-#include <type_traits>
-
 #include "wd_kernels.hpp"
 
 namespace wd {
@@ -60,7 +58,9 @@ template <> struct Proj<3> { static constexpr int E = 0, F = 0, I1 = 1, I2 = 0; 
 
 // Where a hop reads its input sites: memory, or (STG) an LDS copy of the window [base, base + nsl)
 // of input sites for the x and y directions.
-template <int SF, bool STG>
+// SFA >= 0: the input is the sum of `in` and a second field in storage format SFA (x_hi + x_lo of a
+// residual update), formed where it is loaded (the LDS copy holds the sums).
+template <int SF, bool STG, int SFA = -1>
 struct HopIn {
     const SpinorRef& in;
     const Stg<SF, STG>& L;
@@ -68,10 +68,25 @@ struct HopIn {
     bool tg;  // temporal gauge: unit time links inside the lattice
     bool nc;  // spinors in the non-chiral basis (the time hop of hop_t_nc)
     const void* links_nb = nullptr;  // FULL: the links of the input's parity
+    const SpinorRef* add = nullptr;  // SFA: the second field (NULL: it is zero)
 };
 
-template <int MU, int D, bool DAG, int SFI, bool STG, class T>
-__device__ __forceinline__ void hop_dir(const Geo& g, int cb, int x, int y, int z, int t, const HopIn<SFI, STG>& in,
+template <int SF, int SFA, class T>
+__device__ __forceinline__ void load_spinor_sum(const SpinorRef& r, const SpinorRef* add, long i, cx<T> v[12])
+{
+    load_spinor<SF, T>(r, i, v);
+    if constexpr (SFA >= 0) {
+        if (add) {
+            cx<typename SReal<SFA>::T> l[12];
+            load_spinor<SFA, typename SReal<SFA>::T>(*add, i, l);
+#pragma unroll
+            for (int k = 0; k < 12; k++) v[k] = v[k] + mk<T>((T)l[k].re, (T)l[k].im);
+        }
+    }
+}
+
+template <int MU, int D, bool DAG, int SFI, bool STG, class T, int SFA>
+__device__ __forceinline__ void hop_dir(const Geo& g, int cb, int x, int y, int z, int t, const HopIn<SFI, STG, SFA>& in,
                                         const cx<T> W[9], cx<T> acc[12], int dep, bool unit)
 {
     const int nb = nb_from_cb<MU, D>(g, cb, x, y, z, t) + dep;
@@ -89,9 +104,9 @@ __device__ __forceinline__ void hop_dir(const Geo& g, int cb, int x, int y, int 
     } else if constexpr (STG && MU < 2) {
         const int k = nb - in.base;
         if ((unsigned)k < (unsigned)in.nsl) load_spinor_stg<SFI, T>(in.L, k, psi);
-        else load_spinor<SFI, T>(in.in, nb, psi);
+        else load_spinor_sum<SFI, SFA, T>(in.in, in.add, nb, psi);
     } else {
-        load_spinor<SFI, T>(in.in, nb, psi);
+        load_spinor_sum<SFI, SFA, T>(in.in, in.add, nb, psi);
     }
     constexpr bool minus = (D == 0) != DAG;  // projector 1 - gamma
     constexpr int E = Proj<MU>::E + (minus ? 0 : 2);
@@ -188,15 +203,26 @@ __device__ __forceinline__ T load_spin_pair(const SpinorRef& r, long i, cx<T> h[
 // spin components (S0 = 2 for the projector 1 - gamma_4, 0 for 1 + gamma_4), multiplies them by the
 // link and adds twice the product to the same two components of the output: no projection sums,
 // half the expansion, half the neighbour bytes of the chiral time hop.
-template <int D, bool DAG, int SFI, class T>
+template <int D, bool DAG, int SFI, class T, int SFA = -1>
 __device__ __forceinline__ void hop_t_nc(const Geo& g, int cb, int x, int y, int z, int t, const SpinorRef& in,
-                                         const cx<T> W[9], cx<T> acc[12], int dep, bool unit)
+                                         const cx<T> W[9], cx<T> acc[12], int dep, bool unit,
+                                         const SpinorRef* add = nullptr)
 {
     constexpr bool minus = (D == 0) != DAG;  // projector 1 - gamma_4
     constexpr int S0 = minus ? 2 : 0;
     const int nb = nb_from_cb<3, D>(g, cb, x, y, z, t) + dep;
     cx<T> h[2][3];
     const T sc = load_spin_pair<SFI, S0, T>(in, nb, h);
+    if constexpr (SFA >= 0) {
+        if (add) {
+            cx<typename SReal<SFA>::T> l[2][3];
+            (void)load_spin_pair<SFA, S0, typename SReal<SFA>::T>(*add, nb, l);
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) h[a][c] = h[a][c] + mk<T>((T)l[a][c].re, (T)l[a][c].im);
+        }
+    }
     cx<T> gg[2][3];
 #pragma unroll
     for (int a = 0; a < 2; a++)
@@ -242,8 +268,8 @@ __device__ __forceinline__ void group_barrier(cx<T> acc[12], int& dep)
 // the paired 16-bit formats). G = directions per ordering group. NTL: non-temporal link loads.
 // FULL: the backward link is formed from the neighbour's forward link instead of its stored copy.
 // acc takes the forward, accb (usually the same) the backward direction.
-template <int MU, int G, bool DAG, int SFI, int LF, bool STG, bool NTL, bool FULL, class T>
-__device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int z, int t, const HopIn<SFI, STG>& in,
+template <int MU, int G, bool DAG, int SFI, int LF, bool STG, bool NTL, bool FULL, class T, int SFA>
+__device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int z, int t, const HopIn<SFI, STG, SFA>& in,
                                          const void* links, long lcs, cx<T> acc[12], cx<T> accb[12], int& dep)
 {
     cx<T> Wf[9], Wb[9];
@@ -264,9 +290,9 @@ __device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int
         load_link_pair<LF, T, NTL>(links, lcs, MU, cb + dep, Wf, Wb);
     }
     if (MU == 3 && in.nc) {
-        hop_t_nc<0, DAG, SFI, T>(g, cb, x, y, z, t, in.in, Wf, acc, dep, unit_f);
+        hop_t_nc<0, DAG, SFI, T, SFA>(g, cb, x, y, z, t, in.in, Wf, acc, dep, unit_f, in.add);
         group_barrier<2 * MU, G>(acc, dep);
-        hop_t_nc<1, DAG, SFI, T>(g, cb, x, y, z, t, in.in, Wb, accb, dep, unit_b);
+        hop_t_nc<1, DAG, SFI, T, SFA>(g, cb, x, y, z, t, in.in, Wb, accb, dep, unit_b, in.add);
         group_barrier<2 * MU + 1, G>(acc, dep);
         return;
     }
@@ -276,8 +302,8 @@ __device__ __forceinline__ void hop_axis(const Geo& g, int cb, int x, int y, int
     group_barrier<2 * MU + 1, G>(acc, dep);
 }
 
-template <bool DAG, int SFI, int LF, bool STG, bool NTL, bool FULL, class T>
-__device__ __forceinline__ void hop_site(const Geo& g, int p, int cb, const HopIn<SFI, STG>& in, const void* links,
+template <bool DAG, int SFI, int LF, bool STG, bool NTL, bool FULL, class T, int SFA>
+__device__ __forceinline__ void hop_site(const Geo& g, int p, int cb, const HopIn<SFI, STG, SFA>& in, const void* links,
                                          long lcs, cx<T> acc[12])
 {
     constexpr int G = HopGroup<SFI>::G;
@@ -405,17 +431,69 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
 // lattice over four times as many CUs.
 constexpr int SPLIT_SITES = 64;
 constexpr int SPLIT_THREADS = 5 * 64;
+// The partial results in LDS: the x axis' sum, then each direction of y, z and t, added in the order of
+// k_hop, so that the result is the same to the last bit (FP16 spinors: up to the rounding of their scale).
+template <class T> struct SplitPart;  // 16-byte pieces of an accumulator
+template <> struct SplitPart<float> { using V = f4v; static constexpr int NC = 6, PC = 2; };
+template <> struct SplitPart<double> { using V = d2v; static constexpr int NC = 12, PC = 1; };
+
+// waves 0..3: both directions of one axis
+template <bool DAG, int LF, class T, int SF, int SFA>
+__device__ __forceinline__ void split_part(const HopJob& J, const HopIn<SF, false, SFA>& hin, int wave, int lane, int cb,
+                                           bool ok, typename SplitPart<T>::V (*part)[SplitPart<T>::NC][SPLIT_SITES])
+{
+    using V = typename SplitPart<T>::V;
+    constexpr int NC = SplitPart<T>::NC, PC = SplitPart<T>::PC;
+    cx<T> acc[2][12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) acc[0][k] = acc[1][k] = mk<T>(T(0), T(0));
+    if (ok) {
+        int x, y, z, t, dep = 0;
+        cb_coords(J.g, J.parity, cb, x, y, z, t);
+        if (wave == 0) hop_axis<0, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+        else if (wave == 1) hop_axis<1, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+        else if (wave == 2) hop_axis<2, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+        else hop_axis<3, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
+    }
+    if (wave == 0)
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[0][k] = acc[0][k] + acc[1][k];
+#pragma unroll
+    for (int d = 0; d < 2; d++) {
+        if (d == 1 && wave == 0) break;
+#pragma unroll
+        for (int j = 0; j < NC; j++) {
+            V q;
+#pragma unroll
+            for (int c = 0; c < PC; c++) {
+                q[2 * c] = acc[d][j * PC + c].re;
+                q[2 * c + 1] = acc[d][j * PC + c].im;
+            }
+            part[wave == 0 ? 0 : 2 * wave - 1 + d][j][lane] = q;
+        }
+    }
+}
+template <class T>
+__device__ __forceinline__ void split_sum(const typename SplitPart<T>::V (*part)[SplitPart<T>::NC][SPLIT_SITES], int lane,
+                                          cx<T> acc[12])
+{
+    constexpr int NC = SplitPart<T>::NC, PC = SplitPart<T>::PC;
+#pragma unroll
+    for (int j = 0; j < NC; j++) {
+        typename SplitPart<T>::V q = part[0][j][lane];
+#pragma unroll
+        for (int d = 1; d < 7; d++) q = q + part[d][j][lane];
+#pragma unroll
+        for (int k = 0; k < PC; k++) acc[j * PC + k] = mk<T>(q[2 * k], q[2 * k + 1]);
+    }
+}
+
 template <int SF, int LF, bool DAG, int RED, bool TG>
 __global__ __launch_bounds__(SPLIT_THREADS) void k_hop_split(const HopJob* __restrict__ jobs, int njobs,
                                                              SysState* __restrict__ sys, int gated, int* exec)
 {
     using T = typename SReal<SF>::T;
-    using V = typename std::conditional<SF == SF64, d2v, f4v>::type;
-    constexpr int NC = SF == SF64 ? 12 : 6;      // 16-byte pieces of an accumulator
-    constexpr int PC = SF == SF64 ? 1 : 2;       // complex numbers per piece
-    // the x axis' sum, then each direction of y, z and t: added in the order of k_hop, so that the result
-    // is the same to the last bit (FP16 spinors: up to the rounding of their scale)
-    __shared__ V part[7][NC][SPLIT_SITES];
+    __shared__ typename SplitPart<T>::V part[7][SplitPart<T>::NC][SPLIT_SITES];
     const int b = (int)blockIdx.x;
     const HopJob& J = jobs[find_job(jobs, njobs, b)];
     SysState* S = sys + J.sys;
@@ -426,36 +504,9 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_hop_split(const HopJob* __res
     const int cb = lb * SPLIT_SITES + lane;
     const bool ok = cb < J.g.Vh;
     if (wave < 4) {
-        cx<T> acc[2][12];
-#pragma unroll
-        for (int k = 0; k < 12; k++) acc[0][k] = acc[1][k] = mk<T>(T(0), T(0));
-        if (ok) {
-            const Stg<SF, false> none{};
-            const HopIn<SF, false> hin{J.in, none, 0, 0, TG && J.tg != 0, J.nc != 0};
-            int x, y, z, t, dep = 0;
-            cb_coords(J.g, J.parity, cb, x, y, z, t);
-            if (wave == 0) hop_axis<0, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
-            else if (wave == 1) hop_axis<1, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
-            else if (wave == 2) hop_axis<2, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
-            else hop_axis<3, 8, DAG, SF, LF, false, false, false, T>(J.g, cb, x, y, z, t, hin, J.links, J.lcs, acc[0], acc[1], dep);
-        }
-        if (wave == 0)
-#pragma unroll
-            for (int k = 0; k < 12; k++) acc[0][k] = acc[0][k] + acc[1][k];
-#pragma unroll
-        for (int d = 0; d < 2; d++) {
-            if (d == 1 && wave == 0) break;
-#pragma unroll
-            for (int j = 0; j < NC; j++) {
-                V q;
-#pragma unroll
-                for (int c = 0; c < PC; c++) {
-                    q[2 * c] = acc[d][j * PC + c].re;
-                    q[2 * c + 1] = acc[d][j * PC + c].im;
-                }
-                part[wave == 0 ? 0 : 2 * wave - 1 + d][j][lane] = q;
-            }
-        }
+        const Stg<SF, false> none{};
+        const HopIn<SF, false> hin{J.in, none, 0, 0, TG && J.tg != 0, J.nc != 0};
+        split_part<DAG, LF, T>(J, hin, wave, lane, cb, ok, part);
         __syncthreads();
         return;
     }
@@ -470,14 +521,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_hop_split(const HopJob* __res
     double v[NRED] = {0.0, 0.0, 0.0, 0.0};
     if (ok) {
         cx<T> acc[12];
-#pragma unroll
-        for (int j = 0; j < NC; j++) {
-            V q = part[0][j][lane];
-#pragma unroll
-            for (int d = 1; d < 7; d++) q = q + part[d][j][lane];
-#pragma unroll
-            for (int k = 0; k < PC; k++) acc[j * PC + k] = mk<T>(q[2 * k], q[2 * k + 1]);
-        }
+        split_sum<T>(part, lane, acc);
         const T c2 = (T)J.c2;
 #pragma unroll
         for (int k = 0; k < 12; k++) acc[k] = c2 * acc[k];

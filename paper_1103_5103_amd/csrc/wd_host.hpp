@@ -183,15 +183,17 @@ struct Reports {
     template <class F>
     View wait(int i, F&& ok) const
     {
-        View v = get(i);
-        for (long n = 1; !ok(v); n++) {
-            pause(n, i);
-            v = get(i);
+        bool drained = false;
+        for (long n = 1;; n++) {
+            const View v = get(i);
+            if (ok(v)) return v;
+            if (drained) throw Error{WD_ERR_HIP, "the stream ended without the report of system " + std::to_string(i)};
+            drained = pause(n);
         }
-        return v;
     }
-    void pause(long n, int i) const;
-    mutable bool idle = false;  // the stream had drained at the last look
+    // a moment's wait, now and then a look at the stream; true: it had drained (a report that was to come
+    // is there at the next look)
+    bool pause(long n) const;
 };
 
 // wd_apply_noalloc: a fixed device array per GPU (kNoallocScratchBytes) takes a copy of an input that
@@ -215,6 +217,9 @@ void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool da
 // links are shared or small), else forced (0 off, 1 on)
 void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>& t, SysState* sys, int gated,
              hipStream_t s, double bytes_per_site_total, int stage = -1, int ntl = -1);
+// a hop of an FP64 residual update (launch_update), gated on the stopped statuses; hop 2 is followed by
+// FIN_UPDATE
+void run_update(int hop, int sf, int lf, const JobTable<HopJob>& t, SysState* sys, hipStream_t s, double bytes_total);
 // fold: the sweep does the finisher of the reduction before it and leaves its own to the next sweep
 void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int gated, hipStream_t s,
                double bytes_total, bool fold = false);

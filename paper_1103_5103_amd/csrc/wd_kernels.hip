@@ -43,11 +43,11 @@ __device__ __forceinline__ double c_abs2(double2 a) { return a.x * a.x + a.y * a
 __device__ __forceinline__ bool c_finite(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 
 // Tell the host (relaxed system-scope stores; the first has left before the second is issued).
-__device__ __forceinline__ void report(SysState* S)
+__device__ __forceinline__ void report(SysState* S, double rr)
 {
     SysReport* R = S->report;
     if (!R) return;
-    __hip_atomic_store(&R->rr, S->rr_true, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&R->rr, rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __builtin_amdgcn_s_waitcnt(0);
     const unsigned long long v = ((unsigned long long)S->status << 56) |
                                  ((unsigned long long)(S->nrel & 0xffffff) << 32) | (unsigned)S->iter;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void report(SysState* S)
 __device__ __forceinline__ void stop(SysState* S, int status)
 {
     S->status = status;
-    report(S);
+    report(S, S->rr);
 }
 
 // The scalars of a BiCGstab iteration from the reduced sums; each returns the status that follows.
@@ -109,7 +109,8 @@ __device__ __forceinline__ void store_alpha(SysState* S, int iter, const double*
     }
     S->alpha = alpha;
     S->delta = make_double2(tot[0], tot[1]);
-    report(S);
+    S->fresh = 0;
+    report(S, rr);
 }
 
 template <int FIN>
@@ -135,20 +136,29 @@ __device__ void finish(SysState* S, const double* tot)
         S->rr = tot[2];
         S->maxrr = tot[2];
         S->status = (isfinite(tot[2]) && c_finite(S->delta)) ? ST_RUNNING : ST_NAN;
-        report(S);
+        report(S, S->rr);
     } else if constexpr (FIN == FIN_UPDATE) {
-        // the true residual: finished, or go on with rhat and s kept (SEL1) or from r alone (SEL2: after a
-        // breakdown, and every outer step of defect correction)
+        // the true residual |r|^2 (tot[2]): finished, or go on with rhat and s kept (SEL1) or from r alone
+        // (SEL2: after a breakdown, and every outer step of defect correction). The update of a system
+        // that was not expected to finish has left the new residual and its sums <rhat, r>, |r_lo|^2.
         const double rr = tot[2];
         const int was = S->status;
         S->nrel += 1;
         S->rr_true = rr;
+        S->fresh = 1;
+        S->t_zero = 0;
         if (!isfinite(rr)) S->status = ST_NAN;
         else if (rr <= S->target2) S->status = ST_DONE;
         else if (was == ST_MAXIT || S->iter >= S->maxit) S->status = ST_NOCONV;
         else if (was == ST_BREAKDOWN) S->status = ++S->restarts > 2 ? ST_BROKEN : ST_SEL2;
         else S->status = S->dc ? ST_SEL2 : ST_SEL1;
-        report(S);
+        if (((GATE_GOES_ON >> was) & 1) && (S->status == ST_SEL1 || S->status == ST_SEL2)) {
+            S->delta = make_double2(tot[0], tot[1]);
+            S->rr = tot[3];
+            S->maxrr = tot[3];
+            S->status = (isfinite(tot[3]) && c_finite(S->delta)) ? ST_RUNNING : ST_NAN;
+        }
+        report(S, S->status == ST_RUNNING ? S->rr : rr);
     } else if constexpr (FIN == FIN_CGA) {
         // CG: alpha_n = |r_n|^2 / <p_n, A p_n> (tot[0] = Re <p, A p>; A Hermitian positive definite)
         const double pAp = tot[0];
@@ -288,7 +298,12 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         // x <- x - beta s + chi w ; r_{n+1} = w - chi A w ; <rhat, r_{n+1}>, |r_{n+1}|^2
         cx<T> x[12], s[12], w[12];
         if (ok) {
-            load_spinor<SFX, T, true>(J.f[R_F0], i, x);
+            if (S->fresh) {
+#pragma unroll
+                for (int k = 0; k < 12; k++) x[k] = mk<T>(T(0), T(0));
+            } else {
+                load_spinor<SFX, T, true>(J.f[R_F0], i, x);
+            }
             load_spinor<SFL, T, true>(J.f[R_F2], i, s);
             load_spinor<SFL, T, true>(J.f[R_F3], i, w);
         }
@@ -1082,7 +1097,7 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     FIN_CASE(3, FIN_CHI)
     FIN_CASE(3, FIN_ALPHA)
     FIN_CASE(3, FIN_RESTART)
-    FIN_CASE(3, FIN_UPDATE)
+    FIN_CASE(4, FIN_UPDATE)
     FIN_CASE(3, FIN_CGA)
     FIN_CASE(3, FIN_CGB)
     return hipErrorInvalidValue;

@@ -36,6 +36,11 @@ int split_blocks(int Vh);
 hipError_t launch_hop_split(int sf, int lf, bool dag, int red, const HopJob* jobs, int njobs, long nblocks,
                             SysState* sys, int gated, hipStream_t s, int* exec = nullptr, int tg = 0,
                             hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// The hops of an FP64 residual update (wd_update.hip): hop 1 (or 3, where T does not hold D_oe x_hi) with
+// sf = storage of x_lo (FP64 or FP32), hop 2 with sf = storage of the iteration. Gated (mask of the stopped statuses); FIN_UPDATE follows.
+hipError_t launch_update(int hop, int sf, int lf, const HopJob* jobs, int njobs, long nblocks, SysState* sys, int gated,
+                         hipStream_t s, int* exec = nullptr, int split = 0, int tg = 0, int ntl = 1,
+                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Multi-RHS hop (tables whose jobs have rhs >= 2): kt = mrhs_kt(largest group), 2 or 4 systems per
 // thread at most (0: unsupported group size). Low-precision spinors only.
 int mrhs_kt(int k);

@@ -114,15 +114,14 @@ Reports::View Reports::get(int i) const
     v.rr = r[i].rr;
     return v;
 }
-void Reports::pause(long n, int i) const
+bool Reports::pause(long n) const
 {
-    if (idle) throw Error{WD_ERR_HIP, "the stream ended without the report of system " + std::to_string(i)};
     __builtin_ia32_pause();
-    if (n % 4096) return;
-    // about every 100 us: has the stream failed, or ended (then the report is there at the next look)?
+    if (n % 4096) return false;  // (about every 100 us)
     const hipError_t e = hipStreamQuery(st);
-    if (e == hipSuccess) idle = true;
-    else if (e != hipErrorNotReady) throw Error{WD_ERR_HIP, std::string("hipStreamQuery: ") + hipGetErrorString(e)};
+    if (e != hipSuccess && e != hipErrorNotReady)
+        throw Error{WD_ERR_HIP, std::string("hipStreamQuery: ") + hipGetErrorString(e)};
+    return e == hipSuccess;
 }
 
 // ---------------------------------------------------------------- timing
@@ -293,6 +292,42 @@ static void run_finish(int nr, int fin, const JobTable<J>& t, SysState* sys, int
     if (timed) T.pending.push_back({TK_FINISH, a, b, 0.0, -1, 0, -1});
 }
 
+// Non-temporal link loads keep the links from evicting the neighbour spinors in L2. They pay
+// off when the links cannot stay in the 256 MB Infinity Cache between hops anyway (more than
+// 64 MB of links in the launch), and not when interleaved systems read the shared links from L2.
+static int stream_links(const JobTable<HopJob>& t, int lf)
+{
+    double link_bytes = 0;
+    for (auto& j : t.host) {
+        if (j.ilv > 1) return 0;
+        link_bytes += (double)j.g.Vh * 8 * link_chunks(lf) * link_chunk_bytes(lf);
+    }
+    return link_bytes > 64.0 * (1 << 20);
+}
+
+void run_update(int hop, int sf, int lf, const JobTable<HopJob>& t, SysState* sys, hipStream_t s, double bytes)
+{
+    Timer& T = timer();
+    hipEvent_t a = nullptr, b = nullptr;
+    int* flag = nullptr;
+    const bool timed = T.on && t.nblocks > 0;
+    if (timed) {
+        flag = T.slot();
+        a = T.get();
+        b = T.get();
+    }
+    int tg = 0;
+    for (const HopJob& j : t.host) {
+        tg |= j.tg;
+        if (!j.in.p || !j.out.p || !j.z.p || (hop == 2 && !(j.x0.p && j.x1.p && j.u_r.p && j.u_rh.p && j.u_s.p && j.u_as.p)))
+            throw Error{WD_ERR_ARG, "update job without a field that its hop uses"};
+    }
+    WD_CHECK_HIP(launch_update(hop, sf, lf, t.d(), t.n(), t.nblocks, sys, GATE_STOPPED, s, flag,
+                               t.host.empty() ? 0 : t.host[0].split, tg, stream_links(t, lf), a, b));
+    if (timed) T.pending.push_back({TK_HOP_F64, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
+    if (hop == 2) run_finish(4, FIN_UPDATE, t, sys, GATE_STOPPED, s);
+}
+
 void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>& t, SysState* sys, int gated,
              hipStream_t s, double bytes, int stage, int ntl_force)
 {
@@ -306,17 +341,8 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
         a = T.get();
         b = T.get();
     }
-    // Non-temporal link loads keep the links from evicting the neighbour spinors in L2. They pay
-    // off when the links cannot stay in the 256 MB Infinity Cache between hops anyway (more than
-    // 64 MB of links in the launch), and not when interleaved systems read the shared links from L2.
-    int tg = 0, ntl = 1;
-    double link_bytes = 0;
-    for (auto& j : t.host) {
-        tg |= j.tg;
-        if (j.ilv > 1) ntl = 0;
-        link_bytes += (double)j.g.Vh * 8 * link_chunks(lf) * link_chunk_bytes(lf);
-    }
-    if (link_bytes <= 64.0 * (1 << 20)) ntl = 0;
+    int tg = 0, ntl = stream_links(t, lf);
+    for (auto& j : t.host) tg |= j.tg;
     if (ntl_force >= 0) ntl = ntl_force != 0;
     if (!t.host.empty() && t.host[0].split) {
         WD_CHECK_HIP(launch_hop_split(sf, lf, dag, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));

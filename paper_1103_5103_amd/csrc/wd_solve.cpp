@@ -527,6 +527,7 @@ struct EoSys {
     Field X64;         // FP64 solution (even half iterated, odd half rebuilt); caller-provided or own
     bool x_ready = false;  // X64 already holds the start vector (use_x0 handled by the caller)
     bool r_ready = false;  // RH already holds b_prec - M_prec x0 for that start vector (one system only)
+    bool keep_res = false; // RH is read after the solve (a later guess)
     bool keep_odd = false; // store the rebuilt odd half into X64 as well (a later guess reads it)
     bool bp_ready = false; // BP (caller-provided) already holds b_prec (one system only)
     Field RH;              // FP64 residual b_prec - M_prec x_e; caller-provided or own
@@ -618,12 +619,15 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         q.report = (SysReport*)&rep.r[slot0 + i];
         q.target2 = -1.0;
         q.rr_true = -1.0;
+        q.fresh = 1;
+        q.t_zero = !any_x0;
         q.status = ST_RUNNING;
     }
 
     // ---- static job tables
     JobTable<HopJob> Hhb, Hx1, Hx2, Hrec;
-    JobTable<SweepJob> Nb, Bp, InitFirst, Init, Acc;
+    JobTable<SweepJob> Nb, Bp, InitFirst, Init;
+    JobTable<HopJob> Up1, Up2;
     JobTable<HopJob> H1, H2, H3, H4;
     JobTable<SweepJob> SW, SXR, SS;
     std::vector<int> need_src;
@@ -659,6 +663,17 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         j.x1 = e.X64.half(0);
         j.c1 = -e.a * e.a;
         Hx2.host.push_back(j);
+        // the same for x_e + x_lo, the new x_e stored and the residual handed to the iteration
+        j.z = e.xl.all();
+        j.u_r = e.r.all();
+        j.u_rh = e.rh.all();
+        j.u_s = e.s.all();
+        j.u_as = e.As.all();
+        j.keep = e.keep_res;
+        Up2.host.push_back(j);
+        j = Hx1.host.back();
+        j.z = e.xl.all();
+        Up1.host.push_back(j);
         // odd half: x_o = (b_o + 1/2 D_oe x_e) / a  (eq. eo3)
         j = hop_job(g, 1, i, e.X64.half(0), e.X64.half(1), d1, lcs, 0.5 / e.a);
         j.x0 = e.src.B64.half(1);
@@ -672,14 +687,9 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         sj.f[R_F4] = e.xl.all();
         sj.flags = (1 | 2) << 8;  // after an update: keep rhat and s (SEL1), or restart from r (SEL2)
         Init.host.push_back(sj);
-        sj.flags = 1 | 2 | 4;
+        sj.flags = 1 | 2;
         if (!any_x0) sj.f[R_F1] = e.BP.all();  // x0 = 0: the start residual is b_prec
         InitFirst.host.push_back(sj);
-        sj = sweep_job(i, e.xl.nsites());
-        sj.f[R_F0] = e.X64.half(0);
-        sj.f[R_F1] = e.xl.all();
-        sj.flags = 1;
-        Acc.host.push_back(sj);
         // iteration: As = a^2 s - 1/4 D_eo D_oe s, <rhat, As>; w; Aw = M_prec w, <Aw, w>, |Aw|^2; x, r; s
         const void* l0 = e.g->slk(LFL, 0);
         const void* l1 = e.g->slk(LFL, 1);
@@ -716,14 +726,14 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         sj.f[R_F3] = e.r.all();
         SS.host.push_back(sj);
     }
-    for (auto* t : {&Hhb, &Hx1, &Hx2, &Hrec})
+    for (auto* t : {&Hhb, &Hx1, &Hx2, &Up1, &Up2, &Hrec})
         for (auto& j : t->host) set_tile(j, tile_64[j.sys]);
     for (auto* t : {&H1, &H2, &H3, &H4})
         for (auto& j : t->host) {
             set_tile(j, tile_lo[j.sys]);
             j.rhs = rhs_lo;
         }
-    for (auto* t : {&Hhb, &Hx1, &Hx2, &Hrec, &H1, &H2, &H3, &H4}) {
+    for (auto* t : {&Hhb, &Hx1, &Hx2, &Up1, &Up2, &Hrec, &H1, &H2, &H3, &H4}) {
         for (auto& j : t->host) {
             j.tg = S[j.sys].g->tg;  // solver links of a temporal-gauge handle
             j.nc = S[j.sys].g->nc;  // and the handle's spin basis
@@ -734,12 +744,12 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     }
     for (auto& j : SW.host) j.pnblk = H2.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
     for (auto& j : SXR.host) j.pnblk = H4.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
-    for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &Acc, &SW, &SXR, &SS}) layout(*t);
+    for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SS}) layout(*t);
     const bool fold = fold_finishers(SW);
     for (auto& j : H4.host) j.p2 = fold;
     // one copy for all tables, into a buffer kept by the first handle across solves
     upload_tables(st, S[0].g->raw["eo.tables"],
-                  {&Hhb, &Hx1, &Hx2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &Init, &Acc, &SW, &SXR, &SS});
+                  {&Hhb, &Hx1, &Hx2, &Up1, &Up2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SS});
 
     // ---- setup
     if (!need_src.empty()) {
@@ -788,6 +798,8 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
 
     const double bl = spinor_site_bytes(SFL), bx = spinor_site_bytes(SFX);
     const double bH1 = hop_bytes(H1, SFL, LFL, 0), bH2 = hop_bytes(H2, SFL, LFL, 2), bH4 = hop_bytes(H4, SFL, LFL, 1);
+    double sites = 0;
+    for (auto& e : S) sites += (double)e.g->geo.Vh;
     const double bSW = sweep_bytes(SW, 3 * bl), bSXR = sweep_bytes(SXR, 2 * bx + 5 * bl), bSS = sweep_bytes(SS, 4 * bl);
 
     auto iterate = [&](hipStream_t q) {
@@ -805,37 +817,64 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
                              [&](hipStream_t q) {
                                  for (int k = 0; k < poll; k++) iterate(q);
                              });
-    // Reliable update of the systems that stopped (gate GATE_STOPPED; finished systems are marked
-    // ST_DONE first): x_hi += x_lo, r_hi = b_prec - M_prec x_hi, |r_hi|^2. Every step runs on the
-    // full job tables, so no per-subset tables or host synchronisation are needed.
+    // Update of the systems that stopped: x_hi += x_lo, r = b_prec - M_prec x_hi in FP64 (wd_update.hip),
+    // handed to the iteration unless it only verifies convergence. Every step runs on the full job
+    // tables, gated, so no per-subset tables or host synchronisation are needed. The bytes are those of
+    // a reliable update that goes on.
+    const bool dc = P.mixed && P.mixed_mode == WD_MIXED_DEFECT;
+    const double bU1 = hop_bytes(Up1, SF64, L64, 0) + sites * bx;
+    bool have_t = !S[0].r_ready;  // T64 holds D_oe x_hi (0 without a start vector)
+    const double bU2 = hop_bytes(Up2, SF64, L64, 2) + sites * (bx + (dc ? 3 : 6) * bl);
     auto reliable_update = [&]() {
-        run_sweep(OP_ACC, SFL, Acc, sys.d(), GATE_STOPPED, st, sweep_bytes(Acc, 2 * 192 + 2 * bx));
-        run_hop(SF64, L64, false, RED_NONE, FIN_STORE, Hx1, sys.d(), GATE_STOPPED, st, hop_bytes(Hx1, SF64, L64, 0));
-        run_hop(SF64, L64, false, RED_NORM, FIN_UPDATE, Hx2, sys.d(), GATE_STOPPED, st, hop_bytes(Hx2, SF64, L64, 2));
+        run_update(have_t ? 1 : 3, SFX, L64, Up1, sys.d(), st, bU1);
+        have_t = true;
+        run_update(2, SFL, L64, Up2, sys.d(), st, bU2);
     };
-    // the new residual into the iteration, and RUNNING again, for the systems that go on
+    // after a verification that failed: the residual from RH into the iteration, and RUNNING again
     auto resume = [&]() {
         // the s update of the iteration in which the system stopped was gated off: apply it (the
         // scalars and the iterated residual of that iteration are still in place), since a continuing
         // reliable update keeps s; defect correction restarts with s = r instead
-        if (!(P.mixed && P.mixed_mode == WD_MIXED_DEFECT)) run_sweep(OP_S, SFL, SS, sys.d(), 1 << ST_SEL1, st, bSS);
-        run_sweep(OP_INIT, SFL, Init, sys.d(), (1 << ST_SEL1) | (1 << ST_SEL2), st,
-                  init_bytes(Init, SFL, P.mixed && P.mixed_mode == WD_MIXED_DEFECT));
+        if (!dc) run_sweep(OP_S, SFL, SS, sys.d(), 1 << ST_SEL1, st, bSS);
+        run_sweep(OP_INIT, SFL, Init, sys.d(), (1 << ST_SEL1) | (1 << ST_SEL2), st, init_bytes(Init, SFL, dc));
     };
 
     int active = 0;
     for (auto& e : S) active += !e.done;
-    // The host watches the systems' reports and keeps one step of the iteration queued behind the one it
-    // waits for (its launches are gated off where the system has stopped meanwhile). A system that
-    // stopped gets its FP64 update; whether it has finished, goes on or restarts is decided on the
-    // device. After an update that only verifies convergence nothing is queued until its outcome is
-    // known.
+    // The host watches the systems' reports. It queues a second step behind the one it waits for while
+    // the residuals reported so far foretell that the first will not stop the system (one system; with
+    // several, a step queued too much idles those that have stopped). A system that stopped gets its
+    // FP64 update; whether it has finished, goes on or restarts is decided on the device. After an
+    // update that only verifies convergence nothing is queued until its outcome is known. Measured with
+    // no step ahead / one always: 8^4 672 / 718 us, FP64 on 10x6x14x18 600 / 571 us, 16^3x32 six masses 3.97 /
+    // 3.89 ms, 32^3x64 eight masses 42.3 / 42.7 ms, 96 systems 31.9 / 33.7 ms.
     struct Watch {
         int expect = 0;      // the iteration that the queued steps reach
         int nrel = 0;        // updates queued
-        bool verify = false; // waits for the outcome of an update without a resume behind it
+        double rr = -1, rr_max = 0, ratio = 1, target2 = 0, delta2 = 0;
+        // |r|^2 of the iteration after the last one reported, if it falls as it did
+        bool goes_on() const
+        {
+            const double next = rr * ratio;
+            return rr > 0 && next > target2 && next > delta2 * rr_max;
+        }
+        // a new report: the next iteration of the run, or the start of a new one
+        void saw(double v, bool start)
+        {
+            if (!(v > 0)) return;
+            if (!start && rr > 0) ratio = v / rr;
+            rr_max = start ? v : std::max(rr_max, v);
+            rr = v;
+        }
+        int seen = -1;       // iteration and updates of the last report
+        int seen_nrel = 0;
+        bool verify = false; // waits for the outcome of an update that only verifies
     };
     std::vector<Watch> watch(n);
+    for (int i = 0; i < n; i++) {
+        watch[i].target2 = sys.h[i].target2;
+        watch[i].delta2 = P.mixed ? sys.h[i].delta_rel2 : 0.0;
+    }
     const int step = graph ? poll : 1;
     long host_iters = 0;
     const long host_cap = 4L * P.max_iter + 16L * poll + 64;  // with the steps queued past a stop
@@ -851,7 +890,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     while (active > 0) {
         int running = 0;
         for (int i = 0; i < n; i++) running += !S[i].done && !watch[i].verify;
-        while (running > 0 && inflight < 2) {
+        while (running > 0 && inflight < (n == 1 && !graph && watch[0].goes_on() ? 2 : 1)) {
             if (graph) graph->launch(st);
             else iterate(st);
             for (int i = 0; i < n; i++)
@@ -883,7 +922,12 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
                     return (v.status != ST_RUNNING && v.status != ST_SEL1 && v.status != ST_SEL2) ||
                            (v.status == ST_RUNNING && v.iter >= w.expect - back);
                 });
-                stopped = stopped || v.status != ST_RUNNING;
+                if (v.iter != watch[i].seen || v.nrel != watch[i].seen_nrel) {
+                    watch[i].saw(v.rr, watch[i].seen < 0 || v.nrel != watch[i].seen_nrel);
+                    watch[i].seen = v.iter;
+                    watch[i].seen_nrel = v.nrel;
+                }
+                stopped = stopped || v.status != ST_RUNNING || w.verify;
             }
             if (!stopped) break;
         }
@@ -899,24 +943,22 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
             } else if (v.status == ST_SEL1 || v.status == ST_SEL2) {  // the check failed: go on
                 w.verify = false;
                 any_resume = true;
-            } else if (v.status != ST_RUNNING) {
+            } else if (v.status == ST_RUNNING) {
+                w.verify = false;  // (another system's resume has taken it along)
+            } else {
                 w.nrel++;
                 w.verify = v.status == ST_CONVERGED || v.status == ST_MAXIT;
                 any_update = true;
-                any_resume = any_resume || !w.verify;
             }
         }
         if (any_update) reliable_update();
-        if (any_resume) {
-            resume();
-            for (auto& w : watch) w.verify = false;
-        }
+        if (any_resume) resume();
     }
     for (int i = 0; i < n; i++) {
         const Reports::View v = rep.get(slot0 + i);
         S[i].iters = v.iter;
         S[i].reliable = v.nrel;
-        if (v.nrel > 0) S[i].rr_true = v.rr;
+        if (v.nrel > 0 && v.status != ST_RUNNING) S[i].rr_true = v.rr;
     }
 
     // ---- finish: odd half from eq. eo3, unpack. With x_o from eq. eo3 the full residual is
@@ -1642,6 +1684,7 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
         e.X64 = X[idx];
         e.RH = R[idx];
         e.BP = BPm;
+        e.keep_res = guess == WD_GUESS_POLY;
         e.keep_odd = guess == WD_GUESS_MINRES;  // its inner products run over full solutions
         const int kall = (int)done.size();
         const int k = P.guess_order > 0 ? std::min(P.guess_order, kall) : kall;

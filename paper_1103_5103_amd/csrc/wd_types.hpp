@@ -38,6 +38,8 @@ enum SysStatus {
 constexpr int FIN_NONE = -1;
 // Kernel gates are masks of the statuses allowed to run (0: no gating); GATE_RUN = the iteration.
 constexpr int GATE_RUN = 1 << ST_RUNNING;
+// updates of these go on with the iteration unless the target is met (the others only verify)
+constexpr int GATE_GOES_ON = (1 << ST_RELIABLE) | (1 << ST_BREAKDOWN);
 constexpr int GATE_STOPPED = (1 << ST_CONVERGED) | (1 << ST_RELIABLE) | (1 << ST_BREAKDOWN) | (1 << ST_MAXIT);
 
 // Finisher kinds (what the last block does with the reduced sums)
@@ -102,7 +104,7 @@ struct ShiftBlock {
 // watches it instead of copying the record and waiting for the stream. state holds the status, the
 // number of FP64 updates and the iteration in one word, stored after rr.
 struct SysReport {
-    double rr;                 // |r|^2 of the last FP64 residual update
+    double rr;                 // |r|^2: of the iterated residual, of the FP64 one where an update ends the solve
     unsigned long long state;  // status << 56 | updates << 32 | iteration
 };
 
@@ -123,6 +125,8 @@ struct SysState {
     double rr;         // |r|^2 of the iterated residual
     double maxrr;      // max |r|^2 since the last reliable update
     double rr_true;    // |r|^2 of the last FP64 residual update
+    int fresh;         // x_lo counts as zero (start, after an update) and is not read
+    int t_zero;        // T = D_oe x_hi counts as zero (no start vector, no update yet) and is not read
     double target2;    // stop when rr <= target2
     double delta_rel2; // reliable update when rr < delta_rel2 * maxrr
     double cga, cgb;   // CG: alpha_n, beta_n
@@ -150,6 +154,9 @@ struct HopJob {
     SpinorRef out;       // output half field
     SpinorRef x0, x1;    // epilogue terms (p == nullptr: absent)
     SpinorRef z;         // partner of <z, out>
+    // residual update (wd_update.hip): x_lo in z; the second hop's low-precision fields r, rhat, s, A s
+    SpinorRef u_r, u_rh, u_s, u_as;
+    int keep;            // residual update: the FP64 residual is stored whatever follows
     const void* links;   // the 8 links per site of this output parity
     const void* links_nb;  // full-lattice launches: those of the other parity (else NULL)
     long lcs;            // link chunk stride
