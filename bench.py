@@ -377,7 +377,7 @@ def read_tuning(path):
 def hop_variants(rec_by_red):
     """Average duration and algorithmic GB/s of the low-precision hop launches per fused reduction
     (timing classes 4 + r)."""
-    names = ("none", "zdot", "outx", "norm")
+    names = ("none", "zdot", "outx", "norm", "full")
     out = {}
     for r, (ms, n, by) in zip(names, rec_by_red):
         if n > 0 and ms > 0:
@@ -568,7 +568,7 @@ def main():
         for _ in range(args.steps):
             fn()
         torch.cuda.synchronize()
-        r = [wd.timing_get(c) for c in range(8)]
+        r = [wd.timing_get(c) for c in range(9)]
         wd.timing_enable(False)
         return r
 
@@ -608,7 +608,7 @@ def main():
         return round(by / (ms * 1e-3) / 1e9, 1) if ms > 0 else None
 
     hop_ms, hop_n, hop_bytes = seq[0]
-    variants = hop_variants(seq[4:8])
+    variants = hop_variants(seq[4:9])
     # parity of the benchmark's own results: the FP64 oracle residual of every mass of every method
     oracle_res = None
     if not args.no_cpu:
@@ -689,7 +689,7 @@ def main():
         chiral = {f"solve_s_{k}": round(float(np.median(v)), 5) for k, v in tch.items()}
         chiral.update({"lo_hop_GBps": gbs(seq_ch[0]), "lo_hop_avg_us": round(seq_ch[0][0] / max(seq_ch[0][1], 1) * 1e3, 2),
                        "lo_hop_frac_of_peak": round(gbs(seq_ch[0]) / HBM_PEAK_GBS, 4),
-                       "lo_hop_by_reduction": hop_variants(seq_ch[4:8])})
+                       "lo_hop_by_reduction": hop_variants(seq_ch[4:9])})
 
         memory = memory_by_method(torch, wd, U, bd, kappas, p_mixed, p_f64, dev) if args.workload == "32x64" else None
         leg16 = leg_16x32(torch, wd, li, np, dev, args.steps, True) if args.workload == "32x64" else None

@@ -601,7 +601,7 @@ __device__ __forceinline__ void store_link(void* base, long lcs, int k, long i, 
 
 // ---------------------------------------------------------------- reductions
 constexpr int BLOCK = BLOCK_SITES;
-constexpr int NRED = 4;
+constexpr int NRED = 6;
 
 __device__ __forceinline__ double wave_sum(double v)
 {

@@ -377,7 +377,7 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
         __syncthreads();
     }
     const HopIn<SF, STG> hin{J.in, stg, base, nsl, TG && J.tg != 0, J.nc != 0, J.links_nb};
-    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double v[NRED] = {};
     if (cb < J.g.Vh) {
         cx<T> acc[12];
         hop_site<DAG, SF, LF, STG, NTL, FULL, T>(J.g, J.parity, cb, hin, J.links, J.lcs, acc);
@@ -408,19 +408,28 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
                 v[0] += (double)z[k].re * acc[k].re + (double)z[k].im * acc[k].im;
                 v[1] += (double)z[k].re * acc[k].im - (double)z[k].im * acc[k].re;
             }
-        } else if constexpr (RED == RED_OUTX) {
+        } else if constexpr (RED == RED_OUTX || RED == RED_FULL) {
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 v[0] += (double)acc[k].re * x0[k].re + (double)acc[k].im * x0[k].im;
                 v[1] += (double)acc[k].re * x0[k].im - (double)acc[k].im * x0[k].re;
                 v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
             }
+            if constexpr (RED == RED_FULL) {
+                cx<T> z[12];
+                load_spinor<SF, T, NTL || FULL>(J.z, cb, z);
+#pragma unroll
+                for (int k = 0; k < 12; k++) {
+                    v[3] += (double)z[k].re * acc[k].re + (double)z[k].im * acc[k].im;
+                    v[4] += (double)z[k].re * acc[k].im - (double)z[k].im * acc[k].re;
+                }
+            }
         } else if constexpr (RED == RED_NORM) {
 #pragma unroll
             for (int k = 0; k < 12; k++) v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
         }
     }
-    if constexpr (RED != RED_NONE) write_partials<3>(v, S, J.rblk0 + lb, J.p2 != 0);
+    if constexpr (RED != RED_NONE) write_partials<RED == RED_FULL ? 5 : 3>(v, S, J.rblk0 + lb, J.p2 != 0);
 }
 
 // The hop for launches that leave the chip mostly idle (up to kSplitSites sites, one system): such a
@@ -518,7 +527,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_hop_split(const HopJob* __res
         if constexpr (RED == RED_ZDOT) load_spinor<SF, T>(J.z, cb, z);
     }
     __syncthreads();
-    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double v[NRED] = {};
     if (ok) {
         cx<T> acc[12];
         split_sum<T>(part, lane, acc);
@@ -588,7 +597,8 @@ static inline dim3 grid1(long nblk) { return dim3((unsigned)nblk); }
     HOP_CASE(SF_, LF_, DAG_, RED_NONE, FIN_STORE)                                                                  \
     HOP_CASE(SF_, LF_, DAG_, RED_NORM, FIN_STORE)                                                                  \
     HOP_CASE(SF_, LF_, DAG_, RED_ZDOT, FIN_BETA)                                                                   \
-    HOP_CASE(SF_, LF_, DAG_, RED_OUTX, FIN_CHI)
+    HOP_CASE(SF_, LF_, DAG_, RED_OUTX, FIN_CHI)                                                                    \
+    HOP_CASE(SF_, LF_, DAG_, RED_FULL, FIN_CHI)
 // the adjoint hops of the normal equations (CG): the iteration's two, plus the FP64 residual's
 #define HOP_DAG_LO(SF_, LF_)                                                                                       \
     HOP_CASE(SF_, LF_, true, RED_NONE, FIN_STORE)                                                                  \

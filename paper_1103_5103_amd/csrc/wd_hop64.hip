@@ -41,9 +41,11 @@ hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int nj
     if (nblocks <= 0) return hipSuccess;
     HOP_FULL(L64_18, false, RED_ZDOT)
     HOP_FULL(L64_18, false, RED_OUTX)
+    HOP_FULL(L64_18, false, RED_FULL)
     HOP_FULL(L64_18, false, RED_NORM)
     HOP_FULL(L64_12, false, RED_ZDOT)
     HOP_FULL(L64_12, false, RED_OUTX)
+    HOP_FULL(L64_12, false, RED_FULL)
     HOP_FULL(L64_12, false, RED_NORM)
     return hipErrorInvalidValue;
 }

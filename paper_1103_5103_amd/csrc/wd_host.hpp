@@ -66,9 +66,9 @@ struct Field {
 size_t field_bytes(int sf, int halves, long stride);
 
 // ---------------------------------------------------------------- timing
-// TK_HOP_LO_RED + r: the low-precision hops with fused reduction r (RED_NONE .. RED_NORM), also
+// TK_HOP_LO_RED + r: the low-precision hops with fused reduction r (RED_NONE .. RED_FULL), also
 // counted in TK_HOP_LO
-enum { TK_HOP_LO = 0, TK_HOP_F64 = 1, TK_SWEEP = 2, TK_FINISH = 3, TK_HOP_LO_RED = 4, NTK = 8 };
+enum { TK_HOP_LO = 0, TK_HOP_F64 = 1, TK_SWEEP = 2, TK_FINISH = 3, TK_HOP_LO_RED = 4, NTK = 9 };
 struct Timer {
     bool on = false;
     struct Rec { int cls; hipEvent_t a, b; double bytes; int slot; int njobs; int cls2; };

@@ -77,12 +77,9 @@ __device__ __forceinline__ int calc_chi(const double* tot, double2& chi)
     chi = make_double2(aww.x / awaw, aww.y / awaw);
     return ST_RUNNING;
 }
-// iter: the iteration that ends here
-__device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int iter, const double* tot, double2& alpha)
+// status at the end of iteration iter: its |r|^2 and delta' = <rhat, r>
+__device__ __forceinline__ int calc_status(const SysState* S, int iter, double rr, double2 d1)
 {
-    const double2 d1 = make_double2(tot[0], tot[1]);
-    const double rr = tot[2];
-    alpha = c_neg(c_div(c_mul(S->beta, d1), c_mul(delta, S->chi)));
     if (!isfinite(rr) || !c_finite(d1)) return ST_NAN;
     if (rr <= S->target2) return ST_CONVERGED;
     if (S->mixed && rr < S->delta_rel2 * S->maxrr) return ST_RELIABLE;
@@ -90,6 +87,13 @@ __device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int 
     if (c_abs2(d1) == 0.0) return ST_BREAKDOWN;
     return ST_RUNNING;
 }
+__device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int iter, const double* tot, double2& alpha)
+{
+    const double2 d1 = make_double2(tot[0], tot[1]);
+    alpha = c_neg(c_div(c_mul(S->beta, d1), c_mul(delta, S->chi)));
+    return calc_status(S, iter, tot[2], d1);
+}
+// tot: delta', |r|^2
 __device__ __forceinline__ void store_alpha(SysState* S, int iter, const double* tot, double2 alpha, int status)
 {
     const double rr = tot[2];
@@ -131,6 +135,20 @@ __device__ void finish(SysState* S, const double* tot)
         double2 alpha;
         const int iter = S->iter + 1, st = calc_alpha(S, S->delta, iter, tot, alpha);
         store_alpha(S, iter, tot, alpha, st);
+    } else if constexpr (FIN == FIN_CHIALPHA) {
+        // <rhat, w> = 0 by the choice of beta, so delta' = <rhat, w - chi A w> = -chi <rhat, A w>, and
+        // alpha = -beta delta' / (delta chi) = beta <rhat, A w> / delta are known before the sweep
+        double2 chi;
+        const double2 rhAw = make_double2(tot[3], tot[4]);
+        const int st = !c_finite(rhAw) ? ST_NAN : calc_chi(tot, chi);
+        if (st != ST_RUNNING) return stop(S, st);
+        S->chi = chi;
+        S->alpha = c_div(c_mul(S->beta, rhAw), S->delta);
+        S->delta = c_neg(c_mul(chi, rhAw));
+    } else if constexpr (FIN == FIN_RR) {
+        const int iter = S->iter + 1;
+        const double t3[3] = {S->delta.x, S->delta.y, tot[2]};
+        store_alpha(S, iter, t3, S->alpha, calc_status(S, iter, tot[2], S->delta));
     } else if constexpr (FIN == FIN_RESTART) {
         S->delta = make_double2(tot[0], tot[1]);
         S->rr = tot[2];
@@ -201,7 +219,7 @@ __global__ __launch_bounds__(BLOCK) void k_finish(const FinJob* __restrict__ fin
     const FinJob F = fin[blockIdx.x];
     SysState* S = sys + F.sys;
     if (gated && !((gated >> S->status) & 1)) return;  // gated: mask of the statuses that run
-    double tot[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double tot[NRED] = {};
     if constexpr (NR > 0) {
         for (int i = threadIdx.x; i < F.rnblk; i += BLOCK) {
 #pragma unroll
@@ -253,7 +271,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
     // too, except those of the low-precision x / r update, whose new residual the next sweep reads
     // at once (measured on the 32^3x64 mixed solves: sweeps 4.9 -> 5.2-5.6 TB/s, and the hops that
     // follow them 2% faster).
-    constexpr bool NTS = !(OP == OP_XR && SFL != SF64);
+    constexpr bool NTS = !((OP == OP_XR || OP == OP_XRS) && SFL != SF64);
     const int b = blockIdx.x;
     const SweepJob& J = jobs[find_job(jobs, njobs, b)];
     SysState* S = sys + J.sys;
@@ -262,7 +280,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
     if (exec && lb == 0 && threadIdx.x == 0) atomicAdd(exec, 1);
     const long i = (long)lb * BLOCK + threadIdx.x;
     const bool ok = i < J.n;
-    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double v[NRED] = {};
 
     if constexpr (OP == OP_W) {
         // w = r + beta A s
@@ -338,6 +356,36 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
                 v[1] += (double)rh[k].re * w[k].im - (double)rh[k].im * w[k].re;
                 v[2] += (double)w[k].re * w[k].re + (double)w[k].im * w[k].im;
             }
+        }
+        write_partials<3>(v, S, J.rblk0 + lb);
+    } else if constexpr (OP == OP_XRS) {
+        // x <- x - beta s + chi w ; r_{n+1} = w - chi A w, |r_{n+1}|^2 ; s <- r_{n+1} + alpha (s - chi A s) in one pass
+        // (alpha is known: FIN_CHIALPHA)
+        if (ok) {
+            const cx<T> beta = cvt<T>(S->beta), chi = cvt<T>(S->chi), alpha = cvt<T>(S->alpha);
+            cx<T> x[12], s[12], w[12];
+            if (S->fresh) {
+#pragma unroll
+                for (int k = 0; k < 12; k++) x[k] = mk<T>(T(0), T(0));
+            } else {
+                load_spinor<SFX, T, true>(J.f[R_F0], i, x);
+            }
+            load_spinor<SFL, T, true>(J.f[R_F2], i, s);
+            load_spinor<SFL, T, true>(J.f[R_F3], i, w);
+#pragma unroll
+            for (int k = 0; k < 12; k++) x[k] = x[k] - beta * s[k] + chi * w[k];
+            store_spinor<SFX, T, NTS>(J.f[R_F0], i, x);
+            cx<T> aw[12];
+            load_spinor<SFL, T, true>(J.f[R_F4], i, aw);
+#pragma unroll
+            for (int k = 0; k < 12; k++) w[k] = w[k] - chi * aw[k];
+            store_spinor<SFL, T, NTS>(J.f[R_F6], i, w);
+            load_spinor<SFL, T, true>(J.f[R_F5], i, aw);
+#pragma unroll
+            for (int k = 0; k < 12; k++) v[2] += (double)w[k].re * w[k].re + (double)w[k].im * w[k].im;
+#pragma unroll
+            for (int k = 0; k < 12; k++) s[k] = w[k] + alpha * (s[k] - chi * aw[k]);
+            store_spinor<SFL, T, NTS>(J.f[R_F2], i, s);
         }
         write_partials<3>(v, S, J.rblk0 + lb);
     } else if constexpr (OP == OP_S) {
@@ -1098,6 +1146,8 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     FIN_CASE(3, FIN_ALPHA)
     FIN_CASE(3, FIN_RESTART)
     FIN_CASE(4, FIN_UPDATE)
+    FIN_CASE(5, FIN_CHIALPHA)
+    FIN_CASE(3, FIN_RR)
     FIN_CASE(3, FIN_CGA)
     FIN_CASE(3, FIN_CGB)
     return hipErrorInvalidValue;
@@ -1117,7 +1167,7 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     }
 #define SWEEP_ALL(SF_)                                                                                             \
     SWEEP_CASE(OP_W, SF_)                                                                                          \
-    SWEEP_CASE(OP_XR, SF_) SWEEP_CASE(OP_S, SF_) SWEEP_CASE(OP_INIT, SF_) SWEEP_CASE(OP_ACC, SF_)                 \
+    SWEEP_CASE(OP_XR, SF_) SWEEP_CASE(OP_XRS, SF_) SWEEP_CASE(OP_S, SF_) SWEEP_CASE(OP_INIT, SF_) SWEEP_CASE(OP_ACC, SF_)                 \
     SWEEP_CASE(OP_CGX, SF_) SWEEP_CASE(OP_CGP, SF_)
 
 hipError_t launch_sweep(int op, int sfl, const SweepJob* jobs, int njobs, long nblocks, SysState* sys, int gated,

@@ -359,7 +359,7 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     }
     if (timed)
         T.pending.push_back({cls, a, b, bytes, (int)(flag - T.dflags), t.n(), cls == TK_HOP_LO ? TK_HOP_LO_RED + red : -1});
-    if (red != RED_NONE && fin != FIN_NONE) run_finish(3, fin, t, sys, gated, s);
+    if (red != RED_NONE && fin != FIN_NONE) run_finish(red == RED_FULL ? 5 : 3, fin, t, sys, gated, s);
 }
 
 void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s)
@@ -380,7 +380,8 @@ static unsigned sweep_roles(int op)
 {
     switch (op) {
     case OP_W: return 0b111;
-    case OP_XR: return 0b1111101;
+    case OP_XR:
+    case OP_XRS: return 0b1111101;
     case OP_S: return 0b1101;
     case OP_INIT: return 0b111;
     case OP_ACC: return 0b11;
@@ -413,6 +414,7 @@ void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int 
     if (fold) return;
     switch (op) {
     case OP_XR: run_finish(3, FIN_ALPHA, t, sys, gated, s); break;
+    case OP_XRS: run_finish(3, FIN_RR, t, sys, gated, s); break;
     case OP_INIT:
     case OP_MSINIT: run_finish(3, FIN_RESTART, t, sys, gated, s); break;
     case OP_NORM: run_finish(3, FIN_STORE, t, sys, gated, s); break;

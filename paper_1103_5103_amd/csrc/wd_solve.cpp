@@ -629,7 +629,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     JobTable<SweepJob> Nb, Bp, InitFirst, Init;
     JobTable<HopJob> Up1, Up2;
     JobTable<HopJob> H1, H2, H3, H4;
-    JobTable<SweepJob> SW, SXR, SS;
+    JobTable<SweepJob> SW, SXR, SXRS, SS;
     std::vector<int> need_src;
     for (int i = 0; i < n; i++) {
         EoSys& e = S[i];
@@ -703,6 +703,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         j = hop_job(g, 0, i, e.tmp.all(), e.Aw.all(), l0, lcs, -0.25);
         j.x0 = e.w.all();
         j.c0 = e.a * e.a;
+        j.z = e.rh.all();  // (fused sweep)
         H4.host.push_back(j);
         sj = sweep_job(i, e.r.nsites());
         sj.f[R_F0] = e.w.all();
@@ -719,6 +720,8 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         sj.f[R_F5] = e.rh.all();
         sj.f[R_F6] = e.r.all();
         SXR.host.push_back(sj);
+        sj.f[R_F5] = e.As.all();
+        SXRS.host.push_back(sj);
         sj = sweep_job(i, e.r.nsites());
         sj.f[R_F0] = e.s.all();
         sj.f[R_F1] = e.r.all();
@@ -744,12 +747,14 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     }
     for (auto& j : SW.host) j.pnblk = H2.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
     for (auto& j : SXR.host) j.pnblk = H4.host[0].split ? split_blocks(S[j.sys].g->geo.Vh) : nblk(S[j.sys].g->geo.Vh);
-    for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SS}) layout(*t);
+    for (auto* t : {&Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SXRS, &SS}) layout(*t);
     const bool fold = fold_finishers(SW);
     for (auto& j : H4.host) j.p2 = fold;
+    for (auto& j : Up2.host) j.s_current = !fold;
     // one copy for all tables, into a buffer kept by the first handle across solves
     upload_tables(st, S[0].g->raw["eo.tables"],
-                  {&Hhb, &Hx1, &Hx2, &Up1, &Up2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SS});
+                  {&Hhb, &Hx1, &Hx2, &Up1, &Up2, &Hrec, &H1, &H2, &H3, &H4, &Nb, &Bp, &InitFirst, &Init, &SW, &SXR, &SXRS,
+                   &SS});
 
     // ---- setup
     if (!need_src.empty()) {
@@ -802,18 +807,31 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     for (auto& e : S) sites += (double)e.g->geo.Vh;
     const double bSW = sweep_bytes(SW, 3 * bl), bSXR = sweep_bytes(SXR, 2 * bx + 5 * bl), bSS = sweep_bytes(SS, 4 * bl);
 
+    const double bH4f = hop_bytes(H4, SFL, LFL, 2), bSXRS = sweep_bytes(SXRS, 2 * bx + 6 * bl);
     auto iterate = [&](hipStream_t q) {
+        if (!fold) {
+            // bound by memory: alpha from the second hop's sums, x, r and s in one sweep, 2 spinor passes of
+            // 25 less (32^3x64 eight masses 42.7 -> 42.2 ms, 96 systems 31.4 -> 30.2 ms, 24^3x48 six masses at
+            // once 1.027 -> 1.076 of the former rate, BiCGstab-M 32^3x64 51.5 -> 47.4 ms)
+            run_hop(SFL, LFL, false, RED_NONE, FIN_STORE, H1, sys.d(), GATE_RUN, q, bH1);
+            run_hop(SFL, LFL, false, RED_ZDOT, FIN_BETA, H2, sys.d(), GATE_RUN, q, bH2);
+            run_sweep(OP_W, SFL, SW, sys.d(), GATE_RUN, q, bSW);
+            run_hop(SFL, LFL, false, RED_NONE, FIN_STORE, H3, sys.d(), GATE_RUN, q, bH1);
+            run_hop(SFL, LFL, false, RED_FULL, FIN_CHIALPHA, H4, sys.d(), GATE_RUN, q, bH4f);
+            run_sweep(OP_XRS, SFL, SXRS, sys.d(), GATE_RUN, q, bSXRS);
+            return;
+        }
         run_hop(SFL, LFL, false, RED_NONE, FIN_STORE, H1, sys.d(), GATE_RUN, q, bH1);
-        run_hop(SFL, LFL, false, RED_ZDOT, fold ? FIN_NONE : FIN_BETA, H2, sys.d(), GATE_RUN, q, bH2);
-        run_sweep(OP_W, SFL, SW, sys.d(), GATE_RUN, q, bSW, fold);
+        run_hop(SFL, LFL, false, RED_ZDOT, FIN_NONE, H2, sys.d(), GATE_RUN, q, bH2);
+        run_sweep(OP_W, SFL, SW, sys.d(), GATE_RUN, q, bSW, true);
         run_hop(SFL, LFL, false, RED_NONE, FIN_STORE, H3, sys.d(), GATE_RUN, q, bH1);
-        run_hop(SFL, LFL, false, RED_OUTX, fold ? FIN_NONE : FIN_CHI, H4, sys.d(), GATE_RUN, q, bH4);
-        run_sweep(OP_XR, SFL, SXR, sys.d(), GATE_RUN, q, bSXR, fold);
-        run_sweep(OP_S, SFL, SS, sys.d(), GATE_RUN, q, bSS, fold);
+        run_hop(SFL, LFL, false, RED_OUTX, FIN_NONE, H4, sys.d(), GATE_RUN, q, bH4);
+        run_sweep(OP_XR, SFL, SXR, sys.d(), GATE_RUN, q, bSXR, true);
+        run_sweep(OP_S, SFL, SS, sys.d(), GATE_RUN, q, bSS, true);
     };
     std::shared_ptr<ChunkGraph> graph;
     if (graphs_on())
-        graph = cached_graph(S[0].g, launch_key("eo", poll, SFL, LFL, sys.d(), H1, H2, SW, H3, H4, SXR, SS),
+        graph = cached_graph(S[0].g, launch_key("eo", poll, SFL, LFL, sys.d(), H1, H2, SW, H3, H4, SXR, SXRS, SS),
                              [&](hipStream_t q) {
                                  for (int k = 0; k < poll; k++) iterate(q);
                              });
@@ -835,7 +853,7 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         // the s update of the iteration in which the system stopped was gated off: apply it (the
         // scalars and the iterated residual of that iteration are still in place), since a continuing
         // reliable update keeps s; defect correction restarts with s = r instead
-        if (!dc) run_sweep(OP_S, SFL, SS, sys.d(), 1 << ST_SEL1, st, bSS);
+        if (!dc && fold) run_sweep(OP_S, SFL, SS, sys.d(), 1 << ST_SEL1, st, bSS);
         run_sweep(OP_INIT, SFL, Init, sys.d(), (1 << ST_SEL1) | (1 << ST_SEL2), st, init_bytes(Init, SFL, dc));
     };
 
@@ -1196,7 +1214,7 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     // the sweeps and the second hop of iteration i of a block, for the two orders of the buffers
     // (without shifts: one buffer, updated in place)
     struct Step {
-        JobTable<SweepJob> SW, SXR, SEND;
+        JobTable<SweepJob> SW, SXR, SXRS, SEND;
         JobTable<HopJob> HAw;
     };
     std::vector<Step> steps[2];
@@ -1221,18 +1239,23 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
             j.f[R_F5] = B.all();
             j.f[R_F6] = R1.all();
             S.SXR.host.push_back(j);
+            j.f[R_F5] = AS.all();
+            S.SXRS.host.push_back(j);
             j = sweep_job(0, nsites);
             j.f[R_F0] = Sv.all();
             j.f[R_F2] = AS.all();
             j.f[R_F3] = R1.all();
             S.SEND.host.push_back(j);
-            for (int p = 0; p < 2; p++) S.HAw.host.push_back(hop(W, AW, p, nullptr));
+            for (int p = 0; p < 2; p++) {
+                const SpinorRef z = B.half(p);  // (fused sweep)
+                S.HAw.host.push_back(hop(W, AW, p, &z));
+            }
             set_split(S.HAw);
             const int pn = 2 * (S.HAw.host[0].split ? split_blocks(geo.Vh) : nblk(geo.Vh));
             S.SW.host[0].pnblk = S.SXR.host[0].pnblk = pn;
-            for (auto* t : {&S.SW, &S.SXR, &S.SEND}) layout(*t);
+            for (auto* t : {&S.SW, &S.SXR, &S.SXRS, &S.SEND}) layout(*t);
             layout(S.HAw);
-            for (JobTableBase* t : {(JobTableBase*)&S.SW, (JobTableBase*)&S.SXR, (JobTableBase*)&S.SEND, (JobTableBase*)&S.HAw})
+            for (JobTableBase* t : {(JobTableBase*)&S.SW, (JobTableBase*)&S.SXR, (JobTableBase*)&S.SXRS, (JobTableBase*)&S.SEND, (JobTableBase*)&S.HAw})
                 tabs.push_back(t);
         }
     }
@@ -1257,9 +1280,14 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
     auto iterate = [&](const Step& S, hipStream_t q) {
         run_hop(SF64, L64, false, RED_ZDOT, fold ? FIN_NONE : FIN_BETA, HAs, sys.d(), GATE_RUN, q, bH);
         run_sweep(OP_W, SF64, S.SW, sys.d(), GATE_RUN, q, sweep_bytes(S.SW, 3 * 192), fold);
-        run_hop(SF64, L64, false, RED_OUTX, fold ? FIN_NONE : FIN_CHI, S.HAw, sys.d(), GATE_RUN, q, bHw);
-        run_sweep(OP_XR, SF64, S.SXR, sys.d(), GATE_RUN, q, sweep_bytes(S.SXR, 7 * 192), fold);
-        run_sweep(OP_S, SF64, S.SEND, sys.d(), GATE_RUN, q, sweep_bytes(S.SEND, 4 * 192), fold);
+        if (!fold) {  // as in the even-odd solver
+            run_hop(SF64, L64, false, RED_FULL, FIN_CHIALPHA, S.HAw, sys.d(), GATE_RUN, q, bH);
+            run_sweep(OP_XRS, SF64, S.SXRS, sys.d(), GATE_RUN, q, sweep_bytes(S.SXRS, 8 * 192));
+            return;
+        }
+        run_hop(SF64, L64, false, RED_OUTX, FIN_NONE, S.HAw, sys.d(), GATE_RUN, q, bHw);
+        run_sweep(OP_XR, SF64, S.SXR, sys.d(), GATE_RUN, q, sweep_bytes(S.SXR, 7 * 192), true);
+        run_sweep(OP_S, SF64, S.SEND, sys.d(), GATE_RUN, q, sweep_bytes(S.SEND, 4 * 192), true);
     };
     // between two looks at the status: whole blocks, about `poll` iterations
     const int blocks = std::max(1, poll / m);

@@ -51,6 +51,8 @@ enum Fin {
     FIN_RESTART = 5, // new residual: delta = <rhat, r>, |r|^2, status RUNNING
     FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>
     FIN_UPDATE = 8,  // FP64 residual update: |r|^2, finished or which way to go on
+    FIN_CHIALPHA = 9,  // chi, and alpha from <rhat, A w> (fused sweep OP_XRS)
+    FIN_RR = 10,     // |r|^2 of the fused sweep, status (+ the iteration's scalars for the shifts)
     FIN_CGB = 7,     // CG: beta = |r_new|^2 / |r|^2, status     (+ the iteration's scalars for the shifts)
 };
 
@@ -157,6 +159,7 @@ struct HopJob {
     // residual update (wd_update.hip): x_lo in z; the second hop's low-precision fields r, rhat, s, A s
     SpinorRef u_r, u_rh, u_s, u_as;
     int keep;            // residual update: the FP64 residual is stored whatever follows
+    int s_current;       // residual update: s is up to date (fused sweep OP_XRS)
     const void* links;   // the 8 links per site of this output parity
     const void* links_nb;  // full-lattice launches: those of the other parity (else NULL)
     long lcs;            // link chunk stride

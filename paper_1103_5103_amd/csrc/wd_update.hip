@@ -65,7 +65,8 @@ __device__ __forceinline__ void update_residual(const HopJob& J, const SysState*
     if (!on) return;
     const bool restart = S->dc || st == ST_BREAKDOWN;
     cx<T> r[12], q[12], rh[12];
-    if (!restart) {
+    if (!restart && J.s_current) load_spinor<SFL, T, NT>(J.u_rh, cb, rh);
+    else if (!restart) {
         // s <- r_{n+1} + alpha (s - chi A s) with the iterated residual, before it is replaced
         const cx<T> alpha = mk<T>((T)S->alpha.x, (T)S->alpha.y), chi = mk<T>((T)S->chi.x, (T)S->chi.y);
         cx<T> as[12];
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(BLOCK) void k_update(const HopJob* __restrict__ job
         stage_wait();
     }
     __syncthreads();
-    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double v[NRED] = {};
     if (cb < J.g.Vh) {
         cx<double> acc[12];
         const HopIn<SFI, true, SFA> hin{in, stg, base, nsl, TG && J.tg != 0, J.nc != 0, nullptr, add};
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_update_split(const HopJob* __
         }
     }
     __syncthreads();
-    double v[NRED] = {0.0, 0.0, 0.0, 0.0};
+    double v[NRED] = {};
     if (ok) {
         cx<double> acc[12];
         split_sum<double>(part, lane, acc);

@@ -60,3 +60,23 @@ def test_solve(dims, spinor, links):
         r = b - oracle.apply(U, 0.125, x.cpu().numpy(), dag=bool(kw.get("dagger")))
         assert st["status"] == 0 and np.linalg.norm(r) < 1e-9 * np.linalg.norm(b), (dims, kw, st)
         g.close()
+
+
+@pytest.mark.parametrize("spinor,links", [("f64", "f64"), ("f32", "f16"), ("f16", "f16")])
+def test_solve_above_the_folded_sizes(spinor, links):
+    """Just above the launches with folded finishers (294912 sites per parity, 1152 blocks): the
+    second hop's sums give alpha, and one sweep updates x, r and s."""
+    dims = (32, 32, 32, 18)
+    U, b = li.random_links(dims, 1.0, 1961), li.gaussian_field(dims, 2961)
+    g = wd.wd_gauge_create(_t(U), hint=_params(spinor, links))
+    for kw in (dict(delta=0.1), dict(delta=1e-3, defect_correction=True)):
+        p = _params(spinor, links, tol=1e-9, **kw)
+        x, st = wd.bicgstab_solve(g, 0.13, _t(b), p=p)
+        res = oracle.true_residual(U, 0.13, x.cpu().numpy(), b)
+        print(spinor, kw, st, res, flush=True)
+        assert st["status"] == 0 and res < 1e-9
+        if spinor == "f64":
+            xs, sts = wd.bicgstab_m_solve(g, [0.13, 0.12], _t(b), p=wd.params(tol=1e-9, mixed=False, eo=False))
+            assert all(oracle.true_residual(U, k, x.cpu().numpy(), b) < 1e-9 for k, x in zip([0.13, 0.12], xs))
+            break
+    g.close()
