@@ -140,26 +140,22 @@ wd_status wd_gauge_create(wd_gauge** out, const wd_geom* geom, const double* U, 
         {
             // decide whether the 12-real FP64 format is exact for these links
             const int nb = (G.Vh + BLOCK - 1) / BLOCK;
-            DevMem bm(sizeof(double) * nb);
-            double e = 0.0;
-            std::vector<double> h(nb);
-            for (int p = 0; p < 2; p++) {
-                WD_CHECK_HIP(launch_recon_check(g->lk(L64_18, p), G.Vh, G.stride, (double*)bm.p, s));
-                WD_CHECK_HIP(hipMemcpyAsync(h.data(), bm.p, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
-                WD_CHECK_HIP(hipStreamSynchronize(s));
-                for (double v : h) e = std::max(e, std::isfinite(v) ? v : 1.0);
+            DevMem bm(sizeof(double) * 4 * nb);
+            std::vector<double> h(4 * nb);
+            for (int k = 0; k < 4; k++)  // both parities of the reconstruction's error, then of |u00|
+                WD_CHECK_HIP(launch_recon_check(g->lk(L64_18, k & 1), G.Vh, G.stride, (double*)bm.p + k * (size_t)nb, s, k >> 1));
+            WD_CHECK_HIP(hipMemcpyAsync(h.data(), bm.p, sizeof(double) * 4 * nb, hipMemcpyDeviceToHost, s));
+            WD_CHECK_HIP(hipStreamSynchronize(s));
+            double e = 0.0, u = 0.0;
+            for (int k = 0; k < 2 * nb; k++) {
+                e = std::max(e, std::isfinite(h[k]) ? h[k] : 1.0);
+                u = std::max(u, std::isfinite(h[2 * nb + k]) ? h[2 * nb + k] : 1.0);
             }
             g->recon_err = e;
-            double u = 0.0;
-            for (int p = 0; p < 2; p++) {
-                WD_CHECK_HIP(launch_recon_check(g->lk(L64_18, p), G.Vh, G.stride, (double*)bm.p, s, 1));
-                WD_CHECK_HIP(hipMemcpyAsync(h.data(), bm.p, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
-                WD_CHECK_HIP(hipStreamSynchronize(s));
-                for (double v : h) u = std::max(u, std::isfinite(v) ? v : 1.0);
-            }
             g->u00_max = u;
             const bool tg_on = hint && hint->temporal_gauge;
             if (e < 1e-12) {
+                if (hint && hint->mixed) g->reserve_links({L64_12, link_fmt_of(hint->link_store, hint->recon)});
                 if (tg_on) g->build_temporal_gauge(U, s);
                 else g->ensure_links(L64_12, s);
             }
@@ -168,6 +164,7 @@ wd_status wd_gauge_create(wd_gauge** out, const wd_geom* geom, const double* U, 
             throw Error{WD_ERR_ARG, "gamma_basis must be 0 (chiral) or 1 (non-chiral)"};
         g->nc = hint && hint->gamma_basis == 1 ? 1 : 0;
         if (hint && hint->mixed) g->ensure_slinks(link_fmt_of(hint->link_store, hint->recon), s);
+        g->link_room.reset();
         WD_CHECK_HIP(hipStreamSynchronize(s));
         *out = g.release();
         return WD_OK;

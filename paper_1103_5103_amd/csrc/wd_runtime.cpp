@@ -24,7 +24,7 @@ DevMem::DevMem(size_t n) : bytes(n)
 }
 DevMem::~DevMem()
 {
-    if (p) (void)hipFree(p);
+    if (p && !owner) (void)hipFree(p);
 }
 
 size_t field_bytes(int sf, int halves, long stride)
@@ -464,6 +464,33 @@ static size_t link_bytes(int lf, long stride)
     return (size_t)2 * 8 * link_chunks(lf) * link_chunk_bytes(lf) * stride;
 }
 
+static size_t room_of(size_t bytes)
+{
+    constexpr size_t align = 4096;
+    return (bytes + align - 1) / align * align;
+}
+
+void wd_gauge::reserve_links(std::initializer_list<int> fmts)
+{
+    size_t total = 0;
+    for (int lf : fmts) total += room_of(link_bytes(lf, geo.stride));
+    try {
+        link_room = std::make_shared<DevMem>(total);
+        link_used = 0;
+    } catch (const Error& e) {
+        if (e.code != WD_ERR_OOM) throw;
+    }
+}
+
+std::unique_ptr<DevMem> wd_gauge::new_links(int lf)
+{
+    const size_t n = link_bytes(lf, geo.stride);
+    if (!link_room || link_used + n > link_room->bytes) return std::make_unique<DevMem>(n);
+    auto m = std::make_unique<DevMem>(link_room, link_used, n);
+    link_used += room_of(n);
+    return m;
+}
+
 void wd_gauge::ensure_links(int lf, hipStream_t s)
 {
     if (links[lf]) return;
@@ -475,7 +502,7 @@ void wd_gauge::ensure_links(int lf, hipStream_t s)
             throw Error{WD_ERR_UNSUPPORTED, "a link has |u00| = 1 to within 1e-6 (e.g. unit links): the 8-real "
                                             "format cannot rebuild it; use recon 12"};
     }
-    auto m = std::make_unique<DevMem>(link_bytes(lf, geo.stride));
+    auto m = new_links(lf);
     const size_t half = m->bytes / 2;
     for (int p = 0; p < 2; p++)
         WD_CHECK_HIP(launch_convert_links(lf, L64_18, lk(L64_18, p), (char*)m->p + p * half, geo.Vh, geo.stride, s));
@@ -493,7 +520,7 @@ void wd_gauge::ensure_slinks(int lf, hipStream_t s)
                                         "format cannot rebuild; use recon 12"};
     if (fixed[lf]) return;
     // every other format is converted from the transformed 12-real FP64 links (exact for SU(3))
-    auto m = std::make_unique<DevMem>(link_bytes(lf, geo.stride));
+    auto m = new_links(lf);
     const size_t half = m->bytes / 2;
     for (int p = 0; p < 2; p++)
         WD_CHECK_HIP(launch_convert_links(lf, L64_12, slk(L64_12, p), (char*)m->p + p * half, geo.Vh, geo.stride, s));
@@ -510,7 +537,7 @@ void wd_gauge::build_temporal_gauge(const double* U, hipStream_t s)
         WD_CHECK_HIP(hipMemsetAsync(f18.p, 0, f18.bytes, s));
         WD_CHECK_HIP(launch_temporal_gauge(U, geo, (double*)gmat->p, (double*)Uf.p, s));
         WD_CHECK_HIP(launch_pack_links((const double*)Uf.p, geo, f18.p, (char*)f18.p + f18.bytes / 2, geo.stride, s));
-        auto m = std::make_unique<DevMem>(link_bytes(L64_12, geo.stride));
+        auto m = new_links(L64_12);
         const size_t half = m->bytes / 2;
         for (int p = 0; p < 2; p++)
             WD_CHECK_HIP(launch_convert_links(L64_12, L64_18, (const char*)f18.p + p * (f18.bytes / 2),
@@ -533,6 +560,38 @@ Field& wd_gauge::field(const std::string& key, int sf, int halves)
     WD_CHECK_HIP(hipMemset(f.mem->p, 0, f.mem->bytes));
     ws[key] = f;
     return ws[key];
+}
+
+void wd_gauge::reserve(const std::vector<FieldSpec>& fields)
+{
+    std::map<int, std::vector<const FieldSpec*>> missing;  // by format: a change of the iteration's gives its part back
+    for (const FieldSpec& f : fields) {
+        auto it = ws.find(f.key);
+        if (it == ws.end() || it->second.sf != f.sf || it->second.halves != f.halves) missing[f.sf].push_back(&f);
+    }
+    for (auto& kv : missing) {
+        size_t total = 0;
+        for (const FieldSpec* f : kv.second) total += room_of(field_bytes(f->sf, f->halves, geo.stride));
+        if (kv.second.size() < 2) continue;
+        std::shared_ptr<DevMem> whole;
+        try {
+            whole = std::make_shared<DevMem>(total);
+        } catch (const Error& e) {
+            if (e.code != WD_ERR_OOM) throw;
+            return;
+        }
+        WD_CHECK_HIP(hipMemset(whole->p, 0, total));
+        size_t off = 0;
+        for (const FieldSpec* k : kv.second) {
+            Field f;
+            f.sf = k->sf;
+            f.halves = k->halves;
+            f.stride = geo.stride;
+            f.mem = std::make_shared<DevMem>(whole, off, field_bytes(f.sf, f.halves, geo.stride));
+            off += room_of(f.mem->bytes);
+            ws[k->key] = f;
+        }
+    }
 }
 
 void* wd_gauge::rawbuf(const std::string& key, size_t bytes)

@@ -580,6 +580,19 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     // systems on the same gauge field share link loads (multi-RHS hop or interleaved block pairs)
     std::vector<int> tile_lo(n), tile_64(n);
     const int rhs_lo = tune_shared_hops(S, SFL, LFL, L64, st, tile_lo, tile_64);
+    std::map<wd_gauge*, std::vector<wd_gauge::FieldSpec>> need;
+    for (auto& e : S) {
+        auto& v = need[e.g];
+        const std::string k = "eo" + std::to_string(e.slot) + ".";
+        if (!e.src.B64.mem) v.insert(v.end(), {{k + "B64", SF64, 2}, {k + "HB", SF64, 1}});
+        if (!e.X64.mem) v.push_back({k + "X64", SF64, 2});
+        if (!e.BP.mem) v.push_back({k + "BP", SF64, 1});
+        if (!e.RH.mem) v.push_back({k + "RH", SF64, 1});
+        v.push_back({k + "T64", SF64, 1});
+        for (const char* f : {"r", "rh", "s", "w", "As", "Aw", "tmp"}) v.push_back({k + f, SFL, 1});
+        v.push_back({k + "xl", SFX, 1});
+    }
+    for (auto& f : need) f.first->reserve(f.second);
     for (auto& e : S) {
         e.g->ensure_slinks(LFL, st);
         e.g->ensure_slinks(L64, st);
@@ -1146,6 +1159,15 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
             mass_of_shift.push_back(i);
         }
 
+    {
+        std::vector<wd_gauge::FieldSpec> need;
+        for (const char* f : {"B", "X", "S", "AS", "AW"}) need.push_back({std::string("ms.") + f, SF64, 2});
+        for (int k = 0; k < ns; k++)
+            need.insert(need.end(), {{"ms.XS" + std::to_string(k), SF64, 2}, {"ms.SS" + std::to_string(k), SF64, 2}});
+        for (int j = 0; j <= (ns > 0 ? SHIFT_BLOCK : 0); j++) need.push_back({"ms.R" + std::to_string(j), SF64, 2});
+        for (int j = 0; j < (ns > 0 ? SHIFT_BLOCK : 1); j++) need.push_back({"ms.W" + std::to_string(j), SF64, 2});
+        g->reserve(need);
+    }
     Field B = g->field("ms.B", SF64, 2), X = g->field("ms.X", SF64, 2);
     Field Sv = g->field("ms.S", SF64, 2), AS = g->field("ms.AS", SF64, 2);
     Field AW = g->field("ms.AW", SF64, 2);
@@ -1682,6 +1704,12 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
     }
     // the source is packed once and 1/2 D_eo b_o is shared by all masses; every mass keeps its
     // FP64 solution so that the next start vector is a combination of them in the internal layout
+    {
+        std::vector<wd_gauge::FieldSpec> need{{"mm.B64", SF64, 2}, {"mm.HB", SF64, 1}, {"mm.BP", SF64, 1}};
+        for (int i = 0; i < n; i++)
+            need.insert(need.end(), {{"mm.X" + std::to_string(i), SF64, 2}, {"mm.R" + std::to_string(i), SF64, 1}});
+        g->reserve(need);
+    }
     EoSource src;
     prepare_source(g, "mm.", b, P.dagger, src, st);
     // and its final FP64 residual b_prec - M_prec x_e (for the next start residual)
@@ -1894,6 +1922,18 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
     // systems on the same gauge field share link loads (multi-RHS hop or interleaved block pairs)
     std::vector<int> tile_lo(n), tile_64(n);
     const int rhs_lo = tune_shared_hops(S, SFL, LFL, L64, st, tile_lo, tile_64);
+    std::map<wd_gauge*, std::vector<wd_gauge::FieldSpec>> need;
+    for (auto& e : S) {
+        auto& v = need[e.g];
+        const std::string k = "cg" + std::to_string(e.slot) + ".";
+        if (!e.src.B64.mem) v.insert(v.end(), {{k + "B64", SF64, 2}, {k + "HB", SF64, 1}});
+        if (!e.X64.mem) v.push_back({k + "X64", SF64, 2});
+        if (!e.RH.mem) v.push_back({k + "RH", SF64, 1});
+        v.insert(v.end(), {{k + "T64", SF64, 1}, {k + "V64", SF64, 1}});
+        for (const char* f : {"r", "p", "t", "v", "w"}) v.push_back({k + f, SFL, 1});
+        v.push_back({k + "xl", SFX, 1});
+    }
+    for (auto& f : need) f.first->reserve(f.second);
     for (auto& e : S) {
         e.g->ensure_slinks(LFL, st);
         e.g->ensure_slinks(L64, st);
@@ -2225,6 +2265,16 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
     const Geo& geo = g->geo;
     const int L64 = g->f64_links();
     g->ensure_slinks(L64, st);
+    {
+        std::vector<wd_gauge::FieldSpec> need{{"cgm.B", SF64, 2}};
+        for (const char* f : {"p", "t", "v", "w"}) need.push_back({std::string("cgm.") + f, SF64, 1});
+        for (int i = 0; i < n; i++) need.push_back({"cgm.X" + std::to_string(i), SF64, 2});
+        for (int k = 0; k < ns; k++) need.push_back({"cgm.P" + std::to_string(k), SF64, 1});
+        for (int j = 0; j <= (ns > 0 ? SHIFT_BLOCK : 0); j++) need.push_back({"cgm.R" + std::to_string(j), SF64, 1});
+        for (int i = 0; i < n; i++)
+            for (const char* f : {"RT", "RV", "RR"}) need.push_back({std::string("cgm.") + f + std::to_string(i), SF64, 1});
+        g->reserve(need);
+    }
     Field B = g->field("cgm.B", SF64, 2);
     std::vector<Field> X(n), PS(ns);
     for (int i = 0; i < n; i++) X[i] = g->field("cgm.X" + std::to_string(i), SF64, 2);
@@ -2490,6 +2540,12 @@ wd_status solve_normal(wd_gauge* g, double kappa, int n, const double* sigmas, d
         }
         if (e.final_status != WD_OK && worst == WD_OK) worst = (wd_status)e.final_status;
     };
+    {
+        std::vector<wd_gauge::FieldSpec> need{{"nm.B64", SF64, 2}, {"nm.HB", SF64, 1}};
+        for (int i = 0; i < n && method == WD_METHOD_SEQUENTIAL; i++)
+            need.insert(need.end(), {{"nm.X" + std::to_string(i), SF64, 2}, {"nm.R" + std::to_string(i), SF64, 1}});
+        g->reserve(need);
+    }
     EoSource src;
     prepare_source(g, "nm.", b, 0, src, st);
     wd_status worst = WD_OK;
