@@ -149,10 +149,10 @@ wd_status wd_apply_dag(wd_gauge* g, double kappa, double* out, const double* in,
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation): out = M(kappa) in (dagger = 0) or M(kappa)^dag in
  * (dagger = 1), bitwise the result of wd_apply / wd_apply_dag, with no device or pinned
- * allocation, no host-to-device copy and no synchronisation. The packed fields and the job table
- * live in a fixed device array of 64 MiB per GPU that the library holds until the process ends;
- * it fits lattices of at most 87,296 sites per parity after rounding V/2 up to a multiple of 256
- * (16^3 x 32 fits, 24^4 does not); larger lattices give WD_ERR_ARG. Every call on one GPU uses
+ * allocation, no host-to-device copy and no synchronisation. A fixed device array of 64 MiB per GPU,
+ * which the library holds until the process ends, takes a copy of the input where it overlaps the
+ * output; lattices of at most 87,296 sites per parity after rounding V/2 up to a multiple of 256
+ * are accepted (16^3 x 32 is, 24^4 is not); larger ones give WD_ERR_ARG. Every call on one GPU uses
  * that GPU's array: calls that overlap on one GPU (other streams or threads) race, so serialise
  * them. in, out: device [V][3][4] complex128, distinct. Asynchronous on `stream`.
  */

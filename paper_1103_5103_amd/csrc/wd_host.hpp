@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <map>
 #include <memory>
 #include <string>
@@ -201,15 +202,19 @@ struct Reports {
     View wait(int i, F&& ok) const
     {
         bool drained = false;
+        std::chrono::steady_clock::time_point since;
         for (long n = 1;; n++) {
             const View v = get(i);
             if (ok(v)) return v;
-            if (drained) throw Error{WD_ERR_HIP, "the stream ended without the report of system " + std::to_string(i)};
-            drained = pause(n);
+            if (!drained) {
+                drained = pause(n);
+                since = std::chrono::steady_clock::now();
+            } else if (std::chrono::steady_clock::now() - since > std::chrono::seconds(1)) {  // (a report may become visible after the stream's end does)
+                throw Error{WD_ERR_HIP, "the stream ended without the report of system " + std::to_string(i)};
+            }
         }
     }
-    // a moment's wait, now and then a look at the stream; true: it had drained (a report that was to come
-    // is there at the next look)
+    // a moment's wait, now and then a look at the stream; true: it had drained
     bool pause(long n) const;
 };
 

@@ -975,15 +975,17 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
                 w.verify = false;
                 any_resume = true;
             } else if (v.status == ST_RUNNING) {
-                w.verify = false;  // (another system's resume has taken it along)
+                w.verify = false;
             } else {
                 w.nrel++;
                 w.verify = v.status == ST_CONVERGED || v.status == ST_MAXIT;
                 any_update = true;
             }
         }
-        if (any_update) reliable_update();
+        // in this order: a system whose update now fails the check must wait for its own resume, which the
+        // host has seen to be due, or it would run ahead of what the host expects of it
         if (any_resume) resume();
+        if (any_update) reliable_update();
     }
     for (int i = 0; i < n; i++) {
         const Reports::View v = rep.get(slot0 + i);
