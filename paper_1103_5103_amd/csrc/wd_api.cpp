@@ -176,7 +176,7 @@ wd_status wd_gauge_destroy(wd_gauge* g)
     return guarded([&]() -> wd_status {
         if (!g) return WD_ERR_ARG;
         if (g->stream) (void)hipStreamSynchronize(g->stream);
-        (void)hipDeviceSynchronize();
+        if (hipDeviceSynchronize() == hipSuccess) g->retire();
         delete g;
         return WD_OK;
     });

@@ -32,14 +32,27 @@ void set_error(const std::string& msg);
     } while (0)
 
 // ---------------------------------------------------------------- device memory
+// A device allocation. Those of a destroyed handle (retire) are kept for the next handle's of the same size,
+// up to 1 GiB a process, the oldest given back first and all of them when an allocation fails: what is
+// given back to the driver it wipes at some 25 GB/s, and a program that makes a handle for every step of a
+// training loop waits for that in the long run (16^3x32 forward and backward
+// 4.0 ms, 15.7 ms where memory has been through many hands; with the list 3.1 ms).
 struct DevMem {
     void* p = nullptr;
     size_t bytes = 0;
     std::shared_ptr<DevMem> owner;  // set: this is a part of another allocation, which it keeps alive
+    int dev = -1;
+    bool retired = false;
     DevMem() = default;
     explicit DevMem(size_t n);
     DevMem(const std::shared_ptr<DevMem>& whole, size_t off, size_t n) : p((char*)whole->p + off), bytes(n), owner(whole) {}
     ~DevMem();
+    // no work on device `cur` uses the allocation any more: keep it for another handle when it is destroyed
+    void retire(int cur)
+    {
+        DevMem& m = owner ? *owner : *this;
+        m.retired = m.dev == cur;
+    }
     DevMem(const DevMem&) = delete;
     DevMem& operator=(const DevMem&) = delete;
 };
@@ -153,7 +166,7 @@ struct wd_gauge {
     wd::Field& field(const std::string& key, int sf, int halves);
     // The missing ones of these fields in one allocation per format, zeroed: giving memory back takes
     // about 0.24 ms an allocation (of 25 MB or more), whatever its size. 16^3x32 forward and backward
-    // with a handle of its own: 8.2 ms with an allocation per field, of which 3.3 ms for giving 16 of
+    // with a handle of its own: 7.0 ms with an allocation per field, of which 3.3 ms for giving 16 of
     // them back; 4.0 ms so.
     // Where the device does not have it in one piece, field() allocates them one by one.
     struct FieldSpec {
@@ -170,6 +183,7 @@ struct wd_gauge {
     void ensure_links(int lf, hipStream_t s);
     void build_temporal_gauge(const double* U, hipStream_t s);  // U: the caller's canonical links
     size_t device_bytes() const;
+    void retire();  // the device is idle and the handle about to be destroyed
 };
 
 namespace wd {

@@ -12,10 +12,63 @@ static thread_local std::string g_last_error;
 void set_error(const std::string& msg) { g_last_error = msg; }
 const std::string& last_error() { return g_last_error; }
 
+// Allocations of destroyed handles (DevMem::retire). The list itself is never destroyed: handles may outlive
+// static objects at the end of the process.
+constexpr size_t kSpareBytes = (size_t)1 << 30, kSpareMin = (size_t)1 << 20;
+struct Spare {
+    void* p;
+    size_t bytes;
+    int dev;
+};
+static std::mutex g_spare_mu;
+static std::vector<Spare>& spares()
+{
+    static auto* v = new std::vector<Spare>;
+    return *v;
+}
+static void* take_spare(size_t n, int dev)
+{
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    auto& v = spares();
+    for (size_t i = 0; i < v.size(); i++)
+        if (v[i].bytes == n && v[i].dev == dev) {
+            void* p = v[i].p;
+            v.erase(v.begin() + i);
+            return p;
+        }
+    return nullptr;
+}
+// keeps p (or gives it back), and gives the oldest back until at most `limit` bytes are kept
+static void keep_spare(void* p, size_t n, int dev, size_t limit)
+{
+    std::vector<Spare> out;
+    {
+        std::lock_guard<std::mutex> lk(g_spare_mu);
+        auto& v = spares();
+        out.reserve(v.size() + 1);  // (nothing may throw once p is in the list)
+        if (p) v.push_back({p, n, dev});
+        size_t total = 0;
+        for (auto& s : v) total += s.bytes;
+        while (total > limit) {
+            out.push_back(v.front());
+            total -= v.front().bytes;
+            v.erase(v.begin());
+        }
+    }
+    for (auto& s : out) (void)hipFree(s.p);
+}
+
 DevMem::DevMem(size_t n) : bytes(n)
 {
     if (n == 0) return;
+    WD_CHECK_HIP(hipGetDevice(&dev));
+    if (n >= kSpareMin && (p = take_spare(n, dev))) return;
     hipError_t e = hipMalloc(&p, n);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        keep_spare(nullptr, 0, 0, 0);
+        e = hipMalloc(&p, n);
+    }
     if (e != hipSuccess) {
         p = nullptr;
         (void)hipGetLastError();
@@ -24,9 +77,16 @@ DevMem::DevMem(size_t n) : bytes(n)
 }
 DevMem::~DevMem()
 {
-    if (p && !owner) (void)hipFree(p);
+    if (!p || owner) return;
+    if (retired && bytes >= kSpareMin && bytes <= kSpareBytes) {
+        try {
+            keep_spare(p, bytes, dev, kSpareBytes);
+            return;
+        } catch (...) {  // (the list could not grow)
+        }
+    }
+    (void)hipFree(p);
 }
-
 size_t field_bytes(int sf, int halves, long stride)
 {
     size_t n = (size_t)16 * spinor_chunks(sf) * halves * stride;
@@ -602,6 +662,20 @@ void* wd_gauge::rawbuf(const std::string& key, size_t bytes)
     WD_CHECK_HIP(hipMemset(m->p, 0, m->bytes));
     raw[key] = m;
     return m->p;
+}
+
+void wd_gauge::retire()
+{
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess) return;
+    for (auto& l : links)
+        if (l) l->retire(cur);
+    for (auto& l : fixed)
+        if (l) l->retire(cur);
+    if (gmat) gmat->retire(cur);
+    for (auto& kv : ws) kv.second.mem->retire(cur);
+    for (auto& kv : raw)
+        if (kv.second) kv.second->retire(cur);
 }
 
 size_t wd_gauge::device_bytes() const
