@@ -411,8 +411,9 @@ def memory_by_method(torch, wd, U, bd, kappas, p_mixed, p_f64, dev):
         V *= int(d)
     full64 = V * 192
     n = len(kappas)
-    out["note"] = (f"one full FP64 field = {full64} B; BiCGstab-M workspaces hold 9 + 2 (n - 1) = {9 + 2 * (n - 1)} "
-                   f"full FP64 fields for n = {n} masses (x, s per shifted system); the single-mass solver a fixed "
+    out["note"] = (f"one full FP64 field = {full64} B; BiCGstab-M workspaces hold 22 + 2 (n - 1) = {22 + 2 * (n - 1)} "
+                   f"full FP64 fields for n = {n} masses (x, s per shifted system, "
+                   f"and the r and w of 8 iterations); the single-mass solver a fixed "
                    f"set of half fields per system, the sequential driver also n FP64 solutions and n FP64 even "
                    f"residuals for its start guesses")
     return out
