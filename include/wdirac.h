@@ -138,6 +138,9 @@ void wd_params_default(wd_solver_params* p);
  */
 wd_status wd_gauge_create(wd_gauge** g, const wd_geom* geom, const double* U,
                           const wd_solver_params* storage_hint, void* stream);
+/* Waits for the current device. Of the handle's device memory at most 1 GiB a process is kept for the next
+   handle with allocations of the same sizes (the oldest is given back first, all of it when an allocation
+   of the library fails); the rest is given back at once. */
 wd_status wd_gauge_destroy(wd_gauge* g);
 
 /* out = M(kappa) in  (Sec. 2, eq. 3 and 4; FP64). in, out: device [V][3][4] complex128, distinct. */
