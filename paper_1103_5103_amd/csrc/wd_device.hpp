@@ -272,6 +272,33 @@ __device__ __forceinline__ void store_spinor(const SpinorRef& r, long i, const c
     }
 }
 
+// A site's values as a field of storage format SF holds them
+template <int SF, class T> struct Stored {
+    float inv = 0.f, n = 0.f;
+    __device__ __forceinline__ explicit Stored(const cx<T> v[12])
+    {
+        if constexpr (SF == SF16) {
+            float m = 0.f;
+#pragma unroll
+            for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
+            inv = f16_site_inv(m);
+            n = inv == 0.f && m < 1.0f ? 0.f : m;
+        }
+    }
+    __device__ __forceinline__ cx<T> operator()(cx<T> a) const
+    {
+        if constexpr (SF == SF16) return mk<T>((float)(_Float16)(a.re * inv) * n, (float)(_Float16)(a.im * inv) * n);
+        else return a;
+    }
+};
+template <int SF, class T>
+__device__ __forceinline__ void as_stored(cx<T> v[12])
+{
+    const Stored<SF, T> st(v);
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = st(v[k]);
+}
+
 // ---------------------------------------------------------------- LDS staging of input sites
 // A hop block covers BLOCK consecutive checkerboard sites, i.e. whole rows of constant (y, z, t)
 // when Xh divides BLOCK. Its x neighbours lie in the same rows and its y neighbours one row up
@@ -601,7 +628,7 @@ __device__ __forceinline__ void store_link(void* base, long lcs, int k, long i, 
 
 // ---------------------------------------------------------------- reductions
 constexpr int BLOCK = BLOCK_SITES;
-constexpr int NRED = 6;
+constexpr int NRED = 7;
 
 __device__ __forceinline__ double wave_sum(double v)
 {

@@ -28,6 +28,25 @@ __device__ __forceinline__ void write_partials(double v[NRED], SysState* S, int 
     }
 }
 
+// RED_FULL on one site: <out, x0>, |out|^2, <z, out> and <z, x0> (z = rhat, out = A w, x0 = w). FIN_CHIALPHA
+// forms <rhat, w - chi A w> from the last two, so they take out as the next sweep will read it.
+template <int SF, class T>
+__device__ __forceinline__ void full_sums(const cx<T> z[12], const cx<T> out[12], const cx<T> x0[12], double v[NRED])
+{
+    const Stored<SF, T> st(out);
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        v[0] += (double)out[k].re * x0[k].re + (double)out[k].im * x0[k].im;
+        v[1] += (double)out[k].re * x0[k].im - (double)out[k].im * x0[k].re;
+        v[2] += (double)out[k].re * out[k].re + (double)out[k].im * out[k].im;
+        const cx<T> q = st(out[k]);
+        v[3] += (double)z[k].re * q.re + (double)z[k].im * q.im;
+        v[4] += (double)z[k].re * q.im - (double)z[k].im * q.re;
+        v[5] += (double)z[k].re * x0[k].re + (double)z[k].im * x0[k].im;
+        v[6] += (double)z[k].re * x0[k].im - (double)z[k].im * x0[k].re;
+    }
+}
+
 // job of block b: jobs are sorted by blk0
 template <class J>
 __device__ __forceinline__ int find_job(const J* jobs, int njobs, int b)
@@ -408,28 +427,23 @@ __global__ __launch_bounds__(BLOCK) void k_hop(
                 v[0] += (double)z[k].re * acc[k].re + (double)z[k].im * acc[k].im;
                 v[1] += (double)z[k].re * acc[k].im - (double)z[k].im * acc[k].re;
             }
-        } else if constexpr (RED == RED_OUTX || RED == RED_FULL) {
+        } else if constexpr (RED == RED_OUTX) {
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 v[0] += (double)acc[k].re * x0[k].re + (double)acc[k].im * x0[k].im;
                 v[1] += (double)acc[k].re * x0[k].im - (double)acc[k].im * x0[k].re;
                 v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
             }
-            if constexpr (RED == RED_FULL) {
-                cx<T> z[12];
-                load_spinor<SF, T, NTL || FULL>(J.z, cb, z);
-#pragma unroll
-                for (int k = 0; k < 12; k++) {
-                    v[3] += (double)z[k].re * acc[k].re + (double)z[k].im * acc[k].im;
-                    v[4] += (double)z[k].re * acc[k].im - (double)z[k].im * acc[k].re;
-                }
-            }
+        } else if constexpr (RED == RED_FULL) {
+            cx<T> z[12];
+            load_spinor<SF, T, NTL || FULL>(J.z, cb, z);
+            full_sums<SF, T>(z, acc, x0, v);
         } else if constexpr (RED == RED_NORM) {
 #pragma unroll
             for (int k = 0; k < 12; k++) v[2] += (double)acc[k].re * acc[k].re + (double)acc[k].im * acc[k].im;
         }
     }
-    if constexpr (RED != RED_NONE) write_partials<RED == RED_FULL ? 5 : 3>(v, S, J.rblk0 + lb, J.p2 != 0);
+    if constexpr (RED != RED_NONE) write_partials<RED == RED_FULL ? NRED : 3>(v, S, J.rblk0 + lb, J.p2 != 0);
 }
 
 // The hop for launches that leave the chip mostly idle (up to kSplitSites sites, one system): such a

@@ -6,7 +6,7 @@
 
 namespace wd {
 
-// RED_FULL: <out, x0>, |out|^2 and <z, out>
+// RED_FULL: <out, x0>, |out|^2, <z, out> and <z, x0>
 enum HopRed { RED_NONE = 0, RED_ZDOT = 1, RED_OUTX = 2, RED_NORM = 3, RED_FULL = 4 };
 enum SweepOp { OP_W = 0, OP_XR = 1, OP_S = 2, OP_INIT = 4, OP_ACC = 5, OP_NORM = 6, OP_MSINIT = 7, OP_AXPY = 8,
                OP_LINCOMB = 9, OP_CGX = 10, OP_CGP = 11, OP_XRS = 12 };

@@ -144,22 +144,17 @@ __global__ __launch_bounds__(BLOCK) void k_hop_mrhs(const HopJob* __restrict__ j
                     v[k][0] += (double)zz[c].re * acc[k][c].re + (double)zz[c].im * acc[k][c].im;
                     v[k][1] += (double)zz[c].re * acc[k][c].im - (double)zz[c].im * acc[k][c].re;
                 }
-            } else if constexpr (RED == RED_OUTX || RED == RED_FULL) {
+            } else if constexpr (RED == RED_OUTX) {
 #pragma unroll
                 for (int c = 0; c < 12; c++) {
                     v[k][0] += (double)acc[k][c].re * x0[c].re + (double)acc[k][c].im * x0[c].im;
                     v[k][1] += (double)acc[k][c].re * x0[c].im - (double)acc[k][c].im * x0[c].re;
                     v[k][2] += (double)acc[k][c].re * acc[k][c].re + (double)acc[k][c].im * acc[k][c].im;
                 }
-                if constexpr (RED == RED_FULL) {
-                    cx<T> zz[12];
-                    load_spinor<SF, T>(J.z, cb, zz);
-#pragma unroll
-                    for (int c = 0; c < 12; c++) {
-                        v[k][3] += (double)zz[c].re * acc[k][c].re + (double)zz[c].im * acc[k][c].im;
-                        v[k][4] += (double)zz[c].re * acc[k][c].im - (double)zz[c].im * acc[k][c].re;
-                    }
-                }
+            } else if constexpr (RED == RED_FULL) {
+                cx<T> zz[12];
+                load_spinor<SF, T>(J.z, cb, zz);
+                full_sums<SF, T>(zz, acc[k], x0, v[k]);
             } else if constexpr (RED == RED_NORM) {
 #pragma unroll
                 for (int c = 0; c < 12; c++)
@@ -171,7 +166,7 @@ __global__ __launch_bounds__(BLOCK) void k_hop_mrhs(const HopJob* __restrict__ j
         // block-uniform conditions: every thread of the block takes the same branches
 #pragma unroll
         for (int k = 0; k < KT; k++)
-            if (run[k]) write_partials<RED == RED_FULL ? 5 : 3>(v[k], sys + jobs[j0 + k].sys, jobs[j0 + k].rblk0 + lb, jobs[j0 + k].p2 != 0);
+            if (run[k]) write_partials<RED == RED_FULL ? NRED : 3>(v[k], sys + jobs[j0 + k].sys, jobs[j0 + k].rblk0 + lb, jobs[j0 + k].p2 != 0);
     }
 }
 

@@ -419,7 +419,7 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     }
     if (timed)
         T.pending.push_back({cls, a, b, bytes, (int)(flag - T.dflags), t.n(), cls == TK_HOP_LO ? TK_HOP_LO_RED + red : -1});
-    if (red != RED_NONE && fin != FIN_NONE) run_finish(red == RED_FULL ? 5 : 3, fin, t, sys, gated, s);
+    if (red != RED_NONE && fin != FIN_NONE) run_finish(red == RED_FULL ? NRED : 3, fin, t, sys, gated, s);
 }
 
 void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s)

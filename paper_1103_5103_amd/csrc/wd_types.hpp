@@ -51,7 +51,7 @@ enum Fin {
     FIN_RESTART = 5, // new residual: delta = <rhat, r>, |r|^2, status RUNNING
     FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>
     FIN_UPDATE = 8,  // FP64 residual update: |r|^2, finished or which way to go on
-    FIN_CHIALPHA = 9,  // chi, and alpha from <rhat, A w> (fused sweep OP_XRS)
+    FIN_CHIALPHA = 9,  // chi, delta' and alpha from the second hop's sums (fused sweep OP_XRS)
     FIN_RR = 10,     // |r|^2 of the fused sweep, status (+ the iteration's scalars for the shifts)
     FIN_CGB = 7,     // CG: beta = |r_new|^2 / |r|^2, status     (+ the iteration's scalars for the shifts)
 };

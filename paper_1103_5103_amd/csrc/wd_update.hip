@@ -18,22 +18,6 @@
 
 namespace wd {
 
-// v as a field of storage format SF holds it
-template <int SF, class T>
-__device__ __forceinline__ void as_stored(cx<T> v[12])
-{
-    if constexpr (SF == SF16) {
-        float m = 0.f;
-#pragma unroll
-        for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
-        const float inv = f16_site_inv(m);
-        const float n = inv == 0.f && m < 1.0f ? 0.f : m;
-#pragma unroll
-        for (int k = 0; k < 12; k++)
-            v[k] = mk<T>((float)(_Float16)(v[k].re * inv) * n, (float)(_Float16)(v[k].im * inv) * n);
-    }
-}
-
 // keeps the next part's loads from being issued before this part is done (all at once they would spill)
 __device__ __forceinline__ void part_done() { asm volatile("" ::: "memory"); }
 
