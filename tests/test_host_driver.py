@@ -1,0 +1,145 @@
+"""CPU checks of the library's host code against a stand-in for the device (no GPU).
+
+tests/host_driver_probe.cpp replaces the HIP runtime and the kernels: device memory with a capacity and
+range checks, a queue in place of the stream, and scripted ends of iterations and FP64 updates. What is
+checked is what the host does with them: which steps it queues, what it waits for and returns, and
+what memory it holds. The fields hold no numbers.
+"""
+import concurrent.futures as cf
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_1103_5103_amd as wd
+from paper_1103_5103_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1103_5103_amd", "csrc")
+HIP_ERROR, OOM, NOCONV, NAN, BREAKDOWN = 2, 3, 4, 6, 5
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    d = tmp_path_factory.mktemp("host_driver")
+    src = [os.path.join(CSRC, f) for f in ("wd_runtime.cpp", "wd_solve.cpp", "wd_api.cpp")]
+    src.append(os.path.join(ROOT, "tests", "host_driver_probe.cpp"))
+    objs = [str(d / (os.path.basename(s) + ".o")) for s in src]
+
+    def compile_one(s, o):
+        subprocess.run(["hipcc", "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-fPIC", "-I", CSRC, "-c", s, "-o", o],
+                       check=True, capture_output=True)
+
+    with cf.ThreadPoolExecutor(4) as ex:
+        list(ex.map(compile_one, src, objs))
+    so = str(d / "libhost.so")
+    # -Bsymbolic: the stand-in's HIP calls, whatever else the process has loaded
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-o", so, *objs], check=True, capture_output=True)
+    os.environ["WD_TUNE_CACHE"] = str(d / "tune.txt")
+    L = ctypes.CDLL(so)
+    for f in ("fake_live", "fake_peak", "wd_gauge_device_bytes"):
+        getattr(L, f).restype = ctypes.c_size_t
+    return L
+
+
+class Host:
+    """A handle of the stand-in library on a lattice, and calls on it (every device field at one address)."""
+
+    def __init__(self, lib, dims, hint=None):
+        self.lib, self.h = lib, ctypes.c_void_p()
+        self.x = ctypes.c_void_p(1 << 40)  # never touched: the kernels compute nothing
+        geom = _lib.Geom((ctypes.c_int * 4)(*dims), 1)
+        assert lib.wd_gauge_create(ctypes.byref(self.h), ctypes.byref(geom), self.x,
+                                   ctypes.byref(hint) if hint is not None else None, None) == 0
+
+    def params(self, **kw):
+        return params(self.lib, **kw)
+
+    def solve(self, p, kappa=0.12):
+        st = wd.SolverStats()
+        code = self.lib.bicgstab_solve(self.h, ctypes.c_double(kappa), self.x, self.x, ctypes.byref(p), ctypes.byref(st), None)
+        return code, [st]
+
+    def batch(self, p, n):
+        arr = (_lib.System * n)()
+        for s in arr:
+            s.gauge, s.kappa, s.b, s.x = self.h, 0.12, self.x, self.x
+        st = (wd.SolverStats * n)()
+        return self.lib.wd_batch_solve(n, arr, ctypes.byref(p), st, None), list(st)
+
+    def masses(self, p, n, method, normal=False):
+        v = (ctypes.c_double * n)(*[0.12 + 0.001 * i for i in range(n)])
+        xs = (ctypes.c_void_p * n)(*[self.x.value] * n)
+        st = (wd.SolverStats * n)()
+        if normal:
+            code = self.lib.wd_normal_solve(self.h, ctypes.c_double(0.12), n, v, xs, self.x, method, 1, ctypes.byref(p), st, None)
+        else:
+            code = self.lib.wd_multimass_solve(self.h, n, v, xs, self.x, method, 1, ctypes.byref(p), st, None)
+        return code, list(st)
+
+    def bytes(self):
+        return self.lib.wd_gauge_device_bytes(self.h)
+
+    def close(self):
+        assert self.lib.wd_gauge_destroy(self.h) == 0
+
+
+def params(lib, **kw):
+    p = wd.SolverParams()
+    lib.wd_params_default(ctypes.byref(p))
+    for k, v in kw.items():
+        assert hasattr(p, k)
+        setattr(p, k, v)
+    return p
+
+
+def reset(lib, capacity=1 << 62, seed=1):
+    lib.fake_reset(ctypes.c_size_t(capacity), seed)
+
+
+def script(lib, *p):
+    lib.fake_script(*[ctypes.c_double(v) for v in p])
+
+
+def last_error(lib):
+    buf = ctypes.create_string_buffer(512)
+    lib.wd_last_error(buf, 512)
+    return buf.value.decode()
+
+
+# ---------------------------------------------------------------- the schedule of the even-odd solves
+SCRIPTS = {  # reliable, converged, verified, breakdown, nan
+    "reliable": (0.3, 0.1, 1.0, 0.0, 0.0),
+    "failed checks": (0.1, 0.3, 0.2, 0.0, 0.0),
+    "everything": (0.2, 0.15, 0.4, 0.05, 0.02),
+    "iteration cap": (0.2, 0.0, 0.0, 0.0, 0.0),
+}
+
+
+@pytest.mark.parametrize("dims,n", [((4, 4, 4, 4), 1), ((4, 4, 4, 4), 2), ((4, 4, 4, 4), 7), ((16, 16, 16, 16), 9)])
+@pytest.mark.parametrize("kind", SCRIPTS)
+@pytest.mark.parametrize("dc", [0, 1])
+def test_systems_that_stop_at_different_times(lib, dims, n, kind, dc):
+    """Whatever order the systems of a solve stop, go on, fail their check and restart in, the host
+    neither loses count of one (it would wait for a report that never comes) nor gives up early.
+    ((16, 16, 16, 16) x 9: above the folded finishers.)"""
+    reset(lib)
+    g = Host(lib, dims)
+    for seed in range(8):
+        reset(lib, seed=seed)
+        script(lib, *SCRIPTS[kind])
+        p = g.params(max_iter=30, mixed_mode=dc)
+        code, st = g.batch(p, n) if n > 1 else g.solve(p)
+        assert code != HIP_ERROR, (seed, last_error(lib))
+        for s in st:
+            assert 0 <= s.iters <= 30
+            if kind == "iteration cap":
+                assert (s.iters, s.status) == (30, NOCONV)
+            elif kind == "reliable":
+                assert s.status in (0, NOCONV) and s.reliable_updates > 0
+        assert lib.fake_out_of_range() == 0
+    g.close()
