@@ -90,9 +90,11 @@ struct Timer {
     struct Rec { int cls; hipEvent_t a, b; double bytes; int slot; int njobs; int cls2; };
     std::vector<Rec> pending;
     std::vector<hipEvent_t> pool;
+    // pending holds at most kRecords (flush() reads as many flags back); every record goes through push()
+    static constexpr size_t kRecords = 1 << 16;
     int* dflags = nullptr;  // per pending launch: set by the kernel when it did work
-    size_t cap = 0;
-    int* slot();
+    int* slot();            // the flag of the next record, which is pushed before any other
+    void push(const Rec& r);
     double ms[NTK] = {};
     double bytes[NTK] = {};
     long launches[NTK] = {};

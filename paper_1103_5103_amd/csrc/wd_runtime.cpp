@@ -207,12 +207,16 @@ hipEvent_t Timer::get()
 int* Timer::slot()
 {
     if (!dflags) {
-        cap = 1 << 16;
-        WD_CHECK_HIP(hipMalloc(&dflags, cap * sizeof(int)));
-        WD_CHECK_HIP(hipMemset(dflags, 0, cap * sizeof(int)));
+        WD_CHECK_HIP(hipMalloc(&dflags, kRecords * sizeof(int)));
+        WD_CHECK_HIP(hipMemset(dflags, 0, kRecords * sizeof(int)));
     }
-    if (pending.size() >= cap) flush();
+    if (pending.size() >= kRecords) flush();
     return dflags + pending.size();
+}
+void Timer::push(const Rec& r)
+{
+    if (pending.size() >= kRecords) flush();  // (not for a record with a slot, for which slot() made room)
+    pending.push_back(r);
 }
 
 // Launches that every system skipped (gated iterations after convergence) are not counted:
@@ -349,7 +353,7 @@ static void run_finish(int nr, int fin, const JobTable<J>& t, SysState* sys, int
         b = T.get();
     }
     WD_CHECK_HIP(launch_finish(nr, fin, t.fin_d(), (int)t.fin.size(), sys, gated, s, a, b));
-    if (timed) T.pending.push_back({TK_FINISH, a, b, 0.0, -1, 0, -1});
+    if (timed) T.push({TK_FINISH, a, b, 0.0, -1, 0, -1});
 }
 
 // Non-temporal link loads keep the links from evicting the neighbour spinors in L2. They pay
@@ -384,7 +388,7 @@ void run_update(int hop, int sf, int lf, const JobTable<HopJob>& t, SysState* sy
     }
     WD_CHECK_HIP(launch_update(hop, sf, lf, t.d(), t.n(), t.nblocks, sys, GATE_STOPPED, s, flag,
                                t.host.empty() ? 0 : t.host[0].split, tg, stream_links(t, lf), a, b));
-    if (timed) T.pending.push_back({TK_HOP_F64, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
+    if (timed) T.push({TK_HOP_F64, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
     if (hop == 2) run_finish(4, FIN_UPDATE, t, sys, GATE_STOPPED, s);
 }
 
@@ -418,7 +422,7 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
         WD_CHECK_HIP(launch_hop(sf, lf, dag, red, fin, t.d(), t.n(), t.nblocks, sys, gated, s, flag, stage, tg, ntl, a, b));
     }
     if (timed)
-        T.pending.push_back({cls, a, b, bytes, (int)(flag - T.dflags), t.n(), cls == TK_HOP_LO ? TK_HOP_LO_RED + red : -1});
+        T.push({cls, a, b, bytes, (int)(flag - T.dflags), t.n(), cls == TK_HOP_LO ? TK_HOP_LO_RED + red : -1});
     if (red != RED_NONE && fin != FIN_NONE) run_finish(red == RED_FULL ? NRED : 3, fin, t, sys, gated, s);
 }
 
@@ -432,7 +436,7 @@ void run_apply(wd_gauge* g, double kappa, double* out, const double* in, bool da
     }
     WD_CHECK_HIP(launch_apply(dag, out, in, g->geo, g->lk(L64_18, 0), g->lk(L64_18, 1), g->lcs(), 1.0 / (2.0 * kappa), s,
                               a, b));
-    if (T.on) T.pending.push_back({TK_HOP_F64, a, b, (double)g->V * (2 * 192 + 4 * 144), -1, 0, -1});
+    if (T.on) T.push({TK_HOP_F64, a, b, (double)g->V * (2 * 192 + 4 * 144), -1, 0, -1});
 }
 
 // the fields that an operation's kernel reads or writes whatever its flags (bit r: role r)
@@ -470,7 +474,7 @@ void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int 
         b = T.get();
     }
     WD_CHECK_HIP(launch_sweep(op, sfl, t.d(), t.n(), t.nblocks, sys, gated, s, flag, a, b, fold));
-    if (timed) T.pending.push_back({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
+    if (timed) T.push({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
     if (fold) return;
     switch (op) {
     case OP_XR: run_finish(3, FIN_ALPHA, t, sys, gated, s); break;
@@ -495,7 +499,7 @@ void run_shift_update(int nb, const ShiftVectors& v, long n, const ShiftBlock* b
         b = T.get();
     }
     WD_CHECK_HIP(launch_shift_update(nb, v, n, blk, coef, s, flag, a, b));
-    if (T.on) T.pending.push_back({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), 1, -1});
+    if (T.on) T.push({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), 1, -1});
 }
 
 } // namespace wd

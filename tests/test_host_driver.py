@@ -143,3 +143,36 @@ def test_systems_that_stop_at_different_times(lib, dims, n, kind, dc):
                 assert s.status in (0, NOCONV) and s.reliable_updates > 0
         assert lib.fake_out_of_range() == 0
     g.close()
+
+
+# ---------------------------------------------------------------- timing
+def test_timing_of_more_launches_than_it_has_room_for(lib):
+    """Every timed launch leaves a record; 65536 of them are read back at a time, whatever kind of
+    launch the last one is."""
+    reset(lib)
+    g = Host(lib, (4, 4, 4, 4))
+    script(lib, 0.0, 0.1, 1.0, 0.0, 0.0)
+    out = ctypes.c_void_p(1 << 41)
+    ms, n, by = ctypes.c_double(), ctypes.c_long(), ctypes.c_double()
+    lib.wd_timing_reset()
+    lib.wd_timing_enable(1)
+    try:
+        code, st = g.solve(g.params(max_iter=100))
+        assert code == 0
+        assert lib.wd_timing_get(1, ctypes.byref(ms), ctypes.byref(n), ctypes.byref(by)) == 0
+        before = n.value
+        for _ in range(70000):
+            assert lib.wd_apply(g.h, ctypes.c_double(0.12), out, g.x, None) == 0
+        assert lib.wd_timing_get(1, ctypes.byref(ms), ctypes.byref(n), ctypes.byref(by)) == 0
+        assert n.value == before + 70000
+        # a record at the last place of the buffer, and the finisher's behind it
+        for k in range(65536 - 4, 65536 + 1):
+            lib.wd_timing_reset()
+            for _ in range(k):
+                assert lib.wd_apply(g.h, ctypes.c_double(0.12), out, g.x, None) == 0
+            assert g.solve(g.params(max_iter=100))[0] == 0
+            assert lib.wd_timing_get(3, ctypes.byref(ms), ctypes.byref(n), ctypes.byref(by)) == 0
+    finally:
+        lib.wd_timing_enable(0)
+    assert lib.fake_out_of_range() == 0
+    g.close()
