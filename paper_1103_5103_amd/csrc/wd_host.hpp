@@ -197,15 +197,23 @@ void* pinned(size_t bytes);
 char* stage_alloc(size_t bytes);
 
 // Host memory for the reports of one solve's systems (at most kMaxReports), taken from a process-wide
-// pool and given back when the solve ends; the stream must have drained by then. The pool keeps at
-// most kReportPool blocks, the rest is freed. Safe with several threads.
+// pool and given back when the solve ends. A solve ends with finish(): the stream drains, and an error of
+// the kernels queued last (they write the solutions) is the solve's. The destructor drains it where an
+// exception has ended the solve. The pool keeps at most kReportPool blocks, the rest is freed. Safe with
+// several threads.
 constexpr int kMaxReports = 1024;
 constexpr int kReportPool = 16;
 struct Reports {
     volatile SysReport* r = nullptr;
     hipStream_t st;
+    bool drained = false;  // finish() has been called
     explicit Reports(hipStream_t s);
     ~Reports();
+    void finish()
+    {
+        drained = true;
+        WD_CHECK_HIP(hipStreamSynchronize(st));
+    }
     Reports(const Reports&) = delete;
     Reports& operator=(const Reports&) = delete;
     struct View {

@@ -159,7 +159,7 @@ Reports::Reports(hipStream_t s) : st(s)
 }
 Reports::~Reports()
 {
-    (void)hipStreamSynchronize(st);  // no kernel may report into a block that another solve has taken
+    if (!drained) (void)hipStreamSynchronize(st);  // no kernel may report into a block that another solve has taken
     std::lock_guard<std::mutex> lk(g_reports_mu);
     if (g_reports.size() < (size_t)kReportPool) g_reports.push_back((void*)r);
     else (void)hipHostFree((void*)r);

@@ -556,8 +556,8 @@ static void prepare_source(wd_gauge* g, const std::string& key, const double* b,
 // launches after a system has stopped).
 constexpr int kPoll = 3;
 
-// Returns with the last kernels (the unpacking) queued: rep, whose reports slot0 .. are used, ends with
-// the stream drained.
+// Returns with the last kernels (the unpacking) queued; the caller ends with rep.finish(). The reports
+// slot0 .. are used.
 static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream_t st, int poll, const Reports& rep,
                      int slot0 = 0)
 {
@@ -1424,6 +1424,7 @@ wd_status solve_single(wd_gauge* g, double kappa, double* x, const double* b, co
     S[0].slot = 0;
     Reports rep(st);
     eo_solve(S, P, st, kPoll, rep);
+    rep.finish();
     if (stats) {
         stats->iters = S[0].iters;
         stats->reliable_updates = S[0].reliable;
@@ -1459,6 +1460,7 @@ wd_status solve_batch(int nsys, const wd_system* sys, const wd_solver_params& P,
     }
     Reports rep(st);
     eo_solve(S, P, st, kPoll, rep);
+    rep.finish();
     wd_status worst = WD_OK;
     for (int i = 0; i < nsys; i++) {
         if (stats) {
@@ -1675,6 +1677,7 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
         Q.use_x0 = 0;
         Reports rep(st);
         eo_solve(S, Q, st, kPoll, rep);
+        rep.finish();
         wd_status worst = WD_OK;
         for (int i = 0; i < n; i++) {
             if (stats) {
@@ -1873,6 +1876,7 @@ wd_status solve_multimass(wd_gauge* g, int n, const double* kappas, double* cons
             }
         }
     }
+    rep.finish();
     return worst;
 }
 

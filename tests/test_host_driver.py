@@ -176,3 +176,23 @@ def test_timing_of_more_launches_than_it_has_room_for(lib):
         lib.wd_timing_enable(0)
     assert lib.fake_out_of_range() == 0
     g.close()
+
+
+# ---------------------------------------------------------------- errors of the last kernels
+@pytest.mark.parametrize("call", ["single", "batch", "sequential", "batched", "multishift"])
+def test_a_failure_of_the_last_kernels_is_returned(lib, call):
+    """The kernels that write the solutions are the last ones queued; when they fail, the solve that
+    queued them says so."""
+    reset(lib)
+    g = Host(lib, (4, 4, 4, 4))
+    script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+    p, f64 = g.params(max_iter=100), g.params(max_iter=100, mixed=0, eo=0)
+    run = {"single": lambda: g.solve(p), "batch": lambda: g.batch(p, 3), "sequential": lambda: g.masses(p, 1, 0),
+           "batched": lambda: g.masses(p, 3, 2), "multishift": lambda: g.masses(f64, 3, 1)}
+    if call == "multishift":
+        script(lib, 0.0, 1.0, 1.0, 0.0, 0.0)
+    assert run[call]()[0] == 0
+    lib.fake_fail_unpack()
+    assert run[call]()[0] == HIP_ERROR
+    reset(lib)
+    g.close()
