@@ -166,14 +166,16 @@ struct wd_gauge {
     const void* lk(int lf, int parity) const;
     long lcs() const { return geo.stride; }
     wd::Field& field(const std::string& key, int sf, int halves);
-    // The missing ones of these fields in one allocation per format, zeroed: giving memory back takes
+    // The missing ones of these fields in one allocation per group, zeroed: giving memory back takes
     // about 0.24 ms an allocation (of 25 MB or more), whatever its size. 16^3x32 forward and backward
     // with a handle of its own: 7.0 ms with an allocation per field, of which 3.3 ms for giving 16 of
-    // them back; 4.0 ms so.
-    // Where the device does not have it in one piece, field() allocates them one by one.
+    // them back; 4.0 ms so. An allocation lives as long as any of its fields, so a group holds fields that
+    // change their format together: the FP64 ones that never do (0), or those of one system's iteration.
+    // Fields whose format has changed are given back first. A group of one field is left to field(), as
+    // are those that the device does not have room for in one piece.
     struct FieldSpec {
         std::string key;
-        int sf, halves;
+        int sf, halves, group = 0;
     };
     void reserve(const std::vector<FieldSpec>& fields);
     void* rawbuf(const std::string& key, size_t bytes);

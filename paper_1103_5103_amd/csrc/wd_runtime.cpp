@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <set>
 
 #include "wd_host.hpp"
 
@@ -628,10 +629,12 @@ Field& wd_gauge::field(const std::string& key, int sf, int halves)
 
 void wd_gauge::reserve(const std::vector<FieldSpec>& fields)
 {
-    std::map<int, std::vector<const FieldSpec*>> missing;  // by format: a change of the iteration's gives its part back
+    std::map<int, std::vector<const FieldSpec*>> missing;
     for (const FieldSpec& f : fields) {
         auto it = ws.find(f.key);
-        if (it == ws.end() || it->second.sf != f.sf || it->second.halves != f.halves) missing[f.sf].push_back(&f);
+        if (it != ws.end() && it->second.sf == f.sf && it->second.halves == f.halves) continue;
+        if (it != ws.end()) ws.erase(it);
+        missing[f.group].push_back(&f);
     }
     for (auto& kv : missing) {
         size_t total = 0;
@@ -684,13 +687,16 @@ void wd_gauge::retire()
 
 size_t wd_gauge::device_bytes() const
 {
+    std::set<const DevMem*> held;  // whole allocations, whatever number of their parts is in use
+    auto add = [&](const DevMem* m) {
+        if (m) held.insert(m->owner ? m->owner.get() : m);
+    };
+    for (auto& l : links) add(l.get());
+    for (auto& l : fixed) add(l.get());
+    add(gmat.get());
+    for (auto& kv : ws) add(kv.second.mem.get());
+    for (auto& kv : raw) add(kv.second.get());
     size_t n = 0;
-    for (auto& l : links)
-        if (l) n += l->bytes;
-    for (auto& l : fixed)
-        if (l) n += l->bytes;
-    if (gmat) n += gmat->bytes;
-    for (auto& kv : ws) n += kv.second.mem->bytes;
-    for (auto& kv : raw) n += kv.second->bytes;
+    for (const DevMem* m : held) n += m->bytes;
     return n;
 }

@@ -589,8 +589,8 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         if (!e.BP.mem) v.push_back({k + "BP", SF64, 1});
         if (!e.RH.mem) v.push_back({k + "RH", SF64, 1});
         v.push_back({k + "T64", SF64, 1});
-        for (const char* f : {"r", "rh", "s", "w", "As", "Aw", "tmp"}) v.push_back({k + f, SFL, 1});
-        v.push_back({k + "xl", SFX, 1});
+        for (const char* f : {"r", "rh", "s", "w", "As", "Aw", "tmp"}) v.push_back({k + f, SFL, 1, 1 + 2 * e.slot});
+        v.push_back({k + "xl", SFX, 1, 2 + 2 * e.slot});
     }
     for (auto& f : need) f.first->reserve(f.second);
     for (auto& e : S) {
@@ -1936,8 +1936,8 @@ static void cg_solve(std::vector<CgSys>& S, const wd_solver_params& P, hipStream
         if (!e.X64.mem) v.push_back({k + "X64", SF64, 2});
         if (!e.RH.mem) v.push_back({k + "RH", SF64, 1});
         v.insert(v.end(), {{k + "T64", SF64, 1}, {k + "V64", SF64, 1}});
-        for (const char* f : {"r", "p", "t", "v", "w"}) v.push_back({k + f, SFL, 1});
-        v.push_back({k + "xl", SFX, 1});
+        for (const char* f : {"r", "p", "t", "v", "w"}) v.push_back({k + f, SFL, 1, 1 + 2 * e.slot});
+        v.push_back({k + "xl", SFX, 1, 2 + 2 * e.slot});
     }
     for (auto& f : need) f.first->reserve(f.second);
     for (auto& e : S) {

@@ -196,3 +196,68 @@ def test_a_failure_of_the_last_kernels_is_returned(lib, call):
     assert run[call]()[0] == HIP_ERROR
     reset(lib)
     g.close()
+
+
+# ---------------------------------------------------------------- memory
+F64, F32, F16 = 0, 1, 2  # wd_prec
+
+
+def _spinors(g, f):
+    return g.params(max_iter=100, mixed=0) if f == F64 else g.params(max_iter=100, spinor_store=f)
+
+
+def _held(lib, dims, calls):
+    """Device memory that a handle holds after each of these calls, and the handle's own count of it."""
+    reset(lib)
+    script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+    base = lib.fake_live()
+    g = Host(lib, dims, params(lib))
+    out = []
+    for f, n in calls:
+        p = _spinors(g, f)
+        assert (g.solve(p) if n == 1 else g.batch(p, n))[0] == 0
+        out.append((lib.fake_live() - base, g.bytes()))
+    g.close()
+    assert lib.fake_live() == base
+    return out
+
+
+@pytest.mark.parametrize("seq", [(F32, F16), (F32, F16, F32), (F64, F32), (F64, F32, F64, F16), (F16, F64, F32, F16)])
+def test_a_change_of_storage_gives_the_old_fields_back(lib, seq):
+    """A handle that went through other formats holds what one holds that has only run the last."""
+    dims = (4, 4, 4, 8)  # (allocations too small to be kept for the next handle)
+    for n in (1, 2):
+        _held(lib, dims, [(f, n) for f in seq])  # (the hop tuner's first run needs a buffer)
+        got = _held(lib, dims, [(f, n) for f in seq])
+        want = _held(lib, dims, [(seq[-1], n)])
+        assert got[-1][0] == want[-1][0], (seq, n)
+        assert all(live == count for live, count in got)
+
+
+def test_a_change_of_storage_of_some_systems(lib):
+    """The fields of one system of a batch are given back when it changes, though the others keep theirs."""
+    dims = (4, 4, 4, 8)
+    d = _held(lib, dims, [(F16, 1)])[0][0] - _held(lib, dims, [(F32, 1)])[0][0]
+    got = _held(lib, dims, [(F32, 2), (F16, 1)])
+    assert got[1][0] == got[0][0] + d
+
+
+@pytest.mark.parametrize("seq", [(F32, F16, F32), (F64, F32, F64)])
+def test_a_change_of_storage_where_memory_is_short(lib, seq):
+    """The old fields are given back before the new ones are made: a device that has room for either set
+    is enough."""
+    dims = (4, 4, 4, 8)
+    reset(lib)
+    script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+    base = lib.fake_live()
+    g = Host(lib, dims, params(lib))
+    limit = 0
+    for f in set(seq):
+        assert g.solve(_spinors(g, f))[0] == 0
+        limit = max(limit, lib.fake_live())
+    for f in seq:
+        reset(lib, capacity=limit)
+        script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+        assert g.solve(_spinors(g, f))[0] == 0, last_error(lib)
+    g.close()
+    assert lib.fake_live() == base
