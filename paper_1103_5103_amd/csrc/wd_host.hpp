@@ -80,6 +80,7 @@ struct Field {
     long nsites() const { return stride * halves; }
 };
 size_t field_bytes(int sf, int halves, long stride);
+size_t room_of(size_t bytes);  // rounded up to what a part of an allocation takes
 
 // ---------------------------------------------------------------- timing
 // TK_HOP_LO_RED + r: the low-precision hops with fused reduction r (RED_NONE .. RED_FULL), also
@@ -179,6 +180,11 @@ struct wd_gauge {
     };
     void reserve(const std::vector<FieldSpec>& fields);
     void* rawbuf(const std::string& key, size_t bytes);
+    // Memory that a solve is faster with but can do without (zeroed when made; NULL: the device has no
+    // room). The handle keeps it for its next solve; when an allocation of the library fails, those
+    // that no solve holds are given back, whichever handle keeps them.
+    std::shared_ptr<wd::DevMem> room(const std::string& key, size_t bytes);
+    ~wd_gauge();
     // the same for the link formats that a handle makes when it is created
     void reserve_links(std::initializer_list<int> fmts);
     std::unique_ptr<wd::DevMem> new_links(int lf);

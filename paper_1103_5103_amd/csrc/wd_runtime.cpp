@@ -59,6 +59,33 @@ static void keep_spare(void* p, size_t n, int dev, size_t limit)
     for (auto& s : out) (void)hipFree(s.p);
 }
 
+// Rooms (wd_gauge::room) by handle and name; as the list above, never destroyed.
+static std::mutex g_rooms_mu;
+static std::map<std::pair<const wd_gauge*, std::string>, std::shared_ptr<DevMem>>& rooms()
+{
+    static auto* m = new std::map<std::pair<const wd_gauge*, std::string>, std::shared_ptr<DevMem>>;
+    return *m;
+}
+// gives back the rooms on device dev that no solve uses; were there any
+static bool drop_rooms(int dev)
+{
+    std::vector<std::shared_ptr<DevMem>> out;
+    {
+        std::lock_guard<std::mutex> lk(g_rooms_mu);
+        auto& m = rooms();
+        out.reserve(m.size());
+        for (auto it = m.begin(); it != m.end();) {
+            if (it->second->dev == dev && it->second.use_count() == 1) {
+                out.push_back(std::move(it->second));
+                it = m.erase(it);
+            } else {
+                ++it;
+            }
+        }
+    }
+    return !out.empty();
+}
+
 DevMem::DevMem(size_t n) : bytes(n)
 {
     if (n == 0) return;
@@ -69,6 +96,10 @@ DevMem::DevMem(size_t n) : bytes(n)
         (void)hipGetLastError();
         keep_spare(nullptr, 0, 0, 0);
         e = hipMalloc(&p, n);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (drop_rooms(dev)) e = hipMalloc(&p, n);
     }
     if (e != hipSuccess) {
         p = nullptr;
@@ -87,6 +118,11 @@ DevMem::~DevMem()
         }
     }
     (void)hipFree(p);
+}
+size_t room_of(size_t bytes)
+{
+    constexpr size_t align = 4096;
+    return (bytes + align - 1) / align * align;
 }
 size_t field_bytes(int sf, int halves, long stride)
 {
@@ -529,11 +565,6 @@ static size_t link_bytes(int lf, long stride)
     return (size_t)2 * 8 * link_chunks(lf) * link_chunk_bytes(lf) * stride;
 }
 
-static size_t room_of(size_t bytes)
-{
-    constexpr size_t align = 4096;
-    return (bytes + align - 1) / align * align;
-}
 
 void wd_gauge::reserve_links(std::initializer_list<int> fmts)
 {
@@ -661,6 +692,51 @@ void wd_gauge::reserve(const std::vector<FieldSpec>& fields)
     }
 }
 
+std::shared_ptr<DevMem> wd_gauge::room(const std::string& key, size_t bytes)
+{
+    const auto id = std::make_pair((const wd_gauge*)this, key);
+    std::shared_ptr<DevMem> m;
+    {
+        std::lock_guard<std::mutex> lk(g_rooms_mu);
+        auto it = rooms().find(id);
+        if (it != rooms().end()) m = it->second;
+    }
+    if (m && m->bytes == bytes) return m;
+    // One of another size goes only where that makes place for this one, which takes the last of the
+    // memory from nobody: not from another room, nor what the solve itself is still to allocate.
+    const size_t rest = field_bytes(SF64, 2, geo.stride) + ((size_t)4 << 20), had = m ? m->bytes : 0;
+    size_t free = 0, total = 0;
+    for (int k = 0; k < 2; k++) {
+        WD_CHECK_HIP(hipMemGetInfo(&free, &total));
+        if (free + had >= bytes + rest) break;
+        if (k == 0) keep_spare(nullptr, 0, 0, 0);
+    }
+    if (free + had < bytes + rest) return nullptr;
+    {
+        std::lock_guard<std::mutex> lk(g_rooms_mu);
+        rooms().erase(id);
+    }
+    m.reset();
+    try {
+        m = std::make_shared<DevMem>(bytes);
+    } catch (const Error& e) {
+        if (e.code != WD_ERR_OOM) throw;
+        return nullptr;
+    }
+    WD_CHECK_HIP(hipMemset(m->p, 0, bytes));
+    std::lock_guard<std::mutex> lk(g_rooms_mu);
+    rooms()[id] = m;
+    return m;
+}
+
+wd_gauge::~wd_gauge()
+{
+    std::lock_guard<std::mutex> lk(g_rooms_mu);
+    auto& m = rooms();
+    for (auto it = m.begin(); it != m.end();)
+        it = it->first.first == this ? m.erase(it) : std::next(it);
+}
+
 void* wd_gauge::rawbuf(const std::string& key, size_t bytes)
 {
     auto it = raw.find(key);
@@ -683,6 +759,9 @@ void wd_gauge::retire()
     for (auto& kv : ws) kv.second.mem->retire(cur);
     for (auto& kv : raw)
         if (kv.second) kv.second->retire(cur);
+    std::lock_guard<std::mutex> lk(g_rooms_mu);
+    for (auto& kv : rooms())
+        if (kv.first.first == this) kv.second->retire(cur);
 }
 
 size_t wd_gauge::device_bytes() const
@@ -696,6 +775,9 @@ size_t wd_gauge::device_bytes() const
     add(gmat.get());
     for (auto& kv : ws) add(kv.second.mem.get());
     for (auto& kv : raw) add(kv.second.get());
+    std::lock_guard<std::mutex> lk(g_rooms_mu);
+    for (auto& kv : rooms())
+        if (kv.first.first == this) add(kv.second.get());
     size_t n = 0;
     for (const DevMem* m : held) n += m->bytes;
     return n;

@@ -1051,30 +1051,26 @@ struct ShiftedSystems {
     const Field& w(int j) const { return W[j]; }
 
     // The buffers of m = SHIFT_BLOCK iterations per update, or of fewer where the memory does not
-    // allow that (m = 1: as many fields as an update in every iteration needs).
+    // allow that. m = 1 takes two residuals and one w, as an update in every iteration does; what more
+    // iterations take beyond that is given back when something else needs the memory (wd_gauge::room).
     void alloc(wd_gauge* g, const std::string& key, int ns_, bool cg_, int halves, const std::vector<SpinorRef>& sv,
                hipStream_t st)
     {
         ns = ns_;
         cg = cg_;
-        m = ns > 0 ? SHIFT_BLOCK : 1;
-        for (;;) {
-            R.clear();
-            W.clear();
-            try {
-                // without shifts the one residual is updated in place
-                for (int j = 0; j <= (ns > 0 ? m : 0); j++) R.push_back(g->field(key + "R" + std::to_string(j), SF64, halves));
-                for (int j = 0; j < (cg ? 0 : m); j++) W.push_back(g->field(key + "W" + std::to_string(j), SF64, halves));
-                break;
-            } catch (const Error& e) {
-                if (e.code != WD_ERR_OOM || m == 1) throw;
-                R.clear();
-                W.clear();
-                m /= 2;
-                for (int j = m + 1; j <= SHIFT_BLOCK; j++) g->ws.erase(key + "R" + std::to_string(j));
-                for (int j = m; j < SHIFT_BLOCK; j++) g->ws.erase(key + "W" + std::to_string(j));
+        // without shifts the one residual is updated in place
+        for (int j = 0; j <= (ns > 0 ? 1 : 0); j++) R.push_back(g->field(key + "R" + std::to_string(j), SF64, halves));
+        if (!cg) W.push_back(g->field(key + "W0", SF64, halves));
+        const size_t one = room_of(field_bytes(SF64, halves, g->geo.stride));
+        std::shared_ptr<DevMem> whole;
+        for (m = ns > 0 ? SHIFT_BLOCK : 1; m > 1 && !(whole = g->room(key, (size_t)(m - 1) * (cg ? 1 : 2) * one)); m /= 2) {}
+        size_t off = 0;
+        for (std::vector<Field>* v : {&R, &W})
+            for (int j = 1; j < m && !v->empty(); j++, off += one) {
+                Field f = R[0];
+                f.mem = std::make_shared<DevMem>(whole, off, R[0].mem->bytes);
+                v->push_back(f);
             }
-        }
         n = R[0].nsites() * 12;
         sites = (double)R[0].nsites();
         if (ns == 0) return;
@@ -1166,8 +1162,8 @@ static wd_status ms_solve(wd_gauge* g, int nk, const double* kappas, double* con
         for (const char* f : {"B", "X", "S", "AS", "AW"}) need.push_back({std::string("ms.") + f, SF64, 2});
         for (int k = 0; k < ns; k++)
             need.insert(need.end(), {{"ms.XS" + std::to_string(k), SF64, 2}, {"ms.SS" + std::to_string(k), SF64, 2}});
-        for (int j = 0; j <= (ns > 0 ? SHIFT_BLOCK : 0); j++) need.push_back({"ms.R" + std::to_string(j), SF64, 2});
-        for (int j = 0; j < (ns > 0 ? SHIFT_BLOCK : 1); j++) need.push_back({"ms.W" + std::to_string(j), SF64, 2});
+        for (int j = 0; j <= (ns > 0 ? 1 : 0); j++) need.push_back({"ms.R" + std::to_string(j), SF64, 2});
+        need.push_back({"ms.W0", SF64, 2});
         g->reserve(need);
     }
     Field B = g->field("ms.B", SF64, 2), X = g->field("ms.X", SF64, 2);
@@ -2276,7 +2272,7 @@ static wd_status cgm_solve(wd_gauge* g, double kappa, int n, const double* sigma
         for (const char* f : {"p", "t", "v", "w"}) need.push_back({std::string("cgm.") + f, SF64, 1});
         for (int i = 0; i < n; i++) need.push_back({"cgm.X" + std::to_string(i), SF64, 2});
         for (int k = 0; k < ns; k++) need.push_back({"cgm.P" + std::to_string(k), SF64, 1});
-        for (int j = 0; j <= (ns > 0 ? SHIFT_BLOCK : 0); j++) need.push_back({"cgm.R" + std::to_string(j), SF64, 1});
+        for (int j = 0; j <= (ns > 0 ? 1 : 0); j++) need.push_back({"cgm.R" + std::to_string(j), SF64, 1});
         for (int i = 0; i < n; i++)
             for (const char* f : {"RT", "RV", "RR"}) need.push_back({std::string("cgm.") + f + std::to_string(i), SF64, 1});
         g->reserve(need);

@@ -130,6 +130,12 @@ hipError_t hipFree(void* p)
     std::free(p);
     return hipSuccess;
 }
+hipError_t hipMemGetInfo(size_t* free, size_t* total)
+{
+    *total = F.capacity;
+    *free = F.capacity - std::min(F.capacity, F.live);
+    return hipSuccess;
+}
 hipError_t hipHostMalloc(void** p, size_t n, unsigned)
 {
     *p = std::calloc(1, n);

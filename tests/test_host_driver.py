@@ -101,6 +101,14 @@ def reset(lib, capacity=1 << 62, seed=1):
     lib.fake_reset(ctypes.c_size_t(capacity), seed)
 
 
+def drop_spares(lib):
+    """Allocations of closed handles go when an allocation fails."""
+    reset(lib, capacity=0)
+    h, geom = ctypes.c_void_p(), _lib.Geom((ctypes.c_int * 4)(4, 4, 4, 4), 1)
+    assert lib.wd_gauge_create(ctypes.byref(h), ctypes.byref(geom), ctypes.c_void_p(1 << 40), None, None) == OOM
+    reset(lib)
+
+
 def script(lib, *p):
     lib.fake_script(*[ctypes.c_double(v) for v in p])
 
@@ -261,3 +269,43 @@ def test_a_change_of_storage_where_memory_is_short(lib, seq):
         assert g.solve(_spinors(g, f))[0] == 0, last_error(lib)
     g.close()
     assert lib.fake_live() == base
+
+
+BLOCK_FIELDS = 15  # BiCGstab-M: what it holds beyond the fields that an update in every iteration needs
+
+
+def _full_field(dims):
+    v = dims[0] * dims[1] * dims[2] * dims[3]
+    return 2 * ((v // 2 + 255) // 256 * 256) * 192
+
+
+@pytest.mark.parametrize("other", ["more masses", "even-odd", "another handle", "normal"])
+def test_vectors_kept_for_block_updates_give_way(lib, other):
+    """The residuals that BiCGstab-M (CG-M) keeps for its block updates are given back when an
+    allocation needs the room, whoever makes it: a call that fits without them is not refused because
+    an earlier solve left them."""
+    dims = (8, 8, 8, 8)
+    drop_spares(lib)
+    script(lib, 0.0, 0.2, 1.0, 0.0, 0.0)
+    f64, eo = params(lib, max_iter=100, mixed=0, eo=0), params(lib, max_iter=100, mixed=0)
+    g, g2 = Host(lib, dims, params(lib)), Host(lib, dims, params(lib))
+    one = _full_field(dims)
+    normal = other == "normal"
+    calls = {"more masses": lambda: g.masses(f64, 6, 1), "even-odd": lambda: g.solve(eo), "another handle": lambda: g2.solve(eo),
+             "normal": lambda: g.masses(f64, 6, 1)}
+    before = lib.fake_live()
+    assert g.masses(f64, 2, 1, normal=normal)[0] == 0
+    kept = lib.fake_live()
+    assert kept - before > (7 * one // 2 if normal else BLOCK_FIELDS * one)
+    # room for the fields of the second call (BiCGstab-M of 6 masses without blocks: 8 more; even-odd FP64: 8),
+    # less than the kept vectors take
+    room = 0 if not normal else 20 * one
+    for k in range(2):
+        reset(lib, capacity=kept + room)
+        script(lib, 0.0, 0.2, 1.0, 0.0, 0.0)
+        assert calls[other]()[0] == 0, last_error(lib)
+        # and the first call comes back, with shorter blocks if need be
+        assert g.masses(f64, 2, 1, normal=normal)[0] == 0, last_error(lib)
+    assert lib.fake_out_of_range() == 0
+    g.close()
+    g2.close()
