@@ -139,9 +139,14 @@ void wd_params_default(wd_solver_params* p);
 wd_status wd_gauge_create(wd_gauge** g, const wd_geom* geom, const double* U,
                           const wd_solver_params* storage_hint, void* stream);
 /* Waits for the current device. Of the handle's device memory at most 1 GiB a process is kept for the next
-   handle with allocations of the same sizes (the oldest is given back first, all of it when an allocation
-   of the library fails); the rest is given back at once. */
+   handle with allocations of the same sizes, and nothing where the device has less than 8 GiB free (the oldest
+   is given back first, all of it when an allocation of the library fails or wd_trim_memory is called); the
+   rest is given back at once. */
 wd_status wd_gauge_destroy(wd_gauge* g);
+/* Gives back the device memory that the library keeps without need: what wd_gauge_destroy has kept, and
+   the vectors that multi-shift solves keep for their block updates while no such solve runs (the next one
+   makes them again). For a program that needs the memory itself. Safe with several threads. */
+wd_status wd_trim_memory(void);
 
 /* out = M(kappa) in  (Sec. 2, eq. 3 and 4; FP64). in, out: device [V][3][4] complex128, distinct. */
 wd_status wd_apply(wd_gauge* g, double kappa, double* out, const double* in, void* stream);

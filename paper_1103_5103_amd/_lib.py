@@ -88,7 +88,7 @@ EXPORTED = [
     "wd_params_default", "wd_gauge_create", "wd_gauge_destroy", "wd_apply", "wd_apply_dag", "bicgstab_solve",
     "bicgstab_m_solve", "wd_multimass_solve", "wd_batch_solve", "wd_normal_solve", "wd_gauge_grad",
     "wd_status_str", "wd_last_error", "wd_timing_enable", "wd_timing_reset", "wd_timing_get", "wd_gauge_device_bytes",
-    "wd_set_graphs", "wd_op_variant_default", "wd_apply_prec", "wd_apply_noalloc",
+    "wd_set_graphs", "wd_op_variant_default", "wd_apply_prec", "wd_apply_noalloc", "wd_trim_memory",
 ]
 
 _lib = None
@@ -140,11 +140,12 @@ def load(path: str = LIBPATH):
     L.wd_timing_get.argtypes = [i, ctypes.POINTER(d), ctypes.POINTER(ctypes.c_long), ctypes.POINTER(d)]
     L.wd_set_graphs.argtypes = [i]
     L.wd_set_graphs.restype = None
+    L.wd_trim_memory.argtypes = []
     L.wd_gauge_device_bytes.argtypes = [vp]
     L.wd_gauge_device_bytes.restype = ctypes.c_size_t
     for name in ("wd_gauge_create", "wd_gauge_destroy", "wd_apply", "wd_apply_dag", "bicgstab_solve",
                  "bicgstab_m_solve", "wd_multimass_solve", "wd_batch_solve", "wd_normal_solve", "wd_gauge_grad",
-                 "wd_last_error", "wd_timing_get", "wd_apply_prec", "wd_apply_noalloc"):
+                 "wd_last_error", "wd_timing_get", "wd_apply_prec", "wd_apply_noalloc", "wd_trim_memory"):
         getattr(L, name).restype = ctypes.c_int
     _lib = L
     return L
@@ -244,6 +245,12 @@ def wd_gauge_create(U: torch.Tensor, antiperiodic: bool = True, hint: SolverPara
 
 def wd_gauge_destroy(g: Gauge) -> None:
     g.close()
+
+
+def wd_trim_memory() -> None:
+    """Give back the device memory that the library keeps without need (of closed handles, and block
+    vectors of multi-shift solves), for a program that needs it itself, next to torch.cuda.empty_cache()."""
+    _check(load().wd_trim_memory())
 
 
 def wd_apply(g: Gauge, kappa: float, psi: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:

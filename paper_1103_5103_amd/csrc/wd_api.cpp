@@ -182,6 +182,14 @@ wd_status wd_gauge_destroy(wd_gauge* g)
     });
 }
 
+wd_status wd_trim_memory(void)
+{
+    return guarded([&]() -> wd_status {
+        trim_memory();
+        return WD_OK;
+    });
+}
+
 size_t wd_gauge_device_bytes(const wd_gauge* g) { return g ? g->device_bytes() : 0; }
 
 static wd_status apply_impl(wd_gauge* g, double kappa, double* out, const double* in, void* stream, bool dag)

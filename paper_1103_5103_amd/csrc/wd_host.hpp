@@ -33,7 +33,8 @@ void set_error(const std::string& msg);
 
 // ---------------------------------------------------------------- device memory
 // A device allocation. Those of a destroyed handle (retire) are kept for the next handle's of the same size,
-// up to 1 GiB a process, the oldest given back first and all of them when an allocation fails: what is
+// up to 1 GiB a process while the device has 8 GiB free, the oldest given back first and all of them when an
+// allocation fails or trim_memory() is called: what is
 // given back to the driver it wipes at some 25 GB/s, and a program that makes a handle for every step of a
 // training loop waits for that in the long run (16^3x32 forward and backward
 // 4.0 ms, 15.7 ms where memory has been through many hands; with the list 3.1 ms).
@@ -79,6 +80,7 @@ struct Field {
     SpinorRef all() const { return SpinorRef{base(), nrm(), cs()}; }
     long nsites() const { return stride * halves; }
 };
+void trim_memory();  // gives back the allocations of destroyed handles and the rooms that no solve uses
 size_t field_bytes(int sf, int halves, long stride);
 size_t room_of(size_t bytes);  // rounded up to what a part of an allocation takes
 

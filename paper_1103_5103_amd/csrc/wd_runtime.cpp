@@ -15,7 +15,7 @@ const std::string& last_error() { return g_last_error; }
 
 // Allocations of destroyed handles (DevMem::retire). The list itself is never destroyed: handles may outlive
 // static objects at the end of the process.
-constexpr size_t kSpareBytes = (size_t)1 << 30, kSpareMin = (size_t)1 << 20;
+constexpr size_t kSpareBytes = (size_t)1 << 30, kSpareMin = (size_t)1 << 20, kSpareFree = (size_t)8 << 30;
 struct Spare {
     void* p;
     size_t bytes;
@@ -66,7 +66,7 @@ static std::map<std::pair<const wd_gauge*, std::string>, std::shared_ptr<DevMem>
     static auto* m = new std::map<std::pair<const wd_gauge*, std::string>, std::shared_ptr<DevMem>>;
     return *m;
 }
-// gives back the rooms on device dev that no solve uses; were there any
+// gives back the rooms on device dev (-1: on all) that no solve uses; were there any
 static bool drop_rooms(int dev)
 {
     std::vector<std::shared_ptr<DevMem>> out;
@@ -75,7 +75,7 @@ static bool drop_rooms(int dev)
         auto& m = rooms();
         out.reserve(m.size());
         for (auto it = m.begin(); it != m.end();) {
-            if (it->second->dev == dev && it->second.use_count() == 1) {
+            if ((dev < 0 || it->second->dev == dev) && it->second.use_count() == 1) {
                 out.push_back(std::move(it->second));
                 it = m.erase(it);
             } else {
@@ -84,6 +84,11 @@ static bool drop_rooms(int dev)
         }
     }
     return !out.empty();
+}
+void trim_memory()
+{
+    keep_spare(nullptr, 0, 0, 0);
+    (void)drop_rooms(-1);
 }
 
 DevMem::DevMem(size_t n) : bytes(n)
@@ -750,7 +755,12 @@ void* wd_gauge::rawbuf(const std::string& key, size_t bytes)
 void wd_gauge::retire()
 {
     int cur = -1;
-    if (hipGetDevice(&cur) != hipSuccess) return;
+    size_t free = 0, total = 0;
+    if (hipGetDevice(&cur) != hipSuccess || hipMemGetInfo(&free, &total) != hipSuccess) return;
+    if (free < kSpareFree) {  // whoever else uses the device may need what there is
+        keep_spare(nullptr, 0, 0, 0);
+        return;
+    }
     for (auto& l : links)
         if (l) l->retire(cur);
     for (auto& l : fixed)

@@ -216,7 +216,7 @@ def _spinors(g, f):
 
 def _held(lib, dims, calls):
     """Device memory that a handle holds after each of these calls, and the handle's own count of it."""
-    reset(lib)
+    drop_spares(lib)
     script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
     base = lib.fake_live()
     g = Host(lib, dims, params(lib))
@@ -255,7 +255,7 @@ def test_a_change_of_storage_where_memory_is_short(lib, seq):
     """The old fields are given back before the new ones are made: a device that has room for either set
     is enough."""
     dims = (4, 4, 4, 8)
-    reset(lib)
+    drop_spares(lib)
     script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
     base = lib.fake_live()
     g = Host(lib, dims, params(lib))
@@ -309,3 +309,39 @@ def test_vectors_kept_for_block_updates_give_way(lib, other):
     assert lib.fake_out_of_range() == 0
     g.close()
     g2.close()
+
+
+def test_memory_of_closed_handles(lib):
+    """Kept for the next handle up to 1 GiB, given back on request; not kept where the device is short."""
+    dims = (16, 16, 16, 16)
+    drop_spares(lib)
+    script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+    base = lib.fake_live()
+
+    def one():
+        g = Host(lib, dims, params(lib))
+        assert g.solve(params(lib, max_iter=100))[0] == 0
+        g.close()
+
+    one()
+    kept = lib.fake_live()
+    assert base < kept <= base + (1 << 30)
+    one()
+    assert lib.fake_live() == kept  # taken again
+    assert lib.wd_trim_memory() == 0
+    assert lib.fake_live() == base
+    g = Host(lib, dims, params(lib))  # rooms of live handles
+    f64 = params(lib, max_iter=100, mixed=0, eo=0)
+    assert g.masses(f64, 2, 1)[0] == 0
+    with_room = lib.fake_live()
+    assert lib.wd_trim_memory() == 0
+    assert lib.fake_live() == with_room - 14 * _full_field(dims)
+    assert g.masses(f64, 2, 1)[0] == 0
+    assert lib.fake_live() == with_room
+    g.close()
+    one()
+    assert lib.fake_live() > base
+    reset(lib, capacity=lib.fake_live() + (4 << 30))
+    script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
+    one()
+    assert lib.fake_live() == base
