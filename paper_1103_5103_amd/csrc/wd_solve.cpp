@@ -931,12 +931,13 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
         }
         if (host_iters > host_cap) {
             // the device never reported an exit state: stop instead of iterating forever
-            WD_CHECK_HIP(hipStreamSynchronize(st));
-            for (auto& e : S)
-                if (!e.done) {
-                    e.done = true;
-                    e.final_status = WD_ERR_NOCONV;
-                    e.t1 = now_s();
+            sys.download(st);
+            for (int i = 0; i < n; i++)
+                if (!S[i].done) {
+                    S[i].done = true;
+                    S[i].final_status = WD_ERR_NOCONV;
+                    S[i].t1 = now_s();
+                    S[i].rr_true = sys.h[i].rr_true;
                 }
             break;
         }

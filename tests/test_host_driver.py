@@ -345,3 +345,19 @@ def test_memory_of_closed_handles(lib):
     script(lib, 0.1, 0.2, 1.0, 0.0, 0.0)
     one()
     assert lib.fake_live() == base
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_a_solve_that_never_ends_reports_its_last_residual(lib, n):
+    """The host stops a solve whose device never reports an end; the residual it returns is that of the
+    last FP64 update, not 0."""
+    reset(lib)
+    g = Host(lib, (4, 4, 4, 4))
+    script(lib, 0.3, 0.0, 0.0, 0.0, 0.0)
+    lib.fake_ignore_maxit()
+    p = g.params(max_iter=10)
+    code, st = g.batch(p, n) if n > 1 else g.solve(p)
+    assert code == NOCONV
+    assert all(s.status == NOCONV and s.reliable_updates > 0 and s.true_rel_res > 0 for s in st)
+    reset(lib)
+    g.close()
