@@ -77,21 +77,22 @@ __device__ __forceinline__ int calc_chi(const double* tot, double2& chi)
     chi = make_double2(aww.x / awaw, aww.y / awaw);
     return ST_RUNNING;
 }
-// status at the end of iteration iter: its |r|^2 and delta' = <rhat, r>
-__device__ __forceinline__ int calc_status(const SysState* S, int iter, double rr, double2 d1)
+// status at the end of iteration iter: its |r|^2 and delta' = <rhat, r>; maxrr: before it
+__device__ __forceinline__ int calc_status(const SysState* S, int iter, double maxrr, double rr, double2 d1)
 {
     if (!isfinite(rr) || !c_finite(d1)) return ST_NAN;
     if (rr <= S->target2) return ST_CONVERGED;
-    if (S->mixed && rr < S->delta_rel2 * S->maxrr) return ST_RELIABLE;
+    if (S->mixed && rr < S->delta_rel2 * maxrr) return ST_RELIABLE;
     if (iter >= S->maxit) return ST_MAXIT;
     if (c_abs2(d1) == 0.0) return ST_BREAKDOWN;
     return ST_RUNNING;
 }
-__device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int iter, const double* tot, double2& alpha)
+__device__ __forceinline__ int calc_alpha(const SysState* S, double2 delta, int iter, double maxrr, const double* tot,
+                                          double2& alpha)
 {
     const double2 d1 = make_double2(tot[0], tot[1]);
     alpha = c_neg(c_div(c_mul(S->beta, d1), c_mul(delta, S->chi)));
-    return calc_status(S, iter, tot[2], d1);
+    return calc_status(S, iter, maxrr, tot[2], d1);
 }
 // tot: delta', |r|^2
 __device__ __forceinline__ void store_alpha(SysState* S, int iter, const double* tot, double2 alpha, int status)
@@ -133,7 +134,7 @@ __device__ void finish(SysState* S, const double* tot)
         S->chi = chi;
     } else if constexpr (FIN == FIN_ALPHA) {
         double2 alpha;
-        const int iter = S->iter + 1, st = calc_alpha(S, S->delta, iter, tot, alpha);
+        const int iter = S->iter + 1, st = calc_alpha(S, S->delta, iter, S->maxrr, tot, alpha);
         store_alpha(S, iter, tot, alpha, st);
     } else if constexpr (FIN == FIN_CHIALPHA) {
         // delta' = <rhat, r_{n+1}> = <rhat, w> - chi <rhat, A w> and alpha are known before the sweep. <rhat, w>
@@ -152,7 +153,7 @@ __device__ void finish(SysState* S, const double* tot)
     } else if constexpr (FIN == FIN_RR) {
         const int iter = S->iter + 1;
         const double t3[3] = {S->delta.x, S->delta.y, tot[2]};
-        store_alpha(S, iter, t3, S->alpha, calc_status(S, iter, tot[2], S->delta));
+        store_alpha(S, iter, t3, S->alpha, calc_status(S, iter, S->maxrr, tot[2], S->delta));
     } else if constexpr (FIN == FIN_RESTART) {
         S->delta = make_double2(tot[0], tot[1]);
         S->rr = tot[2];
@@ -304,6 +305,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
                     S->beta = beta_d;
                     S->delta_w = S->delta;
                     S->iter_w = S->iter;
+                    S->maxrr_w = S->maxrr;
                 }
             }
             if (st != ST_RUNNING) return;
@@ -402,10 +404,10 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
         }
         double2 alpha_d;
         if constexpr (FOLD) {
-            // delta, iter: this launch changes them, so the blocks take the copies that OP_W left
+            // delta, iter, maxrr: this launch changes them, so the blocks take the copies that OP_W left
             double tot[NRED];
             sum_partials<3>(S->partials, J.rnblk, tot);
-            const int iter = S->iter_w + 1, st = calc_alpha(S, S->delta_w, iter, tot, alpha_d);
+            const int iter = S->iter_w + 1, st = calc_alpha(S, S->delta_w, iter, S->maxrr_w, tot, alpha_d);
             if (lb == 0 && threadIdx.x == 0) store_alpha(S, iter, tot, alpha_d, st);
             if (st != ST_RUNNING) return;
         } else {

@@ -34,7 +34,11 @@ enum SysStatus {
 // Finishers of small launches are folded into the sweep that follows: every block of the sweep adds the
 // partial sums and computes the scalars itself, block 0 stores them (FIN_NONE: no finisher launch).
 // The sweep after a hop writes its own partial sums while it reads the hop's, so the two hops of an
-// iteration use one set each; what a block reads is never written by the same launch.
+// iteration use one set each. What the scalars follow from is never written by the same launch: the
+// last sweep of an iteration changes delta, iter and maxrr and reads the copies that the first one left.
+// The exception is the gate: block 0 may store a status other than RUNNING before another block looks
+// at it. That block then returns at the gate instead of after its own sums, which gave the same status:
+// a sweep of a system that stops writes nothing in either case.
 constexpr int FIN_NONE = -1;
 // Kernel gates are masks of the statuses allowed to run (0: no gating); GATE_RUN = the iteration.
 constexpr int GATE_RUN = 1 << ST_RUNNING;
@@ -122,7 +126,8 @@ struct SysState {
     int dc;            // defect correction: the reliable-update threshold is relative to the
                        // residual at the start of the inner solve (maxrr is not raised)
     double2 delta, beta, chi, alpha;
-    double2 delta_w;   // folded finishers: delta and iter as they were when w was formed
+    double2 delta_w;   // folded finishers: delta, iter and maxrr as they were when w was formed
+    double maxrr_w;
     int iter_w, pad2;
     double rr;         // |r|^2 of the iterated residual
     double maxrr;      // max |r|^2 since the last reliable update
