@@ -611,8 +611,8 @@ static inline dim3 grid1(long nblk) { return dim3((unsigned)nblk); }
     HOP_CASE(SF_, LF_, DAG_, RED_NONE, FIN_STORE)                                                                  \
     HOP_CASE(SF_, LF_, DAG_, RED_NORM, FIN_STORE)                                                                  \
     HOP_CASE(SF_, LF_, DAG_, RED_ZDOT, FIN_BETA)                                                                   \
-    HOP_CASE(SF_, LF_, DAG_, RED_OUTX, FIN_CHI)                                                                    \
-    HOP_CASE(SF_, LF_, DAG_, RED_FULL, FIN_CHI)
+    HOP_CASE(SF_, LF_, DAG_, RED_OUTX, FIN_STORE)                                                                  \
+    HOP_CASE(SF_, LF_, DAG_, RED_FULL, FIN_CHIALPHA)
 // the adjoint hops of the normal equations (CG): the iteration's two, plus the FP64 residual's
 #define HOP_DAG_LO(SF_, LF_)                                                                                       \
     HOP_CASE(SF_, LF_, true, RED_NONE, FIN_STORE)                                                                  \

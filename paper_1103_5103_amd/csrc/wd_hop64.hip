@@ -1,5 +1,5 @@
 // Instantiations and launcher of the single-system hop for FP64 spinors and links (kernel template
-// in wd_hop.hpp): the reliable updates, b_prec, eq. eo3, BiCGstab-M and wd_apply.
+// in wd_hop.hpp): 1/2 D_eo b_o, the start residual, eq. eo3, CG's operator, and (full lattice) BiCGstab-M.
 #include "wd_hop.hpp"
 
 namespace wd {
@@ -19,11 +19,11 @@ hipError_t launch_hop64(bool dag, int lf, int red, const HopJob* jobs, int njobs
 }
 
 // both parities in one launch (k_hop's FULL)
-#define HOP_FULL(LF_, DAG_, RED_)                                                                                  \
-    if (lf == LF_ && dag == DAG_ && red == RED_) {                                                                 \
-        if (tg) hipExtLaunchKernelGGL((k_hop<SF64, LF_, DAG_, RED_, FIN_STORE, true, false, !DAG_, true>),         \
+#define HOP_FULL(LF_, RED_)                                                                                        \
+    if (lf == LF_ && red == RED_) {                                                                                \
+        if (tg) hipExtLaunchKernelGGL((k_hop<SF64, LF_, false, RED_, FIN_STORE, true, false, true, true>),         \
                                       grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, sys, gated, exec); \
-        else hipExtLaunchKernelGGL((k_hop<SF64, LF_, DAG_, RED_, FIN_STORE, true, false, false, true>),            \
+        else hipExtLaunchKernelGGL((k_hop<SF64, LF_, false, RED_, FIN_STORE, true, false, false, true>),           \
                                    grid1(nblocks), dim3(BLOCK), 0, s, ev0, ev1, 0, jobs, njobs, sys, gated, exec); \
         return hipGetLastError();                                                                                  \
     }
@@ -34,19 +34,18 @@ void full_tile(HopJob& j)
     j.bps = slice / BLOCK;
 }
 
-hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
+hipError_t launch_hop_full(int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
                            int gated, hipStream_t s, int* exec, int tg, hipEvent_t ev0, hipEvent_t ev1)
 {
-    if (tg && dag) return hipErrorInvalidValue;  // the adjoint hop runs on the caller's links only
     if (nblocks <= 0) return hipSuccess;
-    HOP_FULL(L64_18, false, RED_ZDOT)
-    HOP_FULL(L64_18, false, RED_OUTX)
-    HOP_FULL(L64_18, false, RED_FULL)
-    HOP_FULL(L64_18, false, RED_NORM)
-    HOP_FULL(L64_12, false, RED_ZDOT)
-    HOP_FULL(L64_12, false, RED_OUTX)
-    HOP_FULL(L64_12, false, RED_FULL)
-    HOP_FULL(L64_12, false, RED_NORM)
+    HOP_FULL(L64_18, RED_ZDOT)
+    HOP_FULL(L64_18, RED_OUTX)
+    HOP_FULL(L64_18, RED_FULL)
+    HOP_FULL(L64_18, RED_NORM)
+    HOP_FULL(L64_12, RED_ZDOT)
+    HOP_FULL(L64_12, RED_OUTX)
+    HOP_FULL(L64_12, RED_FULL)
+    HOP_FULL(L64_12, RED_NORM)
     return hipErrorInvalidValue;
 }
 

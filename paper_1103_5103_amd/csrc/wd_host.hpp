@@ -253,11 +253,12 @@ struct Reports {
 };
 
 // wd_apply_noalloc: a fixed device array per GPU (kNoallocScratchBytes) takes a copy of an input that
-// overlaps the output. The size limit counts a table and two packed fields.
+// overlaps the output (at most 33.5 MB). The largest lattice is a limit of the interface, whether or not
+// a call needs the copy: what it refuses does not depend on how the operator is applied.
 constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;
-constexpr size_t kNoallocTableBytes = (size_t)64 << 10;
+constexpr long kNoallocMaxStride = 87296;  // sites per parity, rounded up to whole blocks
 constexpr int kNoallocMaxDevices = 64;
-size_t noalloc_scratch_need(long stride);
+static_assert((size_t)2 * kNoallocMaxStride * 192 <= kNoallocScratchBytes, "the copy of an input fits");
 void apply_noalloc(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s);
 
 // do two device ranges of this many bytes share an address

@@ -35,7 +35,6 @@ __device__ __forceinline__ double2 c_mul(double2 a, double2 b)
 {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-__device__ __forceinline__ double2 c_add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 c_sub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ double2 c_neg(double2 a) { return make_double2(-a.x, -a.y); }
 __device__ __forceinline__ double2 c_real(double r) { return make_double2(r, 0.0); }
@@ -127,15 +126,6 @@ __device__ void finish(SysState* S, const double* tot)
         const int st = calc_beta(S->delta, tot, beta);
         if (st != ST_RUNNING) return stop(S, st);
         S->beta = beta;
-    } else if constexpr (FIN == FIN_CHI) {
-        double2 chi;
-        const int st = calc_chi(tot, chi);
-        if (st != ST_RUNNING) return stop(S, st);
-        S->chi = chi;
-    } else if constexpr (FIN == FIN_ALPHA) {
-        double2 alpha;
-        const int iter = S->iter + 1, st = calc_alpha(S, S->delta, iter, S->maxrr, tot, alpha);
-        store_alpha(S, iter, tot, alpha, st);
     } else if constexpr (FIN == FIN_CHIALPHA) {
         // delta' = <rhat, r_{n+1}> = <rhat, w> - chi <rhat, A w> and alpha are known before the sweep. <rhat, w>
         // is zero by the choice of beta, but only up to the rounding of the last delta: left out, delta'
@@ -264,7 +254,7 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ partials
 
 template <class T> __device__ __forceinline__ cx<T> cvt(double2 a) { return mk<T>((T)a.x, (T)a.y); }
 
-// FOLD (OP_W, OP_XR, OP_S): the finisher of the preceding reduction is done here, by every block for
+// FOLD (OP_W, OP_S; OP_XR always): the finisher of the preceding reduction is done here, by every block for
 // itself; block 0 stores its results.
 template <int OP, int SFL, bool FOLD = false>
 __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jobs, int njobs,
@@ -332,18 +322,14 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(const SweepJob* __restrict__ jo
             load_spinor<SFL, T, true>(J.f[R_F3], i, w);
         }
         double2 chi_d;
-        if constexpr (FOLD) {
-            double tot[NRED];
-            sum_partials<3>(S->partials2, J.pnblk, tot);
-            const int st = calc_chi(tot, chi_d);
-            if (lb == 0 && threadIdx.x == 0) {
-                if (st != ST_RUNNING) stop(S, st);
-                else S->chi = chi_d;
-            }
-            if (st != ST_RUNNING) return;
-        } else {
-            chi_d = S->chi;
+        double tot[NRED];
+        sum_partials<3>(S->partials2, J.pnblk, tot);
+        const int st = calc_chi(tot, chi_d);
+        if (lb == 0 && threadIdx.x == 0) {
+            if (st != ST_RUNNING) stop(S, st);
+            else S->chi = chi_d;
         }
+        if (st != ST_RUNNING) return;
         if (ok) {
             const cx<T> beta = cvt<T>(S->beta), chi = cvt<T>(chi_d);
 #pragma unroll
@@ -1148,8 +1134,6 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     if (nfin <= 0) return hipSuccess;
     FIN_CASE(3, FIN_STORE)
     FIN_CASE(3, FIN_BETA)
-    FIN_CASE(3, FIN_CHI)
-    FIN_CASE(3, FIN_ALPHA)
     FIN_CASE(3, FIN_RESTART)
     FIN_CASE(4, FIN_UPDATE)
     FIN_CASE(NRED, FIN_CHIALPHA)
@@ -1173,7 +1157,7 @@ hipError_t launch_finish(int nr, int fin, const FinJob* fins, int nfin, SysState
     }
 #define SWEEP_ALL(SF_)                                                                                             \
     SWEEP_CASE(OP_W, SF_)                                                                                          \
-    SWEEP_CASE(OP_XR, SF_) SWEEP_CASE(OP_XRS, SF_) SWEEP_CASE(OP_S, SF_) SWEEP_CASE(OP_INIT, SF_) SWEEP_CASE(OP_ACC, SF_)                 \
+    SWEEP_CASE(OP_XRS, SF_) SWEEP_CASE(OP_S, SF_) SWEEP_CASE(OP_INIT, SF_) SWEEP_CASE(OP_ACC, SF_)                 \
     SWEEP_CASE(OP_CGX, SF_) SWEEP_CASE(OP_CGP, SF_)
 
 hipError_t launch_sweep(int op, int sfl, const SweepJob* jobs, int njobs, long nblocks, SysState* sys, int gated,

@@ -28,7 +28,7 @@ hipError_t launch_hop(int sf, int lf, bool dag, int red, int fin, const HopJob* 
 // of 4 / 8 / 16 / 32 blocks: 460 / 479 / 428 / 435 / 452 us); site order where t-slices are no whole
 // number of blocks.
 void full_tile(HopJob& j);
-hipError_t launch_hop_full(bool dag, int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
+hipError_t launch_hop_full(int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
                            int gated, hipStream_t s, int* exec = nullptr, int tg = 0, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
 // The hop for small launches (tables whose jobs have split set): all formats, the reductions and

@@ -38,18 +38,11 @@ static char* scratch_address()
     return g_scratch_addr[dev];
 }
 
-size_t noalloc_scratch_need(long stride)
-{
-    return kNoallocTableBytes + 2 * field_bytes(SF64, 2, stride);
-}
-
 void apply_noalloc(wd_gauge* g, double kappa, double* out, const double* in, bool dag, hipStream_t s)
 {
-    const Geo& G = g->geo;
-    const size_t need = noalloc_scratch_need(G.stride);
-    if (need > kNoallocScratchBytes)
-        throw Error{WD_ERR_ARG, "lattice too large for wd_apply_noalloc: needs " + std::to_string(need) +
-                                    " bytes of scratch, the library holds " + std::to_string(kNoallocScratchBytes)};
+    if (g->geo.stride > kNoallocMaxStride)
+        throw Error{WD_ERR_ARG, "lattice too large for wd_apply_noalloc: " + std::to_string(g->geo.stride) +
+                                    " sites per parity, at most " + std::to_string(kNoallocMaxStride)};
     const size_t bytes = (size_t)g->V * 24 * sizeof(double);
     if (ranges_overlap(out, in, bytes)) {
         char* copy = scratch_address();

@@ -453,7 +453,8 @@ void run_hop(int sf, int lf, bool dag, int red, int fin, const JobTable<HopJob>&
     if (!t.host.empty() && t.host[0].split) {
         WD_CHECK_HIP(launch_hop_split(sf, lf, dag, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));
     } else if (!t.host.empty() && t.host[0].links_nb) {
-        WD_CHECK_HIP(launch_hop_full(dag, lf, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));
+        if (dag) throw Error{WD_ERR_ARG, "the full-lattice hop has no adjoint"};
+        WD_CHECK_HIP(launch_hop_full(lf, red, t.d(), t.n(), t.nblocks, sys, gated, s, flag, tg, a, b));
     } else if (!t.host.empty() && t.host[0].rhs >= 2) {
         int kmax = 1;
         for (auto& j : t.host) kmax = std::max(kmax, j.ilv);
@@ -519,7 +520,6 @@ void run_sweep(int op, int sfl, const JobTable<SweepJob>& t, SysState* sys, int 
     if (timed) T.push({TK_SWEEP, a, b, bytes, (int)(flag - T.dflags), t.n(), -1});
     if (fold) return;
     switch (op) {
-    case OP_XR: run_finish(3, FIN_ALPHA, t, sys, gated, s); break;
     case OP_XRS: run_finish(3, FIN_RR, t, sys, gated, s); break;
     case OP_INIT:
     case OP_MSINIT: run_finish(3, FIN_RESTART, t, sys, gated, s); break;

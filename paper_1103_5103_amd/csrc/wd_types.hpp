@@ -50,8 +50,6 @@ constexpr int GATE_STOPPED = (1 << ST_CONVERGED) | (1 << ST_RELIABLE) | (1 << ST
 enum Fin {
     FIN_STORE = 0,   // keep the sums in red[] for the host
     FIN_BETA = 1,    // beta = -delta / <rhat, A s>
-    FIN_CHI = 2,     // chi = <A w, w> / <A w, A w>
-    FIN_ALPHA = 3,   // delta' = <rhat, r>, |r|^2, alpha, status (+ the iteration's scalars for the shifts)
     FIN_RESTART = 5, // new residual: delta = <rhat, r>, |r|^2, status RUNNING
     FIN_CGA = 6,     // CG: alpha = |r|^2 / <p, A p>
     FIN_UPDATE = 8,  // FP64 residual update: |r|^2, finished or which way to go on

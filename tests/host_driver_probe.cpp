@@ -272,7 +272,7 @@ hipError_t launch_hop(int, int, bool, int, int, const HopJob*, int njobs, long, 
 {
     return ran(exec, njobs);
 }
-hipError_t launch_hop_full(bool, int, int, const HopJob*, int njobs, long, SysState*, int, hipStream_t, int* exec, int,
+hipError_t launch_hop_full(int, int, const HopJob*, int njobs, long, SysState*, int, hipStream_t, int* exec, int,
                            hipEvent_t, hipEvent_t)
 {
     return ran(exec, njobs);
