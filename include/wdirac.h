@@ -311,7 +311,7 @@ wd_status wd_last_error(char* buf, size_t n);
  * while timing is on.
  * class: 0 = low-precision even-odd hop, 1 = FP64 hop, 2 = fused vector sweeps,
  *        3 = the small finisher kernels that complete the reductions, 4 + r = the low-precision
- *        hops with fused reduction r (WD_RED_NONE .. WD_RED_NORM; 8: <out, x0>, |out|^2 and <z, out>;
+ *        hops with fused reduction r (WD_RED_NONE .. WD_RED_NORM; 8: <out, x0>, |out|^2, <z, out> and <z, x0>;
  *        also counted in class 0).
  * bytes: the compulsory bytes of the counted launches (launches in which every system was gated
  *        off are not counted).

@@ -24,9 +24,11 @@ hipError_t launch_hop(int sf, int lf, bool dag, int red, int fin, const HopJob* 
 // FP64 hop of both parities of full-lattice fields (every job with links_nb set, its two parities
 // in one group); red: one of the fused reductions
 // Block order of such a launch: t fastest within groups of 8 blocks (2048 sites of each parity), so
-// that the t neighbours' spinors and links are still in L2 (32^3x64, <rhat, A s> in site order / groups
-// of 4 / 8 / 16 / 32 blocks: 460 / 479 / 428 / 435 / 452 us); site order where t-slices are no whole
-// number of blocks.
+// that the t neighbours' spinors and links are still in L2; site order where t-slices are no whole
+// number of blocks. Measured, all hops of a BiCGstab-M solve in site order / groups of 2 / 4 / 8 / 16 / 32 blocks, us:
+// 16^3x32 30.4 / 30.1 / 30.1 / 30.9 / 30.6 / 30.8, 16^2x32^2 63.9 / 55.6 / 54.8 / 57.5 / 64.0 / 64.0, 24^3x48 175 / 169 / 159 /
+// 160 / 168 / 176, 32^4 276 / 275 / 254 / 237 / 249 / 272, 48x24^3 183 / 179 / 171 / 166 / 174 / 182, 32^3x64 538 / 596 / 508 / 468 /
+// 480 / 540.
 void full_tile(HopJob& j);
 hipError_t launch_hop_full(int lf, int red, const HopJob* jobs, int njobs, long nblocks, SysState* sys,
                            int gated, hipStream_t s, int* exec = nullptr, int tg = 0, hipEvent_t ev0 = nullptr,

@@ -9,9 +9,10 @@
 //  * multimass : heaviest mass first, polynomial start guess (Sec. 6.2.1, Sec. 7).
 //
 // All kernels of an iteration are queued without host round trips: the BiCGstab scalars live on
-// the device and each kernel skips systems that are no longer RUNNING. The host reads the
-// per-system status every `poll` iterations and performs reliable updates, restarts and
-// convergence checks.
+// the device and each kernel skips systems that are no longer RUNNING. In the even-odd BiCGstab the
+// host queues one iteration (or one captured chunk) at a time, watches the systems' reports in host memory and
+// queues the FP64 updates; their outcome is decided on the device. CG and the multi-shift solvers read the
+// records every `poll` iterations, and CG's host performs the updates and checks.
 #include <algorithm>
 #include <type_traits>
 #include <chrono>
@@ -504,7 +505,12 @@ static int tune_shared_hops(const std::vector<Sys>& S, int SFL, int LFL, int L64
 // sums of its system: worth it while the launch is bound by latency, that is up to about 4 blocks per CU.
 // Measured with / without: 8^4 one mass 911 / 963 us, 10x6x14x18 FP64 691 / 820 us, 16^3x32 six masses
 // 4.20 / 4.50 ms, BiCGstab-M 16^3x32 (512 blocks) 3.27 / 3.62 ms; at 32^3x64 (4096 blocks
-// and as many partial sums) a finisher of its own takes 7 us of 80.
+// and as many partial sums) a finisher of its own takes 7 us of 80. Around the line, one mass with
+// FP32 / FP16 / FP64 spinors, then BiCGstab-M of two masses, us with / without: 384 blocks 1271 / 1307, 1214 / 1262,
+// 1848 / 1897; 512 blocks 1484 / 1498, 1366 / 1410, 2191 / 2243; 768 blocks 2233 / 2240, 2046 / 2063, 3436 / 3423, 4258 /
+// 4225; 1024 blocks 2613 / 2626, 2274 / 2148, 4152 / 4152, 5330 / 5185; 1536 blocks 4397 / 4266, 3783 / 3731, 6183 / 6121,
+// 7785 / 7406; 2048 blocks 5238 / 5040, 4563 / 4411, 8135 / 7976, 10916 / 10279. (Without, x, r and s are updated in
+// one sweep, too.)
 constexpr long kFoldBlocks = 1024;
 static bool fold_finishers(const JobTable<SweepJob>& t) { return t.nblocks <= kFoldBlocks; }
 
@@ -551,9 +557,9 @@ static void prepare_source(wd_gauge* g, const std::string& key, const double* b,
     src.bb = -1;
 }
 
-// Iterations queued between host checks of the systems' status in the even-odd solver (measured
-// best of 2/3/4/6/8 at 16^3x32 and 32^3x64: fewer means more round trips, more means more gated
-// launches after a system has stopped).
+// Iterations of a captured chunk (graph replay) in the even-odd BiCGstab, and between the host's looks at
+// the records in CG (measured there as the best of 2/3/4/6/8 at 16^3x32 and 32^3x64: fewer means more
+// round trips, more means more gated launches after a system has stopped).
 constexpr int kPoll = 3;
 
 // Returns with the last kernels (the unpacking) queued; the caller ends with rep.finish(). The reports
@@ -824,8 +830,8 @@ static void eo_solve(std::vector<EoSys>& S, const wd_solver_params& P, hipStream
     auto iterate = [&](hipStream_t q) {
         if (!fold) {
             // bound by memory: alpha from the second hop's sums, x, r and s in one sweep, 2 spinor passes of
-            // 25 less (32^3x64 eight masses 42.7 -> 42.2 ms, 96 systems 31.4 -> 30.2 ms, 24^3x48 six masses at
-            // once 1.027 -> 1.076 of the former rate, BiCGstab-M 32^3x64 51.5 -> 47.4 ms)
+            // 25 less (32^3x64 eight masses 42.7 -> 42.2 ms, 96 systems 31.4 -> 30.2 ms, BiCGstab-M 32^3x64 51.5 ->
+            // 47.4 ms; <rhat, w> among those sums costs 96 systems 0.3 ms of 30.6, the others nothing)
             run_hop(SFL, LFL, false, RED_NONE, FIN_STORE, H1, sys.d(), GATE_RUN, q, bH1);
             run_hop(SFL, LFL, false, RED_ZDOT, FIN_BETA, H2, sys.d(), GATE_RUN, q, bH2);
             run_sweep(OP_W, SFL, SW, sys.d(), GATE_RUN, q, bSW);

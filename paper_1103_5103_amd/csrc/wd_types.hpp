@@ -46,7 +46,7 @@ constexpr int GATE_RUN = 1 << ST_RUNNING;
 constexpr int GATE_GOES_ON = (1 << ST_RELIABLE) | (1 << ST_BREAKDOWN);
 constexpr int GATE_STOPPED = (1 << ST_CONVERGED) | (1 << ST_RELIABLE) | (1 << ST_BREAKDOWN) | (1 << ST_MAXIT);
 
-// Finisher kinds (what the last block does with the reduced sums)
+// Finisher kinds (what follows from the reduced sums)
 enum Fin {
     FIN_STORE = 0,   // keep the sums in red[] for the host
     FIN_BETA = 1,    // beta = -delta / <rhat, A s>

@@ -1,7 +1,9 @@
-"""FP64 operators on both parities in one launch (wd_apply, wd_apply_dag, BiCGstab-M): forward links
-only, the two parities' blocks in turn, blocks ordered t fastest in groups of a t-slice. Shapes at the
-edges of that order: slices of 9 blocks (a smaller last group), of exactly one group, of one block, of
-no whole number of blocks, T = 2, and the smallest lattice; links that are not SU(3) too.
+"""FP64 operators on both parities in one launch: wd_apply and wd_apply_dag (on the caller's fields,
+links that are not SU(3) too), and BiCGstab-M, whose final residuals take the full-lattice hop (forward
+links only, the two parities' blocks in turn, blocks ordered t fastest in groups of a t-slice) on every
+lattice and whose iteration does so above 16384 sites, here 8x16x36x4. Shapes at the edges of that order:
+slices of 9 blocks (a smaller last group), of exactly one group, of one block, of no whole number of
+blocks, T = 2, and the smallest lattice.
 
 Tolerance: one application has about 150 rounded FP64 terms per component, of comparable size:
 150 x 1.1e-16 < 2e-14 relative to the largest component.

@@ -1,11 +1,9 @@
 """wd_apply_noalloc, the operator application for callers that cannot allocate, against wd_apply.
 
-The two run the same kernels with the same launch configuration, so the results must be bitwise
-equal; the allocation-free entry point keeps its packed fields and job table in the library's
-fixed per-GPU array, which holds the previous call's contents: two calls in a row, the second on a
-smaller lattice, must each give wd_apply's result. Free device memory must not change across
-calls once each kind of call has run (the library makes no allocation), and a lattice too large
-for the array is refused.
+The two run the same kernel with the same launch configuration, so the results must be bitwise
+equal: two calls in a row, the second on a smaller lattice, must each give wd_apply's result. Free
+device memory must not change across calls once each kind of call has run (the library makes no
+allocation), and a lattice above the interface's limit is refused.
 """
 import numpy as np
 import pytest
