@@ -221,8 +221,8 @@ struct Reports {
     ~Reports();
     void finish()
     {
-        drained = true;
         WD_CHECK_HIP(hipStreamSynchronize(st));
+        drained = true;
     }
     Reports(const Reports&) = delete;
     Reports& operator=(const Reports&) = delete;

@@ -39,11 +39,12 @@ def lib(tmp_path_factory):
     so = str(d / "libhost.so")
     # -Bsymbolic: the stand-in's HIP calls, whatever else the process has loaded
     subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-o", so, *objs], check=True, capture_output=True)
-    os.environ["WD_TUNE_CACHE"] = str(d / "tune.txt")
     L = ctypes.CDLL(so)
     for f in ("fake_live", "fake_peak", "wd_gauge_device_bytes"):
         getattr(L, f).restype = ctypes.c_size_t
-    return L
+    with pytest.MonkeyPatch.context() as m:
+        m.setenv("WD_TUNE_CACHE", str(d / "tune.txt"))
+        yield L
 
 
 class Host:
